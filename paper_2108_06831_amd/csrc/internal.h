@@ -102,6 +102,7 @@ struct SkinnyDesc {
   int32_t gidx[1 << kSkinnyMaxG];   // G element of (b, m, k), b slowest
   int32_t bt_pos[kSkinnyMaxG];      // position in T of G's batch bit j
   int32_t g_unit;                   // G is a diagonal gate whose entries all have modulus one
+  int32_t g_signs;                  // diagonal with known entries +-1: bit b set where entry b is -1; else -1
   int32_t g_form;                   // shape of G's values that fewer multiplies serve (kForm*), from the gate kinds
 };
 
@@ -135,6 +136,7 @@ struct SweepGateDesc {
                          // the chunk is -(address position + 1)
   int32_t rb[2];         // dense gates: index in the segment's register bits of bit j
   int32_t unit;          // diagonal with unit-modulus entries
+  int32_t signs;         // SkinnyDesc::g_signs
   int32_t g_buf;
   int32_t form;          // GateForm of the values
   int32_t voff;          // the gate's values in the chain's value table: dense (m, k) row-major, diagonal by b
@@ -174,7 +176,56 @@ struct SweepPass {
   int32_t n_red;  // adjoint passes: gradient accumulators of the pass
   int32_t ctab_off = 0, ctab_n = 0;  // the pass's power tables in the chain's value table
   int32_t val_off = 0;               // the pass's first gate value (its values run up to ctab_off + ctab_n)
+  int32_t reg_seg = -1;              // the pass's first RegSeg, or -1: not in register form
 };
+
+// A pass in register form (k_sweep_regs, k_adjoint_regs): the chunk stays in
+// registers, sixteen elements per thread and state, and LDS only carries it
+// from one segment's layout to the next.  The planner rewrites the pass's gate
+// list as operations whose control flow is the same for the whole launch:
+// bits are address positions (the kernel tests them in the element index of
+// the thread's register combination 0), runs of gates are one operation, and
+// everything known on the host is resolved.  A pass qualifies with a chunk of
+// 2^kSweepMaxLocal elements on a state of at most 2^32 that holds dense
+// one-qubit gates, diagonals with known signs, unit diagonals (in the adjoint:
+// with at most one bit in the registers, of one qubit) and, forward, count groups.
+struct RegSeg {
+  int32_t rbits[4];
+  int32_t tpos[8], gpos[8];  // thread bit t -> local bit, address position
+  int32_t rgpos[4];          // register bit j -> address position
+  int32_t physoff[16];       // as in SweepSegment
+  int32_t sign_off, n_sign;  // words p | q << 8: the thread's factor is negated where address bits p and q are 1
+  int32_t phase_off, n_phase;
+  int32_t op_off, n_op;
+  int32_t ph_used;           // the thread's factor may differ from 1
+  int32_t lead_sums;         // adjoint: a leading phase has a gradient term
+};
+// a diagonal gate with no bit in the registers: one factor per thread
+struct RegPhase {
+  int32_t p[2];     // address positions of the index bits (p[1] = -1: one bit)
+  int32_t src;      // forward: offset in the value table; adjoint: 16 * gate
+  int32_t red;      // adjoint: gradient accumulator, or -1
+  float q[4];       // adjoint: the generator's (real) diagonal
+};
+// operation types (one flag each: the kernels test them in turn)
+enum RegOpType { REG_REAL = 1, REG_RXLIKE = 2, REG_DENSE = 4, REG_SIGNS = 8, REG_DIAG = 16, REG_DIAG2 = 32, REG_COUNT = 64 };
+struct RegOp {
+  int32_t type;
+  int32_t mask;         // SIGNS: register combinations negated on every thread; DIAG and dense gates (REAL, RXLIKE,
+                        // DENSE: shape of their values): register bits of the gates
+  int32_t form;         // DIAG2 with both bits in the registers: k0 | k1 << 8
+  int32_t off, n, n2;   // words (SIGNS: p | ones << 16: the combinations `ones` negated where address bit p
+                        // is 1; COUNT: n edges p | q << 8 between address bits, n2 edges p | j << 8 from register bit j)
+  int32_t sums;         // adjoint DIAG: form the gradient sums anew
+  int32_t other;        // DIAG2: -1, or p | which << 8: index bit `which` is address bit p (the other: mask)
+  int32_t src[4];       // per register bit: the gate's values (as RegPhase::src); COUNT: src[0] the power table
+  int32_t red[4];       // adjoint, per register bit: gradient accumulator, or -1
+  int32_t gform[4];     // adjoint dense, per register bit: AdjForm of the generator
+  float g0[4], g1[4];   // adjoint, per register bit: DIAG the generator's entries; dense with ADJ_GEN_X its factor in g0
+  int32_t tot;          // COUNT: per register bit (bytes) its edges to address bits
+  int32_t pc[3];        // COUNT: edges between register bits, per unordered pair (bytes, see count_pair)
+};
+static_assert(sizeof(RegOp) == 128 && sizeof(RegPhase) == 32 && sizeof(RegSeg) % 16 == 0, "read with wide scalar loads");
 
 // Reverse sweep of the adjoint gradient in fused passes: psi and lambda
 // chunks of 2^l elements stay in LDS while every gate of the pass is undone
@@ -418,6 +469,11 @@ struct tn_path {
   std::shared_ptr<tn_network> sliced_net;
   std::vector<int32_t> slice_modes;
   std::vector<tnq::SliceTensor> slice_tensors;
+  // passes in register form (SweepPass::reg_seg), of the forward chains and of the adjoint
+  std::vector<tnq::RegSeg> reg_segs, adj_reg_segs;
+  std::vector<tnq::RegOp> reg_ops, adj_reg_ops;
+  std::vector<tnq::RegPhase> reg_phases, adj_reg_phases;
+  std::vector<uint32_t> reg_words, adj_reg_words;
   // Q3.28 fixed-point program (q_state 1: built; -1: a step exceeds the kernel's bit limits)
   int32_t q_state = 0;
   std::vector<tnq::QStep> q_steps;
@@ -439,6 +495,9 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
 std::vector<int32_t> output_layout(const tn_network* net);
 // fused passes of the adjoint sweep over the path's final tensor (sets path->adj_state)
 void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<int32_t>& slot_of_gate);
+// regpass.cpp: the register form of a planned pass on a 2^R state (see RegSeg); sets ps.reg_seg
+void build_reg_pass(tn_path* path, SweepPass& ps, int R);
+void build_adj_reg_pass(tn_path* path, SweepPass& ps, int R);
 // moves every step that is small and depends only on inputs or such steps to the
 // front; of the rest, likely per-output products that are ready together are
 // placed next to each other

@@ -109,6 +109,16 @@ hipError_t launch_small_steps(hipStream_t s, const SmallStep* steps, const int32
 hipError_t launch_sweep_pass(hipStream_t s, const SweepPass& ps, int bits, const SweepGateDesc* gates_dev,
                              const SweepSegment* segs_dev, const float2* in, int64_t in_bs, float2* out,
                              int64_t out_bs, const float2* vals, int64_t vals_bs, int batch, int precision);
+// The same for a pass in register form (SweepPass::reg_seg >= 0; complex64 only).
+struct RegTables {
+  const RegSeg* segs;
+  const RegOp* ops;
+  const RegPhase* phases;
+  const uint32_t* words;
+};
+hipError_t launch_sweep_regs(hipStream_t s, const SweepPass& ps, int bits, const RegTables& t, const float2* in,
+                             int64_t in_bs, float2* out, int64_t out_bs, const float2* vals, int64_t vals_bs,
+                             int batch);
 // out[z][i] = value i of a chain's table: src[i] = element offset | (BUF_IN or BUF_WS) << 56.
 hipError_t launch_gather_vals(hipStream_t s, const int64_t* src, int n, const float2* IN, int64_t in_bs,
                               const float2* WS, int64_t ws_bs, float2* out, int64_t out_bs, int batch);
@@ -149,6 +159,11 @@ hipError_t launch_adjoint_pass(hipStream_t s, const SweepPass& ps, int bits, con
                                const SweepSegment* segs_dev, const float2* u, int64_t u_bs, float2* psi,
                                int64_t psi_bs, float2* lam, int64_t lam_bs, int batch, double* partials,
                                int64_t partial_stride, int precision);
+// The same for a pass in register form (complex64 only).
+hipError_t launch_adjoint_regs(hipStream_t s, const SweepPass& ps, int bits, const RegTables& t,
+                               const AdjGateDesc* gates_dev, const float2* u, int64_t u_bs, float2* psi,
+                               int64_t psi_bs, float2* lam, int64_t lam_bs, int batch, double* partials,
+                               int64_t partial_stride);
 // grad[z][p] = scale_z * sum over slots with param p and blocks of partials
 hipError_t launch_gradient_reduce(hipStream_t s, const double* partials, int64_t partial_stride, int n_slots,
                                   const int32_t* slot_param, int n_params, const double* grad_out, int batch,

@@ -430,6 +430,10 @@ void build_chains(tn_path* path, int T) {
   path->segments.clear();
   path->sweep_gates.clear();
   path->sweep_val_src.clear();
+  path->reg_segs.clear();
+  path->reg_ops.clear();
+  path->reg_phases.clear();
+  path->reg_words.clear();
   const int S = (int)path->steps.size();
   auto sweepable = [&](int s) {
     const StepProgram& P = path->steps[s];
@@ -497,6 +501,7 @@ void build_chains(tn_path* path, int T) {
         }
         gd.g_buf = d.g.buf;
         gd.unit = gd.diag ? d.g_unit : 0;
+        gd.signs = gd.diag ? d.g_signs : -1;
         gd.form = d.g_form;
         gd.g_off = d.g.off;
         for (int j = 0; j < 16; ++j) gd.gidx[j] = 0;
@@ -600,6 +605,7 @@ void build_chains(tn_path* path, int T) {
       ps.ctab_off = (int32_t)path->sweep_val_src.size() - ch.first_val;
       ps.ctab_n = (int32_t)ctab.size();
       path->sweep_val_src.insert(path->sweep_val_src.end(), ctab.begin(), ctab.end());
+      build_reg_pass(path, ps, R);
       path->passes.push_back(ps);
     }
     ch.n_passes = (int32_t)path->passes.size() - ch.first_pass;
@@ -918,6 +924,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
       // the gate tensor's value shape, from its gate kinds: unit-modulus or +-1 diagonals; real or
       // RX-like one-qubit matrices (products of real matrices are real, of RX-like ones RX-like)
       d.g_unit = 0;
+      d.g_signs = -1;
       d.g_form = kFormGeneric;
       {
         const int gid = a_small ? ia : ib;
@@ -937,6 +944,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
           if (d.nk == 0 && d.nm == 0 && r.diag && whole) {
             d.g_unit = unit ? 1 : 0;
             d.g_form = signs ? kFormSigns : unit ? kFormUnit : kFormGeneric;
+            if (signs && r.op_end - r.op_begin == 1) d.g_signs = net->ops[r.op_begin].kind == TN_GATE_CZ ? 8 : 2;
             if (d.nb == 2 && r.nq == 2 && r.op_end - r.op_begin == 1 && net->ops[r.op_begin].kind == TN_GATE_ZZPHASE) {
               P.zz_param = net->ops[r.op_begin].param[0];
               P.zz_angle = P.zz_param >= 0 ? 0.0 : net->ops[r.op_begin].angle[0];
@@ -1387,6 +1395,10 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
   path->adj_passes.clear();
   path->adj_segments.clear();
   path->adj_gates.clear();
+  path->adj_reg_segs.clear();
+  path->adj_reg_ops.clear();
+  path->adj_reg_phases.clear();
+  path->adj_reg_words.clear();
   path->adj_state = -1;
   const int R = (int)path->final_bits.size();
   // whole waves for the gradient reductions need chunks of 2^10 elements at least
@@ -1526,6 +1538,7 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
       path->adj_segments.push_back(seg);
     }
     ps.n_segs = (int32_t)pp.segs.size();
+    build_adj_reg_pass(path, ps, R);
     path->adj_passes.push_back(ps);
   }
   path->adj_state = 1;

@@ -218,8 +218,16 @@ struct DevPath {
   SweepSegment* segments = nullptr;
   int64_t* sweep_val_src = nullptr;
   SliceTensor* slice_tensors = nullptr;
+  RegSeg* reg_segs = nullptr;           // passes in register form
+  RegOp* reg_ops = nullptr;
+  RegPhase* reg_phases = nullptr;
+  uint32_t* reg_words = nullptr;
   AdjGateDesc* adj_gates = nullptr;     // uploaded on the first backward call
   SweepSegment* adj_segments = nullptr;
+  RegSeg* adj_reg_segs = nullptr;
+  RegOp* adj_reg_ops = nullptr;
+  RegPhase* adj_reg_phases = nullptr;
+  uint32_t* adj_reg_words = nullptr;
 };
 
 static tn_status ensure_path_device(tn_path* path, DevPath** out) {
@@ -239,6 +247,10 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   HIP_TRY(upload(&d->segments, path->segments));
   HIP_TRY(upload(&d->sweep_val_src, path->sweep_val_src));
   HIP_TRY(upload(&d->slice_tensors, path->slice_tensors));
+  HIP_TRY(upload(&d->reg_segs, path->reg_segs));
+  HIP_TRY(upload(&d->reg_ops, path->reg_ops));
+  HIP_TRY(upload(&d->reg_phases, path->reg_phases));
+  HIP_TRY(upload(&d->reg_words, path->reg_words));
   *out = d;
   return TN_OK;
 }
@@ -257,6 +269,9 @@ void device_release_path(tn_path* path) {
   (void)hipFree(d->segments);
   (void)hipFree(d->sweep_val_src);
   (void)hipFree(d->slice_tensors);
+  for (void* p : {(void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
+                  (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words})
+    (void)hipFree(p);
   (void)hipFree(d->adj_gates);
   (void)hipFree(d->adj_segments);
   (void)hipSetDevice(cur);
@@ -371,8 +386,12 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
       for (int k = 0; k < ch.n_passes; ++k) {
         const SweepPass& ps = path->passes[ch.first_pass + k];
         hipEvent_t ev = prof_start(s, TN_KERNEL_SWEEP);
-        HIP_TRY(launch_sweep_pass(s, ps, ch.bits, dp->sweep_gates, dp->segments, k == 0 ? ip : op,
-                                  k == 0 ? ibs : obs, op, obs, vals, vbs, batch, precision));
+        if (ps.reg_seg >= 0 && precision == TN_PREC_C64 && vals)
+          HIP_TRY(launch_sweep_regs(s, ps, ch.bits, RegTables{dp->reg_segs, dp->reg_ops, dp->reg_phases, dp->reg_words},
+                                    k == 0 ? ip : op, k == 0 ? ibs : obs, op, obs, vals, vbs, batch));
+        else
+          HIP_TRY(launch_sweep_pass(s, ps, ch.bits, dp->sweep_gates, dp->segments, k == 0 ? ip : op,
+                                    k == 0 ? ibs : obs, op, obs, vals, vbs, batch, precision));
         double fl = 0;
         for (int g = 0; g < ps.n_gates; ++g) {
           const SweepGateDesc& gd = path->sweep_gates[ps.first_gate + g];
@@ -1226,6 +1245,10 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     if (!dp->adj_gates) {
       HIP_TRY(upload(&dp->adj_gates, path->adj_gates));
       HIP_TRY(upload(&dp->adj_segments, path->adj_segments));
+      HIP_TRY(upload(&dp->adj_reg_segs, path->adj_reg_segs));
+      HIP_TRY(upload(&dp->adj_reg_ops, path->adj_reg_ops));
+      HIP_TRY(upload(&dp->adj_reg_phases, path->adj_reg_phases));
+      HIP_TRY(upload(&dp->adj_reg_words, path->adj_reg_words));
     }
     const int bits = (int)path->final_bits.size();
     for (const SweepPass& ps : path->adj_passes) {
@@ -1238,9 +1261,14 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
         fl += 2.0 * per * (double)n + (gd.red >= 0 ? 8.0 * (double)n : 0.0);
       }
       hipEvent_t ev = prof_start(s, TN_KERNEL_ADJOINT);
-      HIP_TRY(launch_adjoint_pass(s, ps, bits, dp->adj_gates, dp->adj_segments, umats,
-                                  (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride,
-                                  precision));
+      if (ps.reg_seg >= 0 && precision == TN_PREC_C64)
+        HIP_TRY(launch_adjoint_regs(
+            s, ps, bits, RegTables{dp->adj_reg_segs, dp->adj_reg_ops, dp->adj_reg_phases, dp->adj_reg_words},
+            dp->adj_gates, umats, (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride));
+      else
+        HIP_TRY(launch_adjoint_pass(s, ps, bits, dp->adj_gates, dp->adj_segments, umats,
+                                    (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride,
+                                    precision));
       prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * batch, fl * batch);
     }
   }

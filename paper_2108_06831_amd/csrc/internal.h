@@ -261,6 +261,78 @@ struct SweepChain {
   BufRef vals;
 };
 
+// Ordered passes over a small state (k_seq_pass): the gates of a sequential
+// contraction that starts at |0...0>, or of a reverse sweep, applied one by one
+// in their given order with the arithmetic of a step-by-step contraction.  A
+// block keeps a chunk of 2^l elements in registers, sixteen per thread, in
+// segments as the fused passes do; a state of at most 2^kSeqMaxLocal elements
+// is one chunk and its whole chain one launch.
+constexpr int kSeqMinBits = 5, kSeqMaxBits = 15;  // states of a forward chain
+constexpr int kSeqMaxLocal = 14;                  // widest chunk, forward
+constexpr int kSeqAdjMaxBits = 17;                // states of a reverse sweep
+constexpr int kSeqAdjMaxLocal = 13;               // widest chunk of a reverse sweep (two states)
+constexpr int kSeqMinRun = 12;                    // gates of a forward chain at least
+struct SeqSeg {
+  int32_t tpos[10], gpos[10];  // thread bit t -> local bit, address position
+  int32_t rgpos[4];            // register bit j -> address position
+  int32_t physoff[16];         // LDS slot offsets of the register combinations (as in SweepSegment)
+  int32_t op_off, n_op;
+  int32_t pad[6];
+};
+enum SeqOpType { SEQ_BITS = 1, SEQ_DIAG = 2, SEQ_SIGNS = 4, SEQ_DENSE2 = 8 };
+struct SeqOp {
+  int32_t type;
+  // BITS: register bits (lowest first) with a dense gate (mask) and then a one-bit diagonal (dmask).
+  // SIGNS: combinations negated on every thread.  DIAG: the gate's qubits (1 or 2).  DENSE2: register bits 2 mask, 2 mask + 1.
+  int32_t mask, dmask;
+  int32_t gfirst;        // the gate is the products' first operand: BITS bits 0-3 dense, 4-7 diagonal; else bit 0
+  int32_t off, n;        // SIGNS: words p | q << 8 | ones << 16: `ones` negated where address bits p and q are 1
+  int32_t ones;          // DIAG: entries known to be exactly 1 (bit b)
+  int32_t gen;           // DIAG, adjoint: GenKind
+  int32_t src[4];        // values: BITS dense, per register bit; else src[0]
+  int32_t dsrc[4];       // BITS: the diagonals'.  DIAG: k0, k1 (register bits or -1), p0, p1 (address positions)
+  int32_t form[4];       // BITS: GateForm of the dense values
+  int32_t red[4];        // adjoint: gradient slot or -1 (DIAG: red[0])
+  int32_t dred[4];       // BITS, adjoint: of the diagonals
+  int32_t gform[4];      // BITS, adjoint: GenKind of the dense gates
+  uint32_t perm[2];      // DENSE2, forward: entry e = 4 m + k is value (perm[e / 8] >> 4 (e % 8)) & 15
+  int32_t pad[6];
+};
+static_assert(sizeof(SeqOp) == 160 && sizeof(SeqSeg) == 192, "read with wide scalar loads");
+struct SeqPass {
+  int32_t l;
+  int8_t lpos[kSeqMaxLocal];
+  int32_t first_seg, n_segs;
+};
+struct SeqProgram {
+  std::vector<SeqPass> passes;
+  std::vector<SeqSeg> segs;
+  std::vector<SeqOp> ops;
+  std::vector<uint32_t> words;
+};
+// one gate of an ordered pass
+struct SeqItem {
+  int n = 1;
+  int pos[2] = {0, 0};  // address position of bit j of the gate's own index
+  bool diag = false;
+  bool gate_first = true;
+  int src = 0;          // forward: offset of its values in the input buffer; adjoint: 16 * gate
+  uint64_t perm = 0;    // dense two-qubit gates: nibble 4 m + k names the value of entry (m, k)
+  int form = 0;         // dense: GateForm
+  int signs = -1;       // diagonal of known entries +-1: 2 (Z) or 8 (CZ)
+  int ones = 0;         // two-bit diagonals: entries known to be exactly 1
+  int gen = GEN_NONE, red = -1;
+};
+struct SeqChain {
+  int32_t end = 0;      // steps [0, end) are the chain (0: none)
+  int32_t bits = 0;
+  bool last = false;    // the chain ends the path
+  BufRef out;           // result of step end - 1
+  std::vector<int32_t> in_bits, out_bits;  // layouts of the running state and of the result
+  double flops = 0;
+  SeqProgram prog;
+};
+
 struct PermuteDesc {
   BufRef in, out;
   int32_t bits;                 // total address bits
@@ -454,7 +526,8 @@ struct tn_path {
   std::vector<tnq::SweepSegment> segments;
   std::vector<tnq::SweepGateDesc> sweep_gates;
   std::vector<int64_t> sweep_val_src;        // gate values of the chains: element offset | (buffer << 56)
-  // adjoint gradient passes over the final tensor (built on first use; adj_state 1: built, -1: not possible)
+  // adjoint gradient passes over the final tensor (built on first use; adj_state 1: fused passes, 2: ordered
+  // passes, -1: not possible)
   int32_t adj_state = 0;
   // the layout (labels, C order) the passes run in: the final tensor's, or the qubit order when
   // that needs fewer passes (adj_perm = 1: the state is permuted into it first)
@@ -474,6 +547,9 @@ struct tn_path {
   std::vector<tnq::RegOp> reg_ops, adj_reg_ops;
   std::vector<tnq::RegPhase> reg_phases, adj_reg_phases;
   std::vector<uint32_t> reg_words, adj_reg_words;
+  // the path's leading steps as ordered passes; the reverse sweep as ordered passes (adj_state 2)
+  tnq::SeqChain seq;
+  tnq::SeqProgram adj_seq;
   // Q3.28 fixed-point program (q_state 1: built; -1: a step exceeds the kernel's bit limits)
   int32_t q_state = 0;
   std::vector<tnq::QStep> q_steps;
@@ -498,6 +574,8 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
 // regpass.cpp: the register form of a planned pass on a 2^R state (see RegSeg); sets ps.reg_seg
 void build_reg_pass(tn_path* path, SweepPass& ps, int R);
 void build_adj_reg_pass(tn_path* path, SweepPass& ps, int R);
+// seqpass.cpp: ordered passes over `items` on a 2^R state, chunks of at most 2^lmax elements
+bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, SeqProgram* out);
 // moves every step that is small and depends only on inputs or such steps to the
 // front; of the rest, likely per-output products that are ready together are
 // placed next to each other

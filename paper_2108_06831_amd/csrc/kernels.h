@@ -154,7 +154,12 @@ hipError_t launch_adjoint_step(hipStream_t s, const SweepArgs& a, const float2* 
 // each, per parameter vector): for every gate of the pass, in order, its
 // gradient term (if any) into partials[z][slot][block], then both states
 // undone by U^dagger.  U: [batch][u_bs] matrices, 16 complex64 per gate.
-// Grid: kReduceBlocks blocks per parameter vector, each taking chunks in turn.
+// Grid: adjoint_blocks() blocks per parameter vector, each taking chunks in
+// turn and writing one column of partials.
+inline int adjoint_blocks(const SweepPass& ps, int bits) {
+  return bits - ps.l >= 9 ? kReduceBlocks : 1 << (bits - ps.l);
+}
+static_assert(kReduceBlocks == 1 << 9, "adjoint_blocks");
 hipError_t launch_adjoint_pass(hipStream_t s, const SweepPass& ps, int bits, const AdjGateDesc* gates_dev,
                                const SweepSegment* segs_dev, const float2* u, int64_t u_bs, float2* psi,
                                int64_t psi_bs, float2* lam, int64_t lam_bs, int batch, double* partials,
@@ -164,9 +169,27 @@ hipError_t launch_adjoint_regs(hipStream_t s, const SweepPass& ps, int bits, con
                                const AdjGateDesc* gates_dev, const float2* u, int64_t u_bs, float2* psi,
                                int64_t psi_bs, float2* lam, int64_t lam_bs, int batch, double* partials,
                                int64_t partial_stride);
-// grad[z][p] = scale_z * sum over slots with param p and blocks of partials
-hipError_t launch_gradient_reduce(hipStream_t s, const double* partials, int64_t partial_stride, int n_slots,
-                                  const int32_t* slot_param, int n_params, const double* grad_out, int batch,
+// One ordered pass over a small state (SeqPass): forward from `in` (NULL: from
+// |0...0>) to `out`, address bit p of the state at position out_pos[p] of the
+// result (NULL: p; `last`: the pass's last segment); vals: the network's input
+// tensors.  Reverse sweep over psi and lambda in place; gradient partials in
+// seq_adjoint_columns() columns per slot.
+struct SeqTables {
+  const SeqSeg* segs;
+  const SeqOp* ops;
+  const uint32_t* words;
+};
+hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const SeqSeg& last,
+                              const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,
+                              const float2* vals, int64_t vals_bs, int batch, int precision);
+int seq_adjoint_columns(const SeqPass& ps, int bits);
+hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const float2* u,
+                              int64_t u_bs, float2* psi, int64_t psi_bs, float2* lam, int64_t lam_bs, int batch,
+                              double* partials, int64_t partial_stride, int precision);
+// grad[z][p] = scale_z * sum over the first n_cols partials of every gradient slot of parameter p
+// (param_slots: param_slots[param_slots[p] .. param_slots[p + 1]))
+hipError_t launch_gradient_reduce(hipStream_t s, const double* partials, int64_t partial_stride, int n_cols,
+                                  const int32_t* param_slots, int n_params, const double* grad_out, int batch,
                                   double* grad);
 // sweep gate matrices: recipe r of the sweep -> [batch][n_sweep][16] complex64
 hipError_t launch_sweep_matrices(hipStream_t s, const Recipe* recipes, int n, const RecipeOp* ops, const double* mats,

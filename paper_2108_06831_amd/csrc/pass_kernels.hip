@@ -245,7 +245,7 @@ hipError_t launch_sweep_pass(hipStream_t s, const SweepPass& ps, int bits, const
   a.lds_off = a.gates_in_lds ? ps.val_off : ps.ctab_off;
   a.lds_n = a.gates_in_lds ? n_all : ps.ctab_n;
   a.pad2 = 0;
-  if (ps.l < kSweepMinLocal || ps.l > kSweepMaxLocal) return hipErrorInvalidValue;
+  if (ps.l < kSweepMinLocal || ps.l > kSweepMaxLocal || ps.l > bits) return hipErrorInvalidValue;
   if (ps.ctab_n < 0 || ps.ctab_n > kCountTabMax || n_all < 0 || (a.lds_n > 0 && !vals)) return hipErrorInvalidValue;
   static_assert(kCountTabMax <= kPassValMax, "the power tables alone always fit");
   std::vector<char> local(bits, 0);
@@ -288,14 +288,6 @@ __global__ __launch_bounds__(kThreads) void k_adjoint_pass(AdjPassArgs a, const 
   const int z = blockIdx.y;
   const int L = 1 << a.l;
   const int nt = blockDim.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
-  if (blockIdx.x >= a.n_chunks) {  // no chunk for this block: its partial of every gradient term is zero
-    for (int gi = a.first_gate + tid; gi < a.first_gate + a.n_gates; gi += nt) {
-      const AdjGateDesc& gd = gates[gi];
-      if (gd.red >= 0 && gd.slot >= 0)
-        a.partials[(int64_t)z * a.pstride + (int64_t)gd.slot * kReduceBlocks + blockIdx.x] = 0.0;
-    }
-    return;
-  }
   const float2* Uz = Uall + (int64_t)z * a.u_bs;
   // U of the pass's gates (at most kAdjPreGates) staged in LDS, one load per thread, all in flight
   // together: diagonal U[0], U[3] (one bit) or U[0], U[5], U[10], U[15] (two bits); one-qubit dense
@@ -640,10 +632,10 @@ hipError_t launch_adjoint_pass(hipStream_t s, const SweepPass& ps, int bits, con
   a.n_chunks = (int64_t)1 << nr;
   const int threads = 1 << (ps.l - 4);
   if (precision == TN_PREC_BF16X3)
-    hipLaunchKernelGGL(k_adjoint_pass<TN_PREC_BF16X3>, dim3(kReduceBlocks, batch), dim3(threads), 0, s, a, a.gates,
+    hipLaunchKernelGGL(k_adjoint_pass<TN_PREC_BF16X3>, dim3(adjoint_blocks(ps, bits), batch), dim3(threads), 0, s, a, a.gates,
                        a.segs, a.U);
   else
-    hipLaunchKernelGGL(k_adjoint_pass<TN_PREC_C64>, dim3(kReduceBlocks, batch), dim3(threads), 0, s, a, a.gates, a.segs,
+    hipLaunchKernelGGL(k_adjoint_pass<TN_PREC_C64>, dim3(adjoint_blocks(ps, bits), batch), dim3(threads), 0, s, a, a.gates, a.segs,
                        a.U);
   return hipGetLastError();
 }

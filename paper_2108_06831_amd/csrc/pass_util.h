@@ -103,6 +103,13 @@ __device__ __forceinline__ void chunk_from_lds(float2* dst, const float2* buf, i
   }
 }
 
+// -v of a uniform value, as an integer operation (which stays on the scalar unit)
+__device__ __forceinline__ float neg_s(float v) { return __uint_as_float(__float_as_uint(v) ^ 0x80000000u); }
+// v with the sign bits of s flipped
+__device__ __forceinline__ float2 flip_s(float2 v, uint32_t s) {
+  return f2(__uint_as_float(__float_as_uint(v.x) ^ s), __uint_as_float(__float_as_uint(v.y) ^ s));
+}
+
 // Shapes of a one-qubit matrix that take half the multiplies (known from the
 // gate kinds, see GateForm): every entry real (RY, H, X, ...), or a real
 // diagonal and an imaginary off-diagonal (RX, Y, the QAOA mixer exp(-i b X)).

@@ -682,6 +682,139 @@ void build_outer_chains(tn_path* path, int T) {
   }
 }
 
+namespace {
+
+// The path's leading steps as ordered passes (SeqChain): the merges of the
+// qubits' |0> vectors into one state, then at least kSeqMinRun gates, each
+// contracted with the result of the step before and leaving the state's size.
+// The state then starts as |0...0> whatever the merges' order, so none of
+// these steps runs by itself.  The interpreter's steps are all among them or
+// the chain is not taken (they share one launch).
+void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>& loc,
+                    const std::vector<std::vector<int32_t>>& modes) {
+  path->seq = SeqChain();
+  const int T = (int)net->tensors.size();
+  const int S = (int)path->pairs.size() / 2;
+  std::vector<char> zero(T + S, 0);
+  int n_zero = 0;
+  for (int t = 0; t < T; ++t)
+    if (net->tensors[t].kind == TK_KET0 && net->tensors[t].size == 2 && loc[t].bits.size() == 1) {
+      zero[t] = 1;
+      ++n_zero;
+    }
+  int s = 0;
+  for (; s < S && zero[path->pairs[2 * s]] && zero[path->pairs[2 * s + 1]]; ++s) zero[T + s] = 1;
+  if (s == 0 || s + 1 != n_zero) return;  // every |0> is in one state
+  SeqChain ch;
+  ch.bits = (int)loc[T + s - 1].bits.size();
+  if (ch.bits != n_zero || ch.bits < kSeqMinBits || ch.bits > kSeqMaxBits || net->input_elems > ((int64_t)1 << 30)) return;
+  std::vector<SeqItem> items;
+  std::vector<int32_t> cur = loc[T + s - 1].bits;  // the running state's layout
+  ch.in_bits = cur;
+  const int first = s;
+  bool moved = false;  // the last step's result has another layout
+  for (; s < S && !moved; ++s) {
+    const int ia = path->pairs[2 * s], ib = path->pairs[2 * s + 1];
+    const int t = T + s - 1, g = ia == t ? ib : ia;
+    if ((ia != t && ib != t) || g >= T || net->tensors[g].kind != TK_GATE || net->tensors[g].recipe < 0 ||
+        !path->steps[s].pre.empty())
+      break;
+    const std::vector<int32_t>& gb = loc[g].bits;
+    const int gn = (int)gb.size();
+    auto result_has = [&](int m) { return std::find(modes[T + s].begin(), modes[T + s].end(), m) != modes[T + s].end(); };
+    SeqItem it;
+    it.gate_first = ia == g;
+    it.src = (int)loc[g].ref.off;
+    std::vector<int> kpos, kaddr, maddr;  // summed bits: positions in the state; addresses in G
+    std::vector<int32_t> mlab;
+    bool batch_only = true;
+    for (int j = 0; j < gn; ++j) {  // G's address bits from the least significant
+      const int32_t lab = gb[gn - 1 - j];
+      const int p = pos_of(cur, lab);
+      if (p < 0) {
+        maddr.push_back(j);
+        mlab.push_back(lab);
+        batch_only = false;
+      } else if (!result_has(mode_of(lab))) {
+        kpos.push_back(p);
+        kaddr.push_back(j);
+        batch_only = false;
+      } else if (j < 2) {
+        it.pos[j] = p;
+      }
+    }
+    const Recipe& r = net->recipes[net->tensors[g].recipe];
+    const bool whole = r.split_side < 0 && r.op_end > r.op_begin, single = r.op_end - r.op_begin == 1;
+    const int kind0 = r.op_end > r.op_begin ? net->ops[r.op_begin].kind : -1;
+    if (batch_only) {
+      if (gn < 1 || gn > 2 || !r.diag) break;
+      it.diag = true;
+      it.n = gn;
+      if (whole && single && gn == r.nq) {
+        if (kind0 == TN_GATE_Z) it.signs = 2;
+        if (kind0 == TN_GATE_CZ) it.signs = 8;
+        if (kind0 == TN_GATE_ZZPHASE) it.ones = 1 | 8;
+        if (kind0 == TN_GATE_CPHASE) it.ones = 1 | 2 | 4;
+      }
+    } else {
+      it.n = (int)kpos.size();
+      if ((int)mlab.size() != it.n || it.n > 2 || gn != 2 * it.n) break;
+      if (it.n == 1) {
+        if (kaddr[0] != 0 || maddr[0] != 1) break;
+        it.pos[0] = kpos[0];
+        bool real = whole && r.nq == 1, rxl = real;
+        for (int o = r.op_begin; o < r.op_end; ++o) {
+          const int k = net->ops[o].kind;
+          real &= k == TN_GATE_H || k == TN_GATE_X || k == TN_GATE_Z || k == TN_GATE_RY;
+          rxl &= single && (k == TN_GATE_RX || k == TN_GATE_MIXER || k == TN_GATE_Y);
+        }
+        it.form = real ? kFormReal : rxl ? kFormRxLike : kFormGeneric;
+      } else {
+        if (kpos[0] > kpos[1]) {  // the summed index's bits by ascending position in the state
+          std::swap(kpos[0], kpos[1]);
+          std::swap(kaddr[0], kaddr[1]);
+        }
+        it.pos[0] = kpos[0];
+        it.pos[1] = kpos[1];
+        for (int m = 0; m < 4; ++m)
+          for (int k = 0; k < 4; ++k) {
+            uint64_t a = 0;
+            for (int j = 0; j < 2; ++j) a |= (uint64_t)((m >> j) & 1) << maddr[j] | (uint64_t)((k >> j) & 1) << kaddr[j];
+            it.perm |= a << (4 * (4 * m + k));
+          }
+      }
+      for (int j = 0; j < it.n; ++j) cur[cur.size() - 1 - it.pos[j]] = mlab[j];
+    }
+    const std::vector<int32_t>& cb = loc[T + s].bits;
+    if (cb.size() != cur.size()) break;
+    for (int32_t lab : cur)
+      if (pos_of(cb, lab) < 0) return;
+    moved = cb != cur;
+    // a result in another layout ends the chain; over several passes, whose last would write it
+    // over what other blocks still read, the chain ends before it
+    if (moved && ch.bits > kSeqMaxLocal) break;
+    items.push_back(it);
+    ch.flops += path->steps[s].flops;
+    ch.out_bits = cb;
+    ch.in_bits = cur;
+    ch.end = s + 1;
+  }
+  if (ch.end - first < kSeqMinRun || ch.end < path->n_small) return;
+  const StepProgram& P = path->steps[ch.end - 1];
+  if (P.kind == SK_SMALL) {
+    ch.out.buf = P.sm.c_buf;
+    ch.out.off = P.sm.c_off;
+  } else {
+    ch.out = P.kind == SK_GEMM ? P.gm[0].c : P.sk.c;
+  }
+  if (ch.out.buf != BUF_WS) return;
+  ch.last = ch.end == S;
+  if (!build_seq_program(ch.bits, items, kSeqMaxLocal, &ch.prog)) return;
+  path->seq = std::move(ch);
+}
+
+}  // namespace
+
 tn_status compile_program(const tn_network* net, tn_path* path, const std::vector<int32_t>* final_layout) {
   const int T = (int)net->tensors.size();
   const int S = (int)path->pairs.size() / 2;
@@ -1337,8 +1470,9 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
   }
   build_chains(path, T);
   build_outer_chains(path, T);
+  find_seq_chain(net, path, loc, modes);
   st.n_product_launches = 0;
-  for (int s = path->n_small, run0 = -1, run_len = 0; s < S; ++s) {
+  for (int s = std::max(path->n_small, path->seq.end), run0 = -1, run_len = 0; s < S; ++s) {
     const StepProgram& P = path->steps[s];
     if (P.chain != -1) {
       run0 = -1;
@@ -1400,11 +1534,53 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
   path->adj_reg_phases.clear();
   path->adj_reg_words.clear();
   path->adj_state = -1;
+  path->adj_seq = SeqProgram();
   const int R = (int)path->final_bits.size();
-  // whole waves for the gradient reductions need chunks of 2^10 elements at least
-  if (R < 18 || path->final_elems != ((int64_t)1 << R) || path->final_ref.buf != BUF_WS) return;
+  if (path->final_elems != ((int64_t)1 << R) || path->final_ref.buf != BUF_WS) return;
   const int G = (int)net->sweep.size();
   if ((int)slot_of_gate.size() != G) return;
+  // small states: ordered passes (the fused passes' kernels also need chunks of whole waves, and
+  // sum gradient terms in FP32 within a wave where the ordered ones do so in FP64, as the
+  // step-by-step sweep of small states always has)
+  if (R <= kSeqAdjMaxBits) {
+    std::vector<SeqItem> items;
+    for (int gi = G - 1; gi >= 0; --gi) {
+      const SweepGate& g = net->sweep[gi];
+      const Recipe& rc = net->sweep_recipes[g.recipe];
+      const int kind0 = rc.op_end > rc.op_begin ? net->sweep_ops[rc.op_begin].kind : -1;
+      const bool single = rc.op_end - rc.op_begin == 1;
+      SeqItem it;
+      it.n = g.nq;
+      it.diag = g.diag != 0;
+      it.src = 16 * gi;
+      const int p0 = pos_of(path->final_bits, net->wire_final[g.q[0]] * 64);
+      const int p1 = g.nq == 2 ? pos_of(path->final_bits, net->wire_final[g.q[1]] * 64) : 0;
+      if (p0 < 0 || p1 < 0) return;
+      // bit 0 of the gate's own index is its second qubit (the first is the more significant)
+      it.pos[0] = g.nq == 2 ? p1 : p0;
+      it.pos[1] = g.nq == 2 ? p0 : 0;
+      it.red = slot_of_gate[gi];
+      it.gen = it.red >= 0 ? g.gen : GEN_NONE;
+      if (it.red >= 0) {
+        const bool two = g.gen == GEN_ZZ_PHASE || g.gen == GEN_CPHASE;
+        const bool diag = two || g.gen == GEN_Z_HALF;
+        if (g.gen == GEN_NONE || diag != it.diag || two != (g.nq == 2)) return;
+      }
+      if (it.diag && single && it.red < 0) {
+        if (kind0 == TN_GATE_Z) it.signs = 2;
+        if (kind0 == TN_GATE_CZ) it.signs = 8;
+      }
+      if (it.diag && single && kind0 == TN_GATE_ZZPHASE) it.ones = 1 | 8;
+      if (it.diag && single && kind0 == TN_GATE_CPHASE) it.ones = 1 | 2 | 4;
+      if (!it.diag && g.nq == 1 && single) {
+        if (kind0 == TN_GATE_RY || kind0 == TN_GATE_H || kind0 == TN_GATE_X) it.form = kFormReal;
+        if (kind0 == TN_GATE_RX || kind0 == TN_GATE_MIXER || kind0 == TN_GATE_Y) it.form = kFormRxLike;
+      }
+      items.push_back(it);
+    }
+    if (build_seq_program(R, items, kSeqAdjMaxLocal, &path->adj_seq)) path->adj_state = 2;
+    return;
+  }
   // the passes' operations in a layout (-1: a gate the passes cannot take)
   auto make_items = [&](const std::vector<int32_t>& bits, std::vector<PassItem>& items) {
     items.clear();

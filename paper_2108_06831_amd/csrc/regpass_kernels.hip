@@ -182,12 +182,6 @@ __device__ __forceinline__ uint32_t sign_mask16(const RegOp& op, const uint32_t*
   }
   return m;
 }
-__device__ __forceinline__ float2 flip(float2 v, uint32_t s) {
-  return f2(__uint_as_float(__float_as_uint(v.x) ^ s), __uint_as_float(__float_as_uint(v.y) ^ s));
-}
-
-// -v of a uniform value, as an integer operation (which stays on the scalar unit)
-__device__ __forceinline__ float neg(float v) { return __uint_as_float(__float_as_uint(v) ^ 0x80000000u); }
 
 // x[r] *= q for the combinations whose bit R is 1
 template <int R>
@@ -303,7 +297,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_sweep_regs(RegPassArgs a, const
       }
       ph = cmul<TN_PREC_C64>(ph, f);
     }
-    if (seg.n_sign) ph = flip(ph, lead_signs(seg, words, A));
+    if (seg.n_sign) ph = flip_s(ph, lead_signs(seg, words, A));
     for (int oi = seg.op_off; oi < seg.op_off + seg.n_op; ++oi) {
       const RegOp& op = ops[oi];
       const int mask = op.mask;
@@ -327,7 +321,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_sweep_regs(RegPassArgs a, const
       if (op.type & REG_SIGNS) {
         const uint32_t m = sign_mask16(op, words, A);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = flip(x[r], (m << (31 - r)) & 0x80000000u);
+        for (int r = 0; r < 16; ++r) x[r] = flip_s(x[r], (m << (31 - r)) & 0x80000000u);
       }
       if (op.type & REG_DIAG) {  // one-bit unit diagonals: the first entry joins the factor
 #define TNQ_DIAG_BIT(R)                                                                         \
@@ -468,7 +462,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_adjoint_regs(RegPassArgs a, con
         if (p.red >= 0) add_grad(p.red, q * tT);
         ph = cmul<TN_PREC_C64>(ph, f2(u.x, -u.y));
       }
-      if (seg.n_sign) ph = flip(ph, lead_signs(seg, words, A));
+      if (seg.n_sign) ph = flip_s(ph, lead_signs(seg, words, A));
       float tS0 = 0.f, tS1 = 0.f, tS2 = 0.f, tS3 = 0.f;
       for (int oi = seg.op_off; oi < seg.op_off + seg.n_op; ++oi) {
         const RegOp& op = ops[oi];
@@ -491,12 +485,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_adjoint_regs(RegPassArgs a, con
                            dense_real<R>(xl, u[R][0].x, u[R][2].x, u[R][1].x, u[R][3].x))
           }
           if (op.type & REG_RXLIKE) {
-            TNQ_DENSE_BITS(TNQ_GRAD dense_rxlike<R>(xp, u[R][0].x, neg(u[R][2].y), neg(u[R][1].y), u[R][3].x);
-                           dense_rxlike<R>(xl, u[R][0].x, neg(u[R][2].y), neg(u[R][1].y), u[R][3].x))
+            TNQ_DENSE_BITS(TNQ_GRAD dense_rxlike<R>(xp, u[R][0].x, neg_s(u[R][2].y), neg_s(u[R][1].y), u[R][3].x);
+                           dense_rxlike<R>(xl, u[R][0].x, neg_s(u[R][2].y), neg_s(u[R][1].y), u[R][3].x))
           }
           if (op.type & REG_DENSE) {
-            TNQ_DENSE_BITS(TNQ_GRAD const float2 w0 = f2(u[R][0].x, neg(u[R][0].y)), w1 = f2(u[R][2].x, neg(u[R][2].y)),
-                           w2 = f2(u[R][1].x, neg(u[R][1].y)), w3 = f2(u[R][3].x, neg(u[R][3].y));
+            TNQ_DENSE_BITS(TNQ_GRAD const float2 w0 = f2(u[R][0].x, neg_s(u[R][0].y)), w1 = f2(u[R][2].x, neg_s(u[R][2].y)),
+                           w2 = f2(u[R][1].x, neg_s(u[R][1].y)), w3 = f2(u[R][3].x, neg_s(u[R][3].y));
                            dense_generic<R>(xp, w0, w1, w2, w3); dense_generic<R>(xl, w0, w1, w2, w3))
           }
 #undef TNQ_GRAD
@@ -506,8 +500,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_adjoint_regs(RegPassArgs a, con
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const uint32_t s = (m << (31 - r)) & 0x80000000u;
-            xp[r] = flip(xp[r], s);
-            xl[r] = flip(xl[r], s);
+            xp[r] = flip_s(xp[r], s);
+            xl[r] = flip_s(xl[r], s);
           }
         }
         if (op.type & REG_DIAG) {  // one-bit unit diagonals
@@ -624,7 +618,7 @@ hipError_t launch_adjoint_regs(hipStream_t s, const SweepPass& ps, int bits, con
   if (!rest_bits(ps, bits, &a) || ps.n_red < 0 || ps.n_red > kAdjMaxRed || ps.n_gates < 0)
     return hipErrorInvalidValue;
   static_assert(kAdjMaxRed * 4 * sizeof(double) <= kRegBuf * sizeof(float2), "accumulators fit the exchange buffer");
-  hipLaunchKernelGGL(k_adjoint_regs, dim3(kReduceBlocks, batch), dim3(kThreads), 0, s, a, t.segs + ps.reg_seg, t.ops,
+  hipLaunchKernelGGL(k_adjoint_regs, dim3(adjoint_blocks(ps, bits), batch), dim3(kThreads), 0, s, a, t.segs + ps.reg_seg, t.ops,
                      t.phases, t.words, u, gates_dev);
   return hipGetLastError();
 }

@@ -141,7 +141,7 @@ struct DevNet {
   double* mats = nullptr;
   Recipe* sweep_recipes = nullptr;
   RecipeOp* sweep_ops = nullptr;
-  int32_t* slot_param = nullptr;
+  int32_t* param_slots = nullptr;     // per parameter p: its gradient slots, param_slots[param_slots[p] .. param_slots[p + 1])
   std::vector<int32_t> slot_of_gate;  // per sweep gate: gradient slot or -1
   int n_slots = 0;
 };
@@ -190,7 +190,15 @@ static tn_status ensure_device(tn_network* net, DevNet** out) {
       sp.push_back(net->sweep[i].param);
     }
   d->n_slots = (int)sp.size();
-  HIP_TRY(upload(&d->slot_param, sp));
+  // the slots of each parameter, in order, behind a table of their starts
+  std::vector<int32_t> ps(net->n_params + 1, 0);
+  for (int p = 0; p < net->n_params; ++p) {
+    ps[p] = (int32_t)ps.size();
+    for (size_t i = 0; i < sp.size(); ++i)
+      if (sp[i] == p) ps.push_back((int32_t)i);
+  }
+  ps[net->n_params] = (int32_t)ps.size();
+  HIP_TRY(upload(&d->param_slots, ps));
   *out = d;
   return TN_OK;
 }
@@ -202,7 +210,7 @@ void device_release_network(tn_network* net) {
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(d->device);
   (void)hipFree(d->tensors); (void)hipFree(d->recipes); (void)hipFree(d->ops); (void)hipFree(d->mats);
-  (void)hipFree(d->sweep_recipes); (void)hipFree(d->sweep_ops); (void)hipFree(d->slot_param);
+  (void)hipFree(d->sweep_recipes); (void)hipFree(d->sweep_ops); (void)hipFree(d->param_slots);
   (void)hipSetDevice(cur);
   delete d;
   net->dev = nullptr;
@@ -222,6 +230,12 @@ struct DevPath {
   RegOp* reg_ops = nullptr;
   RegPhase* reg_phases = nullptr;
   uint32_t* reg_words = nullptr;
+  SeqSeg* seq_segs = nullptr;           // ordered passes
+  SeqOp* seq_ops = nullptr;
+  uint32_t* seq_words = nullptr;
+  SeqSeg* adj_seq_segs = nullptr;       // uploaded on the first backward call
+  SeqOp* adj_seq_ops = nullptr;
+  uint32_t* adj_seq_words = nullptr;
   AdjGateDesc* adj_gates = nullptr;     // uploaded on the first backward call
   SweepSegment* adj_segments = nullptr;
   RegSeg* adj_reg_segs = nullptr;
@@ -251,6 +265,9 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   HIP_TRY(upload(&d->reg_ops, path->reg_ops));
   HIP_TRY(upload(&d->reg_phases, path->reg_phases));
   HIP_TRY(upload(&d->reg_words, path->reg_words));
+  HIP_TRY(upload(&d->seq_segs, path->seq.prog.segs));
+  HIP_TRY(upload(&d->seq_ops, path->seq.prog.ops));
+  HIP_TRY(upload(&d->seq_words, path->seq.prog.words));
   *out = d;
   return TN_OK;
 }
@@ -270,7 +287,9 @@ void device_release_path(tn_path* path) {
   (void)hipFree(d->sweep_val_src);
   (void)hipFree(d->slice_tensors);
   for (void* p : {(void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
-                  (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words})
+                  (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words,
+                  (void*)d->seq_segs, (void*)d->seq_ops, (void*)d->seq_words, (void*)d->adj_seq_segs,
+                  (void*)d->adj_seq_ops, (void*)d->adj_seq_words})
     (void)hipFree(p);
   (void)hipFree(d->adj_gates);
   (void)hipFree(d->adj_segments);
@@ -312,6 +331,7 @@ struct Bases {
   // when set, the last step (a matrix product) writes here instead of its workspace buffer
   float2* final_out = nullptr;
   int64_t final_out_bs = 0;
+  const std::vector<int32_t>* final_layout = nullptr;  // final_out's bit order
   // contract_pair: inputs are two separate user buffers
   const float2* pair_a = nullptr;
   const float2* pair_b = nullptr;
@@ -344,13 +364,54 @@ static size_t group_end(const tn_path* path, size_t si, int precision) {
   return e;
 }
 
+static int pos_in(const std::vector<int32_t>& bits, int32_t l) {
+  for (size_t i = 0; i < bits.size(); ++i)
+    if (bits[i] == l) return (int)(bits.size() - 1 - i);
+  return -1;
+}
+
+// The path's leading steps as ordered passes, in place on the last one's result
+// buffer; a chain that ends the path writes the caller's output when it is set.
+static tn_status run_seq(hipStream_t s, tn_path* path, DevPath* dp, const Bases& B, int batch, int precision) {
+  const SeqChain& ch = path->seq;
+  int64_t obs, ibs;
+  float2* out = resolve(B, ch.out, &obs);
+  BufRef ri;
+  ri.buf = BUF_IN;
+  const float2* in = resolve(B, ri, &ibs);
+  const bool direct = ch.last && B.final_out;
+  const std::vector<int32_t>& to = direct ? *B.final_layout : ch.out_bits;
+  int8_t pos[32] = {0};
+  for (int p = 0; p < ch.bits; ++p) {
+    const int q = pos_in(to, ch.in_bits[ch.bits - 1 - p]);
+    if (q < 0) return set_error(TN_EINVAL, "internal: ordered passes miss a leg of the result");
+    pos[p] = (int8_t)q;
+  }
+  hipEvent_t ev = prof_start(s, TN_KERNEL_SWEEP);
+  const int n = (int)ch.prog.passes.size();
+  for (int i = 0; i < n; ++i) {
+    const SeqPass& ps = ch.prog.passes[i];
+    const bool last = i == n - 1;
+    HIP_TRY(launch_seq_forward(s, ps, ch.bits, SeqTables{dp->seq_segs, dp->seq_ops, dp->seq_words},
+                               ch.prog.segs[ps.first_seg + ps.n_segs - 1], i == 0 ? nullptr : out, obs,
+                               last && direct ? B.final_out : out, last && direct ? B.final_out_bs : obs,
+                               last ? pos : nullptr, in, ibs, batch, precision));
+  }
+  prof_stop(s, ev, TN_KERNEL_SWEEP, 16.0 * std::ldexp(1.0, ch.bits) * n * batch, ch.flops * batch);
+  return TN_OK;
+}
+
 static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, int batch, int precision) {
   DevPath* dp = nullptr;
-  if (path->n_small > 0 || !path->chains.empty()) {
+  const int seq_end = B.pair_a ? 0 : path->seq.end;
+  if (path->n_small > 0 || !path->chains.empty() || seq_end > 0) {
     tn_status st = ensure_path_device(path, &dp);
     if (st != TN_OK) return st;
   }
-  if (path->n_small > 0) {
+  if (seq_end > 0) {
+    tn_status st = run_seq(s, path, dp, B, batch, precision);
+    if (st != TN_OK) return st;
+  } else if (path->n_small > 0) {
     int64_t ibs, wbs;
     BufRef ri, rw;
     ri.buf = BUF_IN;
@@ -365,7 +426,7 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
     for (int i = 0; i < path->n_small; ++i) { fl += path->steps[i].flops; by += path->steps[i].bytes; }
     prof_stop(s, ev, TN_KERNEL_INTERP, by * batch, fl * batch);
   }
-  for (size_t si = path->n_small; si < path->steps.size(); ++si) {
+  for (size_t si = std::max(path->n_small, seq_end); si < path->steps.size(); ++si) {
     const StepProgram& P = path->steps[si];
     if (P.chain == -2) continue;
     if (P.chain >= 0) {
@@ -519,12 +580,6 @@ static tn_status materialize(hipStream_t s, tn_network* net, DevNet* d, const do
 }
 
 static int32_t lab(int mode, int j) { return mode * 64 + j; }
-
-static int pos_in(const std::vector<int32_t>& bits, int32_t l) {
-  for (size_t i = 0; i < bits.size(); ++i)
-    if (bits[i] == l) return (int)(bits.size() - 1 - i);
-  return -1;
-}
 
 // move the final tensor (layout `from`) into `dst` with layout `to`
 // the final tensor f (stride fbs per batch item, layout path->final_bits) into dst
@@ -806,11 +861,12 @@ static tn_status contract_path_in(hipStream_t s, int32_t precision, tn_network* 
   B.out_bs = (int64_t)1 << net->n_qubits;
   std::vector<int32_t> to;
   for (int q = 0; q < net->n_qubits; ++q) to.push_back(lab(net->wire_final[q], 0));
-  const bool direct = !path->steps.empty() && path->steps.back().kind == SK_GEMM && path->steps.back().chain == -1 &&
-                      path->final_bits == to;
+  const bool direct = path->seq.last || (!path->steps.empty() && path->steps.back().kind == SK_GEMM &&
+                                         path->steps.back().chain == -1 && path->final_bits == to);
   if (direct) {
     B.final_out = B.out;
     B.final_out_bs = B.out_bs;
+    B.final_layout = &to;
   }
   if ((st = materialize(s, net, d, params_dev, batch, nullptr, 0, B.in)) != TN_OK) return st;
   if ((st = run_steps(s, path, B, batch, precision)) != TN_OK) return st;
@@ -907,7 +963,7 @@ extern "C" tn_status tn_contract_path_noalloc(void* stream, int32_t precision, t
   if (!d || d->device != dev)
     return set_error(TN_EINVAL, "the network's device tables are not on this device: run tn_contract_path once "
                                 "with this network on this device first");
-  const bool needs_path_tables = path->n_small > 0 || !path->chains.empty();
+  const bool needs_path_tables = path->n_small > 0 || !path->chains.empty() || path->seq.end > 0;
   const DevPath* dp = (const DevPath*)path->dev;
   if (needs_path_tables && (!dp || dp->device != dev))
     return set_error(TN_EINVAL, "the path's device tables are not on this device: run tn_contract_path once "
@@ -1238,6 +1294,27 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
                                 net->n_params, batch, umats));
   double* parts = (double*)(w + L.part_off);
   const int64_t pstride = (int64_t)std::max(d->n_slots, 1) * kReduceBlocks;
+  int n_cols = kReduceBlocks;  // columns of partials per gradient term
+  if (path->adj_state == 2) {  // ordered passes
+    DevPath* dp;
+    if ((st = ensure_path_device(path, &dp)) != TN_OK) return st;
+    const SeqProgram& pr = path->adj_seq;
+    if (!dp->adj_seq_segs) {
+      HIP_TRY(upload(&dp->adj_seq_segs, pr.segs));
+      HIP_TRY(upload(&dp->adj_seq_ops, pr.ops));
+      HIP_TRY(upload(&dp->adj_seq_words, pr.words));
+    }
+    const int bits = (int)path->final_bits.size();
+    n_cols = seq_adjoint_columns(pr.passes[0], bits);
+    double fl = 0;  // as counted for the step-by-step sweep
+    for (const SweepGate& g : net->sweep) fl += (2.0 * 8.0 * (1 << g.nq) + (g.gen != GEN_NONE ? 8.0 : 0.0)) * (double)n;
+    hipEvent_t ev = prof_start(s, TN_KERNEL_ADJOINT);
+    for (const SeqPass& ps : pr.passes)
+      HIP_TRY(launch_seq_adjoint(s, ps, bits, SeqTables{dp->adj_seq_segs, dp->adj_seq_ops, dp->adj_seq_words}, umats,
+                                 (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride,
+                                 precision));
+    prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * pr.passes.size() * batch, fl * batch);
+  }
   if (path->adj_state == 1) {
     // fused passes: both states stream through LDS once per pass
     DevPath* dp;
@@ -1251,6 +1328,7 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
       HIP_TRY(upload(&dp->adj_reg_words, path->adj_reg_words));
     }
     const int bits = (int)path->final_bits.size();
+    n_cols = adjoint_blocks(path->adj_passes[0], bits);
     for (const SweepPass& ps : path->adj_passes) {
       double fl = 0;
       for (int i = ps.first_gate; i < ps.first_gate + ps.n_gates; ++i) {
@@ -1272,7 +1350,7 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
       prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * batch, fl * batch);
     }
   }
-  for (int gi = path->adj_state == 1 ? -1 : (int)net->sweep.size() - 1; gi >= 0; --gi) {
+  for (int gi = path->adj_state >= 1 ? -1 : (int)net->sweep.size() - 1; gi >= 0; --gi) {
     const SweepGate& g = net->sweep[gi];
     SweepArgs a;
     a.nq = g.nq;
@@ -1290,7 +1368,7 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
               (2.0 * per + (a.slot >= 0 ? 8.0 : 0.0)) * (double)n * batch);
   }
   if (net->n_params > 0)
-    HIP_TRY(launch_gradient_reduce(s, parts, pstride, d->n_slots, d->slot_param, net->n_params, grad_out_dev, batch,
+    HIP_TRY(launch_gradient_reduce(s, parts, pstride, n_cols, d->param_slots, net->n_params, grad_out_dev, batch,
                                    grad_dev));
   return TN_OK;
 }

@@ -1,0 +1,470 @@
+// Ordered gate passes over small states (see SeqPass in internal.h).
+//
+// A contraction of a circuit on few qubits along the sequential order, or the
+// reverse sweep of its gradient, is a chain of gates on one small state: as
+// one launch per gate it costs about 6 us per gate, all of it launch latency.
+// Here one block carries a chunk of up to 2^14 elements (2^13 of psi and
+// lambda) through the gates, sixteen elements per thread in registers, LDS
+// only between segments; a state of up to that size is one launch, larger ones
+// one per pass.  What bounds it is the instructions of one compute unit (or of
+// a few): about 0.3 us per gate at 2^13 elements.  Every gate is applied by
+// itself and in order, with the products, sums and roundings of the
+// step-by-step kernels (k_small_steps, k_elem_group, k_adjoint_step), so the
+// state is bit for bit theirs; gradient terms are formed and summed in FP64 as
+// in k_adjoint_step.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <vector>
+
+#include "kernels.h"
+#include "pass_util.h"
+
+namespace tnq {
+
+namespace {
+
+struct SeqArgs {
+  const float2* in;  // forward: the state; adjoint: psi
+  float2* out;       // forward: the result; adjoint: lambda (both states in place)
+  int64_t in_bs, out_bs, vals_bs;
+  double* partials;
+  int64_t pstride;
+  int32_t l, n_rest, n_segs, from_zero;  // from_zero: the state is |0...0>
+  int32_t out_t[10], out_r[4];           // forward: positions in the result of the last segment's thread and register bits
+  int8_t rest[32], rest_out[32];
+};
+static_assert(offsetof(SeqArgs, rest) % 4 == 0 && offsetof(SeqArgs, rest_out) % 4 == 0,
+              "position maps aligned to 32-bit words");
+
+__device__ __forceinline__ int bits10(int t, const int32_t* pos) {
+  int o = 0;
+#pragma unroll
+  for (int j = 0; j < 10; ++j) o |= ((t >> j) & 1) << pos[j];
+  return o;
+}
+
+// a <- g0 a + g1 b, b <- g2 a + g3 b (the term of index 0 first, as a sum over the gate's input index)
+template <int PREC, int R>
+__device__ __forceinline__ void dense_seq(float2 (&x)[16], float2 g0, float2 g1, float2 g2, float2 g3, int form,
+                                          bool gate_first) {
+  if (PREC == TN_PREC_C64 && form == kFormReal) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (r & (1 << R)) continue;
+      float t;
+      float2 &a = x[r], &b = x[r | (1 << R)];
+#define TNQ_PAIR(A, B)                                                                  \
+  asm("v_mul_f32 %2, %5, %0\n\t"                                                        \
+      "v_mul_f32 %0, %3, %0\n\t"                                                        \
+      "v_fma_f32 %0, %4, %1, %0\n\t"                                                    \
+      "v_fma_f32 %1, %6, %1, %2"                                                        \
+      : "+v"(A), "+v"(B), "=&v"(t)                                                      \
+      : "s"(g0.x), "s"(g1.x), "s"(g2.x), "s"(g3.x));
+      TNQ_PAIR(a.x, b.x)
+      TNQ_PAIR(a.y, b.y)
+#undef TNQ_PAIR
+    }
+  } else if (PREC == TN_PREC_C64 && form == kFormRxLike) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (r & (1 << R)) continue;
+      float t0, t1;
+      float2 &a = x[r], &b = x[r | (1 << R)];
+      asm("v_mul_f32 %4, -%8, %1\n\t"
+          "v_mul_f32 %5, %8, %0\n\t"
+          "v_mul_f32 %0, %6, %0\n\t"
+          "v_mul_f32 %1, %6, %1\n\t"
+          "v_fma_f32 %0, -%7, %3, %0\n\t"
+          "v_fma_f32 %1, %7, %2, %1\n\t"
+          "v_fma_f32 %2, %9, %2, %4\n\t"
+          "v_fma_f32 %3, %9, %3, %5"
+          : "+v"(a.x), "+v"(a.y), "+v"(b.x), "+v"(b.y), "=&v"(t0), "=&v"(t1)
+          : "s"(g0.x), "s"(g1.y), "s"(g2.y), "s"(g3.x));
+    }
+  } else if (gate_first) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (r & (1 << R)) continue;
+      const float2 a = x[r], b = x[r | (1 << R)];
+      x[r] = cmac<PREC>(cmul<PREC>(g0, a), g1, b);
+      x[r | (1 << R)] = cmac<PREC>(cmul<PREC>(g2, a), g3, b);
+    }
+    variant_end<PREC, 600 + R>();
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (r & (1 << R)) continue;
+      const float2 a = x[r], b = x[r | (1 << R)];
+      x[r] = cmac<PREC>(cmul<PREC>(a, g0), b, g1);
+      x[r | (1 << R)] = cmac<PREC>(cmul<PREC>(a, g2), b, g3);
+    }
+    variant_end<PREC, 604 + R>();
+  }
+}
+
+// A two-qubit gate on register bits 2 H (index bit 0) and 2 H + 1 (bit 1); get(e): entry e = 4 m + k.
+template <int PREC, int H, class Get>
+__device__ __forceinline__ void dense2_seq(float2 (&x)[16], Get get, bool gate_first) {
+  constexpr int s0 = 1 << (2 * H), s1 = 2 << (2 * H);
+  float2 y[16];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const float2 g[4] = {get(4 * m), get(4 * m + 1), get(4 * m + 2), get(4 * m + 3)};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if (r & (s0 | s1)) continue;
+      const float2 v0 = x[r], v1 = x[r | s0], v2 = x[r | s1], v3 = x[r | s0 | s1];
+      float2 acc;
+      if (gate_first) {
+        acc = cmac<PREC>(cmac<PREC>(cmac<PREC>(cmul<PREC>(g[0], v0), g[1], v1), g[2], v2), g[3], v3);
+      } else {
+        acc = cmac<PREC>(cmac<PREC>(cmac<PREC>(cmul<PREC>(v0, g[0]), v1, g[1]), v2, g[2]), v3, g[3]);
+      }
+      y[r | (m & 1 ? s0 : 0) | (m & 2 ? s1 : 0)] = acc;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) x[r] = y[r];
+  variant_end<PREC, 610 + H>();
+}
+
+// x <- g x (the gate the first operand) or x g
+template <int PREC>
+__device__ __forceinline__ void mul_gate(float2& x, float2 g, bool gate_first) {
+  x = gate_first ? cmul<PREC>(g, x) : cmul<PREC>(x, g);
+}
+// x[r] times e1 where bit R of r is 1, else e0
+template <int PREC, int R>
+__device__ __forceinline__ void diag_seq(float2 (&x)[16], float2 e0, float2 e1, bool gate_first) {
+  if (gate_first) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mul_gate<PREC>(x[r], (r >> R) & 1 ? e1 : e0, true);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mul_gate<PREC>(x[r], (r >> R) & 1 ? e1 : e0, false);
+  }
+  variant_end<PREC, 620 + R>();
+}
+
+// What a split-precision product leaves of a component times an exact 1: the sum of its two bfloat16 parts.
+template <int PREC>
+__device__ __forceinline__ float2 times_one(float2 v) {
+  if constexpr (PREC == TN_PREC_C64) return v;
+  else return f2(rmul<PREC>(1.f, v.x), rmul<PREC>(1.f, v.y));
+}
+
+__device__ __forceinline__ double im_d(float2 l, float2 p) { return (double)l.x * p.y - (double)l.y * p.x; }
+__device__ __forceinline__ double re_d(float2 l, float2 p) { return (double)l.x * p.x + (double)l.y * p.y; }
+
+// Im(conj(lambda) G psi) over the thread's elements for a generator on register bit R
+template <int R>
+__device__ __forceinline__ double grad_bit(const float2 (&p)[16], const float2 (&l)[16], int gen) {
+  double g = 0.0;
+  if (gen == GEN_Y_HALF) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (!(r & (1 << R))) g += re_d(l[r | (1 << R)], p[r]) - re_d(l[r], p[r | (1 << R)]);
+  } else if (gen == GEN_Z_HALF) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (!(r & (1 << R))) g += im_d(l[r], p[r]) - im_d(l[r | (1 << R)], p[r | (1 << R)]);
+  } else {  // X
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (!(r & (1 << R))) g += im_d(l[r], p[r | (1 << R)]) + im_d(l[r | (1 << R)], p[r]);
+    if (gen == GEN_X) g *= 2.0;
+  }
+  return g;
+}
+
+// sum over the 64 lanes, the result in lane 63 (as wave_sum_to_63, on both halves of the doubles)
+__device__ __forceinline__ double wave_sum_d(double v) {
+#define TNQ_STEP(CTRL, ROWS)                                                             \
+  {                                                                                      \
+    const long long b = __double_as_longlong(v);                                         \
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);       \
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false); \
+    v += __longlong_as_double(((long long)hi << 32) | (unsigned)lo);                     \
+  }
+  TNQ_STEP(0xb1, 0xf)
+  TNQ_STEP(0x4e, 0xf)
+  TNQ_STEP(0x141, 0xf)
+  TNQ_STEP(0x140, 0xf)
+  TNQ_STEP(0x142, 0xa)
+  TNQ_STEP(0x143, 0xc)
+#undef TNQ_STEP
+  return v;
+}
+
+// NS = 1: forward, from the state `in` (or |0...0>) to `out`; vals: the network's
+// input tensors.  NS = 2: reverse sweep over psi and lambda; vals: U of every
+// gate; gradient slot s of wave w of chunk c into partials[s][c * waves + w].
+template <int PREC, int NS, int LMAX>
+__global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const SeqSeg* __restrict__ segs,
+                                                              const SeqOp* __restrict__ ops,
+                                                              const uint32_t* __restrict__ words,
+                                                              const float2* __restrict__ vals) {
+  constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
+  __shared__ float2 bx[kBuf];
+  __shared__ float2 by[NS == 2 ? kBuf : 1];
+  const int z = blockIdx.y, lane = threadIdx.x & 63;
+  // chunks of fewer than 2^10 elements leave threads of the wave without elements: they repeat others
+  const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
+  const bool active = (int)threadIdx.x < n_thr;
+  const uint32_t base = (uint32_t)deposit(blockIdx.x, a.rest, a.n_rest);
+  const float2* V = vals + (int64_t)z * a.vals_bs;
+  float2* P = const_cast<float2*>(a.in) + (int64_t)z * a.in_bs;
+  float2* O = a.out + (int64_t)z * a.out_bs;
+  const int col = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  double* part = a.partials + (int64_t)z * a.pstride + col;
+  auto add_grad = [&](int slot, double v) {
+    v = wave_sum_d(active ? v : 0.0);
+    if (lane == 63) part[(int64_t)slot * kReduceBlocks] = v;
+  };
+  float2 x[16], y[16];  // psi (or the state), lambda
+  int slot = 0;
+  const int32_t* off = nullptr;
+  for (int sg = 0; sg < a.n_segs; ++sg) {
+    const SeqSeg& seg = segs[sg];
+    const int ob = bits10(tid, seg.tpos), ns = ob + (ob >> 5);
+    const uint32_t A = base | (uint32_t)bits10(tid, seg.gpos);
+    if (sg == 0) {
+      const uint32_t g0 = 1u << seg.rgpos[0], g1 = 1u << seg.rgpos[1], g2 = 1u << seg.rgpos[2], g3 = 1u << seg.rgpos[3];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t e = A | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0);
+        if (NS == 1 && a.from_zero) {
+          x[r] = f2(e == 0 ? 1.f : 0.f, 0.f);
+        } else {
+          x[r] = P[e];
+          if (NS == 2) y[r] = O[e];
+        }
+      }
+    } else {
+      // each thread writes the slots it read last, so one barrier separates the layouts
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        bx[slot + off[r]] = x[r];
+        if (NS == 2) by[slot + off[r]] = y[r];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        x[r] = bx[ns + seg.physoff[r]];
+        if (NS == 2) y[r] = by[ns + seg.physoff[r]];
+      }
+    }
+    slot = ns;
+    off = seg.physoff;
+    for (int oi = seg.op_off; oi < seg.op_off + seg.n_op; ++oi) {
+      const SeqOp& op = ops[oi];
+      if (op.type & SEQ_BITS) {
+#define TNQ_SEQ_BIT(R)                                                                                        \
+  if ((op.mask >> R) & 1) {                                                                                   \
+    if (NS == 2 && op.red[R] >= 0) add_grad(op.red[R], grad_bit<R>(x, y, op.gform[R]));                       \
+    const float2* u = V + op.src[R];                                                                          \
+    float2 g0 = u[0], g1 = u[1], g2 = u[2], g3 = u[3];                                                        \
+    if (NS == 2) { /* U^dagger[m][k] = conj(U[k][m]) */                                                       \
+      const float2 w = g1;                                                                                    \
+      g0 = f2(g0.x, neg_s(g0.y));                                                                             \
+      g1 = f2(g2.x, neg_s(g2.y));                                                                             \
+      g2 = f2(w.x, neg_s(w.y));                                                                               \
+      g3 = f2(g3.x, neg_s(g3.y));                                                                             \
+    }                                                                                                         \
+    dense_seq<PREC, R>(x, g0, g1, g2, g3, op.form[R], NS == 2 || ((op.gfirst >> R) & 1));                     \
+    if (NS == 2) dense_seq<PREC, R>(y, g0, g1, g2, g3, op.form[R], true);                                     \
+  }                                                                                                           \
+  if ((op.dmask >> R) & 1) {                                                                                  \
+    if (NS == 2 && op.dred[R] >= 0) add_grad(op.dred[R], grad_bit<R>(x, y, GEN_Z_HALF));                      \
+    const float2* u = V + op.dsrc[R];                                                                         \
+    float2 e0 = u[0], e1 = u[NS == 2 ? 3 : 1];                                                                \
+    if (NS == 2) {                                                                                            \
+      e0.y = -e0.y;                                                                                           \
+      e1.y = -e1.y;                                                                                           \
+    }                                                                                                         \
+    diag_seq<PREC, R>(x, e0, e1, NS == 2 || ((op.gfirst >> (4 + R)) & 1));                                    \
+    if (NS == 2) diag_seq<PREC, R>(y, e0, e1, true);                                                          \
+  }
+        TNQ_SEQ_BIT(0)
+        TNQ_SEQ_BIT(1)
+        TNQ_SEQ_BIT(2)
+        TNQ_SEQ_BIT(3)
+#undef TNQ_SEQ_BIT
+      }
+      if (op.type & SEQ_SIGNS) {
+        uint32_t m = (uint32_t)op.mask;
+        for (int i = op.off; i < op.off + op.n; ++i) {
+          const uint32_t w = words[i];
+          m ^= (0u - ((A >> (w & 31)) & (A >> ((w >> 8) & 31)) & 1u)) & (w >> 16);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const uint32_t s = (m << (31 - r)) & 0x80000000u;
+          x[r] = flip_s(times_one<PREC>(x[r]), s);
+          if (NS == 2) y[r] = flip_s(times_one<PREC>(y[r]), s);
+        }
+      }
+      if (op.type & SEQ_DIAG) {
+        const int k0 = op.dsrc[0], k1 = op.dsrc[1];
+        const bool two = op.mask == 2, gf = NS == 2 || (op.gfirst & 1);
+        const int c0 = (A >> (op.dsrc[2] & 31)) & 1, c1 = two ? (A >> (op.dsrc[3] & 31)) & 1 : 0;
+        const float2* u = V + op.src[0];
+        float2 d0 = u[0], d1 = u[NS == 2 ? (two ? 5 : 3) : 1], d2 = d0, d3 = d0;
+        if (two) {
+          d2 = u[NS == 2 ? 10 : 2];
+          d3 = u[NS == 2 ? 15 : 3];
+        }
+        if (NS == 2) {
+          d0.y = -d0.y;
+          d1.y = -d1.y;
+          d2.y = -d2.y;
+          d3.y = -d3.y;
+        }
+        if (NS == 2 && op.red[0] >= 0) {
+          double g = 0.0;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int b0 = k0 >= 0 ? (r >> k0) & 1 : c0, b1 = k1 >= 0 ? (r >> k1) & 1 : c1;
+            const double w = op.gen == GEN_ZZ_PHASE ? (b0 != b1 ? 2.0 : 0.0)
+                             : op.gen == GEN_CPHASE ? (b0 && b1 ? -2.0 : 0.0)
+                                                    : (b0 ? -1.0 : 1.0);
+            g += w * im_d(y[r], x[r]);
+          }
+          add_grad(op.red[0], g);
+        }
+        if (two && k0 >= 0 && k1 >= 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int b = ((r >> k0) & 1) | (((r >> k1) & 1) << 1);
+            if (PREC == TN_PREC_C64 && ((op.ones >> b) & 1)) continue;
+            const float2 q = b == 0 ? d0 : b == 1 ? d1 : b == 2 ? d2 : d3;
+            mul_gate<PREC>(x[r], q, gf);
+            if (NS == 2) mul_gate<PREC>(y[r], q, true);
+          }
+        } else if (two && (k0 >= 0 || k1 >= 0)) {
+          const int k = k0 >= 0 ? k0 : k1;
+          const float2 e0 = k0 >= 0 ? (c1 ? d2 : d0) : (c0 ? d1 : d0), e1 = k0 >= 0 ? (c1 ? d3 : d1) : (c0 ? d3 : d2);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float2 q = (r >> k) & 1 ? e1 : e0;
+            mul_gate<PREC>(x[r], q, gf);
+            if (NS == 2) mul_gate<PREC>(y[r], q, true);
+          }
+        } else {
+          const float2 lo = c0 ? d1 : d0, hi = c0 ? d3 : d2;
+          const float2 q = two && c1 ? hi : lo;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            mul_gate<PREC>(x[r], q, gf);
+            if (NS == 2) mul_gate<PREC>(y[r], q, true);
+          }
+        }
+      }
+      if (op.type & SEQ_DENSE2) {
+        const float2* u = V + op.src[0];
+        const uint32_t p0 = op.perm[0], p1 = op.perm[1];
+        auto get = [&](int e) {
+          if (NS == 2) {  // U^dagger
+            const float2 w = u[4 * (e & 3) + (e >> 2)];
+            return f2(w.x, -w.y);
+          }
+          return u[((e < 8 ? p0 : p1) >> (4 * (e & 7))) & 15];
+        };
+        const bool gf = NS == 2 || (op.gfirst & 1);
+        if (op.mask == 0) {
+          dense2_seq<PREC, 0>(x, get, gf);
+          if (NS == 2) dense2_seq<PREC, 0>(y, get, true);
+        } else {
+          dense2_seq<PREC, 1>(x, get, gf);
+          if (NS == 2) dense2_seq<PREC, 1>(y, get, true);
+        }
+      }
+    }
+    if (sg == a.n_segs - 1) {
+      if (NS == 1) {
+        const uint32_t e0 = (uint32_t)deposit(blockIdx.x, a.rest_out, a.n_rest) | (uint32_t)bits10(tid, a.out_t);
+        const uint32_t g0 = 1u << a.out_r[0], g1 = 1u << a.out_r[1], g2 = 1u << a.out_r[2], g3 = 1u << a.out_r[3];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          O[e0 | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0)] = x[r];
+      } else {
+        const uint32_t g0 = 1u << seg.rgpos[0], g1 = 1u << seg.rgpos[1], g2 = 1u << seg.rgpos[2], g3 = 1u << seg.rgpos[3];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const uint32_t e = A | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0);
+          P[e] = x[r];
+          O[e] = y[r];
+        }
+      }
+    }
+  }
+}
+
+template <int PREC, int NS>
+void seq_launch(hipStream_t s, const SeqArgs& a, const SeqTables& t, const SeqPass& ps, const float2* vals, int chunks,
+                int batch) {
+  const dim3 grid(chunks, batch), block(std::max(64, 1 << (ps.l - 4)));
+  if (ps.l <= 12)
+    hipLaunchKernelGGL((k_seq_pass<PREC, NS, 12>), grid, block, 0, s, a, t.segs + ps.first_seg, t.ops, t.words, vals);
+  else
+    hipLaunchKernelGGL((k_seq_pass<PREC, NS, NS == 2 ? kSeqAdjMaxLocal : kSeqMaxLocal>), grid, block, 0, s, a,
+                       t.segs + ps.first_seg, t.ops, t.words, vals);
+}
+
+// the pass's chunk and the bits outside it (out_pos[p]: position of address bit p in the result, NULL: p)
+bool seq_args(const SeqPass& ps, int bits, int lmax, const int8_t* out_pos, SeqArgs* a) {
+  if (ps.l < kSeqMinBits || ps.l > lmax || ps.l > bits || bits > 31 || ps.n_segs < 1) return false;
+  std::vector<char> local(bits, 0);
+  for (int j = 0; j < ps.l; ++j) {
+    if (ps.lpos[j] < 0 || ps.lpos[j] >= bits || local[ps.lpos[j]]) return false;
+    local[ps.lpos[j]] = 1;
+  }
+  a->n_rest = 0;
+  for (int p = 0; p < bits; ++p)
+    if (!local[p]) {
+      a->rest_out[a->n_rest] = out_pos ? out_pos[p] : (int8_t)p;
+      a->rest[a->n_rest++] = (int8_t)p;
+    }
+  a->l = ps.l;
+  a->n_segs = ps.n_segs;
+  return true;
+}
+
+}  // namespace
+
+hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const SeqSeg& last,
+                              const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,
+                              const float2* vals, int64_t vals_bs, int batch, int precision) {
+  SeqArgs a{};
+  a.in = in; a.out = out; a.in_bs = in_bs; a.out_bs = out_bs;
+  a.vals_bs = vals_bs;
+  a.from_zero = in == nullptr;
+  if (!seq_args(ps, bits, kSeqMaxLocal, out_pos, &a)) return hipErrorInvalidValue;
+  for (int j = 0; j < 10; ++j) a.out_t[j] = out_pos ? out_pos[last.gpos[j]] : last.gpos[j];
+  for (int j = 0; j < 4; ++j) a.out_r[j] = out_pos ? out_pos[last.rgpos[j]] : last.rgpos[j];
+  if (precision == TN_PREC_BF16X3) seq_launch<TN_PREC_BF16X3, 1>(s, a, t, ps, vals, 1 << a.n_rest, batch);
+  else seq_launch<TN_PREC_C64, 1>(s, a, t, ps, vals, 1 << a.n_rest, batch);
+  return hipGetLastError();
+}
+
+int seq_adjoint_columns(const SeqPass& ps, int bits) {
+  return (1 << (bits - ps.l)) * std::max(1, (1 << (ps.l - 4)) / 64);
+}
+
+hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const float2* u,
+                              int64_t u_bs, float2* psi, int64_t psi_bs, float2* lam, int64_t lam_bs, int batch,
+                              double* partials, int64_t partial_stride, int precision) {
+  SeqArgs a{};
+  a.in = psi; a.out = lam; a.in_bs = psi_bs; a.out_bs = lam_bs;
+  a.vals_bs = u_bs;
+  a.partials = partials;
+  a.pstride = partial_stride;
+  if (!seq_args(ps, bits, kSeqAdjMaxLocal, nullptr, &a) || seq_adjoint_columns(ps, bits) > kReduceBlocks)
+    return hipErrorInvalidValue;
+  if (precision == TN_PREC_BF16X3) seq_launch<TN_PREC_BF16X3, 2>(s, a, t, ps, u, 1 << a.n_rest, batch);
+  else seq_launch<TN_PREC_C64, 2>(s, a, t, ps, u, 1 << a.n_rest, batch);
+  return hipGetLastError();
+}
+
+}  // namespace tnq

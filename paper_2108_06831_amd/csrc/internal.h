@@ -276,39 +276,43 @@ struct SeqSeg {
   int32_t tpos[10], gpos[10];  // thread bit t -> local bit, address position
   int32_t rgpos[4];            // register bit j -> address position
   int32_t physoff[16];         // LDS slot offsets of the register combinations (as in SweepSegment)
-  int32_t op_off, n_op;
-  int32_t pad[6];
+  int32_t n_op;
+  int32_t pad[7];
 };
+// The gates of a pass as a stream of 32-bit words and a list of the values
+// they use, both in the order the kernel reads them.  A block stages them in
+// LDS, a window of whole segments at a time, so that a gate waits for no
+// memory.  An operation's first word holds its type (bits 0-3) and
+//  BITS: dense gates on the register bits of a mask (4-7), each followed by a one-bit diagonal where the
+//    second mask (8-11) says so; whether the gate is the products' first operand (12-15 dense, 16-19
+//    diagonal); GateForms of the dense gates (20-27, two bits each).  In a reverse sweep one word per gate
+//    follows: GenKind | (slot + 1) << 8.  Values: (4 | 2) per gate.
+//  SIGNS: combinations negated on every thread (16-31); then a word n and n words p | q << 8 | ones << 16:
+//    combinations `ones` negated where address bits p and q are 1.
+//  DIAG: number of qubits (4-7), first operand (12); then k0 + 1 | (k1 + 1) << 4 | p0 << 8 | p1 << 16
+//    (register bit or -1, address position) and ones | GenKind << 4 | (slot + 1) << 8 (ones: entries known
+//    to be exactly 1).  Values: 2 or 4.
+//  DENSE2: on register bits 2 h and 2 h + 1, h in 4-7; first operand (12).  Values: 16.
 enum SeqOpType { SEQ_BITS = 1, SEQ_DIAG = 2, SEQ_SIGNS = 4, SEQ_DENSE2 = 8 };
-struct SeqOp {
-  int32_t type;
-  // BITS: register bits (lowest first) with a dense gate (mask) and then a one-bit diagonal (dmask).
-  // SIGNS: combinations negated on every thread.  DIAG: the gate's qubits (1 or 2).  DENSE2: register bits 2 mask, 2 mask + 1.
-  int32_t mask, dmask;
-  int32_t gfirst;        // the gate is the products' first operand: BITS bits 0-3 dense, 4-7 diagonal; else bit 0
-  int32_t off, n;        // SIGNS: words p | q << 8 | ones << 16: `ones` negated where address bits p and q are 1
-  int32_t ones;          // DIAG: entries known to be exactly 1 (bit b)
-  int32_t gen;           // DIAG, adjoint: GenKind
-  int32_t src[4];        // values: BITS dense, per register bit; else src[0]
-  int32_t dsrc[4];       // BITS: the diagonals'.  DIAG: k0, k1 (register bits or -1), p0, p1 (address positions)
-  int32_t form[4];       // BITS: GateForm of the dense values
-  int32_t red[4];        // adjoint: gradient slot or -1 (DIAG: red[0])
-  int32_t dred[4];       // BITS, adjoint: of the diagonals
-  int32_t gform[4];      // BITS, adjoint: GenKind of the dense gates
-  uint32_t perm[2];      // DENSE2, forward: entry e = 4 m + k is value (perm[e / 8] >> 4 (e % 8)) & 15
-  int32_t pad[6];
+constexpr int kSeqWinWords = 2048, kSeqWinVals = 1536;  // a window's words and values at most
+struct SeqWindow {
+  int32_t n_segs;  // of the pass, in order
+  int32_t word_off, n_words, val_off, n_vals;
+  int32_t pad[3];
 };
-static_assert(sizeof(SeqOp) == 160 && sizeof(SeqSeg) == 192, "read with wide scalar loads");
+static_assert(sizeof(SeqSeg) == 192 && sizeof(SeqWindow) == 32, "read with wide scalar loads");
 struct SeqPass {
   int32_t l;
   int8_t lpos[kSeqMaxLocal];
   int32_t first_seg, n_segs;
+  int32_t first_win, n_wins;
 };
 struct SeqProgram {
   std::vector<SeqPass> passes;
   std::vector<SeqSeg> segs;
-  std::vector<SeqOp> ops;
+  std::vector<SeqWindow> wins;
   std::vector<uint32_t> words;
+  std::vector<int32_t> vals;  // element offsets in the value buffer
 };
 // one gate of an ordered pass
 struct SeqItem {
@@ -316,8 +320,7 @@ struct SeqItem {
   int pos[2] = {0, 0};  // address position of bit j of the gate's own index
   bool diag = false;
   bool gate_first = true;
-  int src = 0;          // forward: offset of its values in the input buffer; adjoint: 16 * gate
-  uint64_t perm = 0;    // dense two-qubit gates: nibble 4 m + k names the value of entry (m, k)
+  int val[16] = {0};    // offsets of its values: 2^n diagonal entries, or 4^n dense ones (m, k) row-major
   int form = 0;         // dense: GateForm
   int signs = -1;       // diagonal of known entries +-1: 2 (Z) or 8 (CZ)
   int ones = 0;         // two-bit diagonals: entries known to be exactly 1
@@ -575,7 +578,7 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
 void build_reg_pass(tn_path* path, SweepPass& ps, int R);
 void build_adj_reg_pass(tn_path* path, SweepPass& ps, int R);
 // seqpass.cpp: ordered passes over `items` on a 2^R state, chunks of at most 2^lmax elements
-bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, SeqProgram* out);
+bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool adjoint, SeqProgram* out);
 // moves every step that is small and depends only on inputs or such steps to the
 // front; of the rest, likely per-output products that are ready together are
 // placed next to each other

@@ -176,8 +176,9 @@ hipError_t launch_adjoint_regs(hipStream_t s, const SweepPass& ps, int bits, con
 // seq_adjoint_columns() columns per slot.
 struct SeqTables {
   const SeqSeg* segs;
-  const SeqOp* ops;
+  const SeqWindow* wins;
   const uint32_t* words;
+  const int32_t* vals;
 };
 hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const SeqSeg& last,
                               const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,

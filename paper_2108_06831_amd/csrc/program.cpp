@@ -695,6 +695,7 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
   path->seq = SeqChain();
   const int T = (int)net->tensors.size();
   const int S = (int)path->pairs.size() / 2;
+  if (S < kSeqMinRun) return;
   std::vector<char> zero(T + S, 0);
   int n_zero = 0;
   for (int t = 0; t < T; ++t)
@@ -724,7 +725,7 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
     auto result_has = [&](int m) { return std::find(modes[T + s].begin(), modes[T + s].end(), m) != modes[T + s].end(); };
     SeqItem it;
     it.gate_first = ia == g;
-    it.src = (int)loc[g].ref.off;
+    const int off = (int)loc[g].ref.off;
     std::vector<int> kpos, kaddr, maddr;  // summed bits: positions in the state; addresses in G
     std::vector<int32_t> mlab;
     bool batch_only = true;
@@ -750,6 +751,7 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
       if (gn < 1 || gn > 2 || !r.diag) break;
       it.diag = true;
       it.n = gn;
+      for (int b = 0; b < (1 << gn); ++b) it.val[b] = off + b;
       if (whole && single && gn == r.nq) {
         if (kind0 == TN_GATE_Z) it.signs = 2;
         if (kind0 == TN_GATE_CZ) it.signs = 8;
@@ -760,7 +762,6 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
       it.n = (int)kpos.size();
       if ((int)mlab.size() != it.n || it.n > 2 || gn != 2 * it.n) break;
       if (it.n == 1) {
-        if (kaddr[0] != 0 || maddr[0] != 1) break;
         it.pos[0] = kpos[0];
         bool real = whole && r.nq == 1, rxl = real;
         for (int o = r.op_begin; o < r.op_end; ++o) {
@@ -776,13 +777,13 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
         }
         it.pos[0] = kpos[0];
         it.pos[1] = kpos[1];
-        for (int m = 0; m < 4; ++m)
-          for (int k = 0; k < 4; ++k) {
-            uint64_t a = 0;
-            for (int j = 0; j < 2; ++j) a |= (uint64_t)((m >> j) & 1) << maddr[j] | (uint64_t)((k >> j) & 1) << kaddr[j];
-            it.perm |= a << (4 * (4 * m + k));
-          }
       }
+      for (int m = 0; m < (1 << it.n); ++m)
+        for (int k = 0; k < (1 << it.n); ++k) {
+          int v = off;
+          for (int j = 0; j < it.n; ++j) v += (((m >> j) & 1) << maddr[j]) | (((k >> j) & 1) << kaddr[j]);
+          it.val[(m << it.n) + k] = v;
+        }
       for (int j = 0; j < it.n; ++j) cur[cur.size() - 1 - it.pos[j]] = mlab[j];
     }
     const std::vector<int32_t>& cb = loc[T + s].bits;
@@ -809,7 +810,7 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
   }
   if (ch.out.buf != BUF_WS) return;
   ch.last = ch.end == S;
-  if (!build_seq_program(ch.bits, items, kSeqMaxLocal, &ch.prog)) return;
+  if (!build_seq_program(ch.bits, items, kSeqMaxLocal, false, &ch.prog)) return;
   path->seq = std::move(ch);
 }
 
@@ -1552,7 +1553,13 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
       SeqItem it;
       it.n = g.nq;
       it.diag = g.diag != 0;
-      it.src = 16 * gi;
+      // entries of U^dagger (the kernel conjugates): the diagonal, or (m, k) = U[k][m]
+      const int d = 1 << g.nq;
+      for (int m = 0; m < d; ++m) {
+        if (it.diag) it.val[m] = 16 * gi + m * (d + 1);
+        else
+          for (int k = 0; k < d; ++k) it.val[m * d + k] = 16 * gi + k * d + m;
+      }
       const int p0 = pos_of(path->final_bits, net->wire_final[g.q[0]] * 64);
       const int p1 = g.nq == 2 ? pos_of(path->final_bits, net->wire_final[g.q[1]] * 64) : 0;
       if (p0 < 0 || p1 < 0) return;
@@ -1578,7 +1585,7 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
       }
       items.push_back(it);
     }
-    if (build_seq_program(R, items, kSeqAdjMaxLocal, &path->adj_seq)) path->adj_state = 2;
+    if (build_seq_program(R, items, kSeqAdjMaxLocal, true, &path->adj_seq)) path->adj_state = 2;
     return;
   }
   // the passes' operations in a layout (-1: a gate the passes cannot take)

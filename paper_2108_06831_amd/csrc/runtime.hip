@@ -231,11 +231,13 @@ struct DevPath {
   RegPhase* reg_phases = nullptr;
   uint32_t* reg_words = nullptr;
   SeqSeg* seq_segs = nullptr;           // ordered passes
-  SeqOp* seq_ops = nullptr;
+  SeqWindow* seq_wins = nullptr;
   uint32_t* seq_words = nullptr;
+  int32_t* seq_vals = nullptr;
   SeqSeg* adj_seq_segs = nullptr;       // uploaded on the first backward call
-  SeqOp* adj_seq_ops = nullptr;
+  SeqWindow* adj_seq_wins = nullptr;
   uint32_t* adj_seq_words = nullptr;
+  int32_t* adj_seq_vals = nullptr;
   AdjGateDesc* adj_gates = nullptr;     // uploaded on the first backward call
   SweepSegment* adj_segments = nullptr;
   RegSeg* adj_reg_segs = nullptr;
@@ -266,8 +268,9 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   HIP_TRY(upload(&d->reg_phases, path->reg_phases));
   HIP_TRY(upload(&d->reg_words, path->reg_words));
   HIP_TRY(upload(&d->seq_segs, path->seq.prog.segs));
-  HIP_TRY(upload(&d->seq_ops, path->seq.prog.ops));
+  HIP_TRY(upload(&d->seq_wins, path->seq.prog.wins));
   HIP_TRY(upload(&d->seq_words, path->seq.prog.words));
+  HIP_TRY(upload(&d->seq_vals, path->seq.prog.vals));
   *out = d;
   return TN_OK;
 }
@@ -288,8 +291,8 @@ void device_release_path(tn_path* path) {
   (void)hipFree(d->slice_tensors);
   for (void* p : {(void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
                   (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words,
-                  (void*)d->seq_segs, (void*)d->seq_ops, (void*)d->seq_words, (void*)d->adj_seq_segs,
-                  (void*)d->adj_seq_ops, (void*)d->adj_seq_words})
+                  (void*)d->seq_segs, (void*)d->seq_wins, (void*)d->seq_words, (void*)d->seq_vals, (void*)d->adj_seq_segs,
+                  (void*)d->adj_seq_wins, (void*)d->adj_seq_words, (void*)d->adj_seq_vals})
     (void)hipFree(p);
   (void)hipFree(d->adj_gates);
   (void)hipFree(d->adj_segments);
@@ -392,7 +395,7 @@ static tn_status run_seq(hipStream_t s, tn_path* path, DevPath* dp, const Bases&
   for (int i = 0; i < n; ++i) {
     const SeqPass& ps = ch.prog.passes[i];
     const bool last = i == n - 1;
-    HIP_TRY(launch_seq_forward(s, ps, ch.bits, SeqTables{dp->seq_segs, dp->seq_ops, dp->seq_words},
+    HIP_TRY(launch_seq_forward(s, ps, ch.bits, SeqTables{dp->seq_segs, dp->seq_wins, dp->seq_words, dp->seq_vals},
                                ch.prog.segs[ps.first_seg + ps.n_segs - 1], i == 0 ? nullptr : out, obs,
                                last && direct ? B.final_out : out, last && direct ? B.final_out_bs : obs,
                                last ? pos : nullptr, in, ibs, batch, precision));
@@ -1301,8 +1304,9 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     const SeqProgram& pr = path->adj_seq;
     if (!dp->adj_seq_segs) {
       HIP_TRY(upload(&dp->adj_seq_segs, pr.segs));
-      HIP_TRY(upload(&dp->adj_seq_ops, pr.ops));
+      HIP_TRY(upload(&dp->adj_seq_wins, pr.wins));
       HIP_TRY(upload(&dp->adj_seq_words, pr.words));
+      HIP_TRY(upload(&dp->adj_seq_vals, pr.vals));
     }
     const int bits = (int)path->final_bits.size();
     n_cols = seq_adjoint_columns(pr.passes[0], bits);
@@ -1310,7 +1314,7 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     for (const SweepGate& g : net->sweep) fl += (2.0 * 8.0 * (1 << g.nq) + (g.gen != GEN_NONE ? 8.0 : 0.0)) * (double)n;
     hipEvent_t ev = prof_start(s, TN_KERNEL_ADJOINT);
     for (const SeqPass& ps : pr.passes)
-      HIP_TRY(launch_seq_adjoint(s, ps, bits, SeqTables{dp->adj_seq_segs, dp->adj_seq_ops, dp->adj_seq_words}, umats,
+      HIP_TRY(launch_seq_adjoint(s, ps, bits, SeqTables{dp->adj_seq_segs, dp->adj_seq_wins, dp->adj_seq_words, dp->adj_seq_vals}, umats,
                                  (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride,
                                  precision));
     prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * pr.passes.size() * batch, fl * batch);

@@ -17,6 +17,7 @@ namespace {
 struct SegBuild {
   std::vector<int> bits;       // address positions in the registers, by register bit
   std::vector<int> items;
+  int words = 0, vals = 0;     // upper bounds
 };
 
 int find(const std::vector<int>& v, int x) {
@@ -42,16 +43,13 @@ bool join(SegBuild& s, const SeqItem& it) {
   return true;
 }
 
-SeqOp new_op(int type) {
-  SeqOp o{};
-  o.type = type;
-  for (int j = 0; j < 4; ++j) o.red[j] = o.dred[j] = -1;
-  return o;
-}
+// words and values an item may need at most
+int words_of(const SeqItem&) { return 3; }
+int vals_of(const SeqItem& it) { return it.diag ? 1 << it.n : 1 << (2 * it.n); }
 
 }  // namespace
 
-bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, SeqProgram* out) {
+bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool adjoint, SeqProgram* out) {
   *out = SeqProgram();
   if (R < kSeqMinBits || R > 31) return false;
   const int l = std::min(R, lmax), low = std::min(5, l);
@@ -87,14 +85,18 @@ bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, SeqPr
       if (local[p]) ps.lpos[n++] = (int8_t)p;
     for (; n < kSeqMaxLocal; ++n) ps.lpos[n] = 0;
     ps.first_seg = (int32_t)out->segs.size();
+    ps.first_win = (int32_t)out->wins.size();
     // segments
     std::vector<SegBuild> sb(1);
     for (size_t k = i; k < e; ++k) {
-      if (!join(sb.back(), items[k])) {
+      if (sb.back().words + words_of(items[k]) > kSeqWinWords || sb.back().vals + vals_of(items[k]) > kSeqWinVals ||
+          !join(sb.back(), items[k])) {
         sb.emplace_back();
         if (!join(sb.back(), items[k])) return false;
       }
       sb.back().items.push_back((int)k);
+      sb.back().words += words_of(items[k]);
+      sb.back().vals += vals_of(items[k]);
     }
     for (SegBuild& s : sb) {
       // unused register bits: the highest local ones, which leave the lanes consecutive addresses
@@ -114,80 +116,81 @@ bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, SeqPr
         }
       }
       for (int c = 0; c < 16; ++c) g.physoff[c] += g.physoff[c] >> 5;
-      g.op_off = (int32_t)out->ops.size();
-      // the operation the next item may join (-1: none), and the register bit it has reached
-      int cur = -1, reached = -1;
-      for (int k : s.items) {
-        const SeqItem& it = items[k];
+      const size_t w0 = out->words.size(), v0 = out->vals.size();
+      auto emit = [&](uint32_t w) { out->words.push_back(w); };
+      auto values = [&](const SeqItem& it) {
+        for (int j = 0; j < vals_of(it); ++j) out->vals.push_back(it.val[j]);
+      };
+      auto slot_word = [](const SeqItem& it) { return (uint32_t)it.gen | ((uint32_t)(it.red + 1) << 8); };
+      for (size_t x = 0; x < s.items.size();) {
+        const SeqItem& it = items[s.items[x]];
         const int k0 = find(s.bits, it.pos[0]), k1 = it.n == 2 ? find(s.bits, it.pos[1]) : -1;
-        if (it.diag && it.signs >= 0 && it.red < 0) {
+        g.n_op++;
+        if (it.diag && it.signs >= 0 && it.red < 0) {  // a run of sign flips
           static const int half[4] = {0xAAAA, 0xCCCC, 0xF0F0, 0xFF00};
-          if (cur < 0 || out->ops[cur].type != SEQ_SIGNS) {
-            cur = (int)out->ops.size();
-            out->ops.push_back(new_op(SEQ_SIGNS));
-            out->ops[cur].off = (int32_t)out->words.size();
+          int mask = 0;
+          std::vector<uint32_t> w;
+          for (; x < s.items.size(); ++x) {
+            const SeqItem& d = items[s.items[x]];
+            if (!d.diag || d.signs < 0 || d.red >= 0) break;
+            const int p0 = d.pos[0], p1 = d.n == 2 ? d.pos[1] : d.pos[0];
+            const int r0 = find(s.bits, p0), r1 = find(s.bits, p1);
+            if (r0 >= 0 && r1 >= 0) {
+              mask ^= half[r0] & half[r1];
+            } else {
+              const int ones = r0 >= 0 ? half[r0] : r1 >= 0 ? half[r1] : 0xFFFF;
+              w.push_back((uint32_t)(r0 >= 0 ? p1 : p0) | ((uint32_t)(r1 >= 0 ? p0 : p1) << 8) | ((uint32_t)ones << 16));
+            }
           }
-          SeqOp& o = out->ops[cur];
-          const int p0 = it.pos[0], p1 = it.n == 2 ? it.pos[1] : it.pos[0];
-          const int r1 = it.n == 2 ? k1 : k0;
-          if (k0 >= 0 && r1 >= 0) {
-            o.mask ^= half[k0] & half[r1];
-          } else {
-            const int ones = k0 >= 0 ? half[k0] : r1 >= 0 ? half[r1] : 0xFFFF;
-            const int p = k0 >= 0 ? p1 : p0, q = r1 >= 0 ? p0 : p1;
-            out->words.push_back((uint32_t)p | ((uint32_t)q << 8) | ((uint32_t)ones << 16));
-            o.n++;
+          emit(SEQ_SIGNS | ((uint32_t)mask << 16));
+          emit((uint32_t)w.size());
+          out->words.insert(out->words.end(), w.begin(), w.end());
+        } else if (it.n == 1 && k0 >= 0) {  // dense gates and diagonals on ascending register bits
+          uint32_t head = SEQ_BITS;
+          std::vector<uint32_t> w;
+          int reached = -1;
+          for (; x < s.items.size(); ++x) {
+            const SeqItem& d = items[s.items[x]];
+            const int r = find(s.bits, d.pos[0]);
+            if (d.n != 1 || r < 0 || (d.diag && d.signs >= 0 && d.red < 0)) break;
+            if (!(r > reached || (r == reached && d.diag && !((head >> (8 + r)) & 1)))) break;
+            reached = r;
+            if (d.diag) {
+              head |= (1u << (8 + r)) | (d.gate_first ? 1u << (16 + r) : 0);
+            } else {
+              head |= (1u << (4 + r)) | (d.gate_first ? 1u << (12 + r) : 0) | ((uint32_t)(d.form & 3) << (20 + 2 * r));
+            }
+            w.push_back(slot_word(d));
+            values(d);
           }
-          continue;
-        }
-        if (it.n == 1 && k0 >= 0) {  // a dense gate, or a diagonal on a register bit
-          const bool joins = cur >= 0 && out->ops[cur].type == SEQ_BITS &&
-                             (k0 > reached || (k0 == reached && it.diag && !((out->ops[cur].dmask >> k0) & 1)));
-          if (!joins) {
-            cur = (int)out->ops.size();
-            out->ops.push_back(new_op(SEQ_BITS));
-          }
-          reached = k0;
-          SeqOp& o = out->ops[cur];
-          if (it.diag) {
-            o.dmask |= 1 << k0;
-            o.gfirst |= it.gate_first ? 16 << k0 : 0;
-            o.dsrc[k0] = it.src;
-            o.dred[k0] = it.red;
-          } else {
-            o.mask |= 1 << k0;
-            o.gfirst |= it.gate_first ? 1 << k0 : 0;
-            o.src[k0] = it.src;
-            o.form[k0] = it.form;
-            o.red[k0] = it.red;
-            o.gform[k0] = it.gen;
-          }
-          continue;
-        }
-        cur = -1;
-        SeqOp o = new_op(it.diag ? SEQ_DIAG : SEQ_DENSE2);
-        o.gfirst = it.gate_first ? 1 : 0;
-        o.src[0] = it.src;
-        o.red[0] = it.red;
-        o.gen = it.gen;
-        if (it.diag) {
-          o.mask = it.n;
-          o.ones = it.ones;
-          o.dsrc[0] = k0;
-          o.dsrc[1] = k1;
-          o.dsrc[2] = it.pos[0];
-          o.dsrc[3] = it.pos[1];
+          emit(head);
+          if (adjoint) out->words.insert(out->words.end(), w.begin(), w.end());
+        } else if (it.diag) {
+          emit(SEQ_DIAG | ((uint32_t)it.n << 4) | (it.gate_first ? 1u << 12 : 0));
+          emit((uint32_t)(k0 + 1) | ((uint32_t)(k1 + 1) << 4) | ((uint32_t)it.pos[0] << 8) | ((uint32_t)it.pos[1] << 16));
+          emit((uint32_t)it.ones | ((uint32_t)it.gen << 4) | ((uint32_t)(it.red + 1) << 8));
+          values(it);
+          ++x;
         } else {
           if (it.red >= 0 || !((k0 == 0 && k1 == 1) || (k0 == 2 && k1 == 3))) return false;
-          o.mask = k0 / 2;
-          o.perm[0] = (uint32_t)it.perm;
-          o.perm[1] = (uint32_t)(it.perm >> 32);
+          emit(SEQ_DENSE2 | ((uint32_t)(k0 / 2) << 4) | (it.gate_first ? 1u << 12 : 0));
+          values(it);
+          ++x;
         }
-        out->ops.push_back(o);
       }
-      g.n_op = (int32_t)out->ops.size() - g.op_off;
+      const int nw = (int)(out->words.size() - w0), nv = (int)(out->vals.size() - v0);
+      if (nw > kSeqWinWords || nv > kSeqWinVals) return false;
+      SeqWindow* win = (int)out->wins.size() > ps.first_win ? &out->wins.back() : nullptr;
+      if (!win || win->n_words + nw > kSeqWinWords || win->n_vals + nv > kSeqWinVals) {
+        out->wins.push_back(SeqWindow{0, (int32_t)w0, 0, (int32_t)v0, 0, {0, 0, 0}});
+        win = &out->wins.back();
+      }
+      win->n_segs++;
+      win->n_words += nw;
+      win->n_vals += nv;
       out->segs.push_back(g);
     }
+    ps.n_wins = (int32_t)out->wins.size() - ps.first_win;
     ps.n_segs = (int32_t)out->segs.size() - ps.first_seg;
     out->passes.push_back(ps);
     i = e;

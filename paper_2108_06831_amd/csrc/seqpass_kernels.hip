@@ -60,7 +60,7 @@ __device__ __forceinline__ void dense_seq(float2 (&x)[16], float2 g0, float2 g1,
       "v_fma_f32 %0, %4, %1, %0\n\t"                                                    \
       "v_fma_f32 %1, %6, %1, %2"                                                        \
       : "+v"(A), "+v"(B), "=&v"(t)                                                      \
-      : "s"(g0.x), "s"(g1.x), "s"(g2.x), "s"(g3.x));
+      : "v"(g0.x), "v"(g1.x), "v"(g2.x), "v"(g3.x));
       TNQ_PAIR(a.x, b.x)
       TNQ_PAIR(a.y, b.y)
 #undef TNQ_PAIR
@@ -80,7 +80,7 @@ __device__ __forceinline__ void dense_seq(float2 (&x)[16], float2 g0, float2 g1,
           "v_fma_f32 %2, %9, %2, %4\n\t"
           "v_fma_f32 %3, %9, %3, %5"
           : "+v"(a.x), "+v"(a.y), "+v"(b.x), "+v"(b.y), "=&v"(t0), "=&v"(t1)
-          : "s"(g0.x), "s"(g1.y), "s"(g2.y), "s"(g3.x));
+          : "v"(g0.x), "v"(g1.y), "v"(g2.y), "v"(g3.x));
     }
   } else if (gate_first) {
 #pragma unroll
@@ -202,12 +202,15 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 // gate; gradient slot s of wave w of chunk c into partials[s][c * waves + w].
 template <int PREC, int NS, int LMAX>
 __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const SeqSeg* __restrict__ segs,
-                                                              const SeqOp* __restrict__ ops,
+                                                              const SeqWindow* __restrict__ wins,
                                                               const uint32_t* __restrict__ words,
+                                                              const int32_t* __restrict__ vsrc,
                                                               const float2* __restrict__ vals) {
   constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
   __shared__ float2 bx[kBuf];
   __shared__ float2 by[NS == 2 ? kBuf : 1];
+  __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];  // the window's values (a reverse sweep's conjugated)
+  __shared__ uint32_t wwin[kSeqWinWords];
   const int z = blockIdx.y, lane = threadIdx.x & 63;
   // chunks of fewer than 2^10 elements leave threads of the wave without elements: they repeat others
   const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
@@ -225,7 +228,22 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
   float2 x[16], y[16];  // psi (or the state), lambda
   int slot = 0;
   const int32_t* off = nullptr;
+  int win = 0, win_end = 0;  // the window's number and the end of its segments
+  int wi = 0, vi = 0;        // the next operation's word and value
+  auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)wwin[i]); };
   for (int sg = 0; sg < a.n_segs; ++sg) {
+    if (sg == win_end) {
+      const SeqWindow w = wins[win++];
+      __syncthreads();  // the window before is no longer read
+      for (int i = threadIdx.x; i < w.n_words; i += blockDim.x) wwin[i] = words[w.word_off + i];
+      for (int i = threadIdx.x; i < w.n_vals; i += blockDim.x) {
+        const float2 v = V[vsrc[w.val_off + i]];
+        vwin[i] = NS == 2 ? f2(v.x, -v.y) : v;
+      }
+      __syncthreads();
+      win_end = sg + w.n_segs;
+      wi = vi = 0;
+    }
     const SeqSeg& seg = segs[sg];
     const int ob = bits10(tid, seg.tpos), ns = ob + (ob >> 5);
     const uint32_t A = base | (uint32_t)bits10(tid, seg.gpos);
@@ -257,33 +275,29 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
     }
     slot = ns;
     off = seg.physoff;
-    for (int oi = seg.op_off; oi < seg.op_off + seg.n_op; ++oi) {
-      const SeqOp& op = ops[oi];
-      if (op.type & SEQ_BITS) {
+    for (int oi = 0; oi < seg.n_op; ++oi) {
+      const uint32_t head = word(wi++);
+      if (head & SEQ_BITS) {
 #define TNQ_SEQ_BIT(R)                                                                                        \
-  if ((op.mask >> R) & 1) {                                                                                   \
-    if (NS == 2 && op.red[R] >= 0) add_grad(op.red[R], grad_bit<R>(x, y, op.gform[R]));                       \
-    const float2* u = V + op.src[R];                                                                          \
-    float2 g0 = u[0], g1 = u[1], g2 = u[2], g3 = u[3];                                                        \
-    if (NS == 2) { /* U^dagger[m][k] = conj(U[k][m]) */                                                       \
-      const float2 w = g1;                                                                                    \
-      g0 = f2(g0.x, neg_s(g0.y));                                                                             \
-      g1 = f2(g2.x, neg_s(g2.y));                                                                             \
-      g2 = f2(w.x, neg_s(w.y));                                                                               \
-      g3 = f2(g3.x, neg_s(g3.y));                                                                             \
-    }                                                                                                         \
-    dense_seq<PREC, R>(x, g0, g1, g2, g3, op.form[R], NS == 2 || ((op.gfirst >> R) & 1));                     \
-    if (NS == 2) dense_seq<PREC, R>(y, g0, g1, g2, g3, op.form[R], true);                                     \
-  }                                                                                                           \
-  if ((op.dmask >> R) & 1) {                                                                                  \
-    if (NS == 2 && op.dred[R] >= 0) add_grad(op.dred[R], grad_bit<R>(x, y, GEN_Z_HALF));                      \
-    const float2* u = V + op.dsrc[R];                                                                         \
-    float2 e0 = u[0], e1 = u[NS == 2 ? 3 : 1];                                                                \
+  if ((head >> (4 + R)) & 1) {                                                                                \
     if (NS == 2) {                                                                                            \
-      e0.y = -e0.y;                                                                                           \
-      e1.y = -e1.y;                                                                                           \
+      const uint32_t w = word(wi++);                                                                          \
+      if (w >> 8) add_grad((int)(w >> 8) - 1, grad_bit<R>(x, y, (int)(w & 255)));                             \
     }                                                                                                         \
-    diag_seq<PREC, R>(x, e0, e1, NS == 2 || ((op.gfirst >> (4 + R)) & 1));                                    \
+    const float2 g0 = vwin[vi], g1 = vwin[vi + 1], g2 = vwin[vi + 2], g3 = vwin[vi + 3];                      \
+    vi += 4;                                                                                                  \
+    const int form = (head >> (20 + 2 * R)) & 3;                                                              \
+    dense_seq<PREC, R>(x, g0, g1, g2, g3, form, NS == 2 || ((head >> (12 + R)) & 1));                         \
+    if (NS == 2) dense_seq<PREC, R>(y, g0, g1, g2, g3, form, true);                                           \
+  }                                                                                                           \
+  if ((head >> (8 + R)) & 1) {                                                                                \
+    if (NS == 2) {                                                                                            \
+      const uint32_t w = word(wi++);                                                                          \
+      if (w >> 8) add_grad((int)(w >> 8) - 1, grad_bit<R>(x, y, GEN_Z_HALF));                                 \
+    }                                                                                                         \
+    const float2 e0 = vwin[vi], e1 = vwin[vi + 1];                                                            \
+    vi += 2;                                                                                                  \
+    diag_seq<PREC, R>(x, e0, e1, NS == 2 || ((head >> (16 + R)) & 1));                                        \
     if (NS == 2) diag_seq<PREC, R>(y, e0, e1, true);                                                          \
   }
         TNQ_SEQ_BIT(0)
@@ -292,12 +306,14 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
         TNQ_SEQ_BIT(3)
 #undef TNQ_SEQ_BIT
       }
-      if (op.type & SEQ_SIGNS) {
-        uint32_t m = (uint32_t)op.mask;
-        for (int i = op.off; i < op.off + op.n; ++i) {
-          const uint32_t w = words[i];
+      if (head & SEQ_SIGNS) {
+        uint32_t m = head >> 16;
+        const int n = (int)word(wi++);
+        for (int i = wi; i < wi + n; ++i) {
+          const uint32_t w = wwin[i];
           m ^= (0u - ((A >> (w & 31)) & (A >> ((w >> 8) & 31)) & 1u)) & (w >> 16);
         }
+        wi += n;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const uint32_t s = (m << (31 - r)) & 0x80000000u;
@@ -305,80 +321,67 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
           if (NS == 2) y[r] = flip_s(times_one<PREC>(y[r]), s);
         }
       }
-      if (op.type & SEQ_DIAG) {
-        const int k0 = op.dsrc[0], k1 = op.dsrc[1];
-        const bool two = op.mask == 2, gf = NS == 2 || (op.gfirst & 1);
-        const int c0 = (A >> (op.dsrc[2] & 31)) & 1, c1 = two ? (A >> (op.dsrc[3] & 31)) & 1 : 0;
-        const float2* u = V + op.src[0];
-        float2 d0 = u[0], d1 = u[NS == 2 ? (two ? 5 : 3) : 1], d2 = d0, d3 = d0;
+      if (head & SEQ_DIAG) {
+        const uint32_t w1 = word(wi), w2 = word(wi + 1);
+        wi += 2;
+        const int k0 = (int)(w1 & 15) - 1, k1 = (int)((w1 >> 4) & 15) - 1;
+        const bool two = ((head >> 4) & 15) == 2, gf = NS == 2 || ((head >> 12) & 1);
+        const int c0 = (A >> ((w1 >> 8) & 31)) & 1, c1 = two ? (A >> ((w1 >> 16) & 31)) & 1 : 0;
+        const float2 d0 = vwin[vi], d1 = vwin[vi + 1];
+        float2 d2 = d0, d3 = d0;
         if (two) {
-          d2 = u[NS == 2 ? 10 : 2];
-          d3 = u[NS == 2 ? 15 : 3];
+          d2 = vwin[vi + 2];
+          d3 = vwin[vi + 3];
         }
-        if (NS == 2) {
-          d0.y = -d0.y;
-          d1.y = -d1.y;
-          d2.y = -d2.y;
-          d3.y = -d3.y;
-        }
-        if (NS == 2 && op.red[0] >= 0) {
+        vi += two ? 4 : 2;
+        if (NS == 2 && (w2 >> 8)) {
+          const int gen = (int)((w2 >> 4) & 15);
           double g = 0.0;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int b0 = k0 >= 0 ? (r >> k0) & 1 : c0, b1 = k1 >= 0 ? (r >> k1) & 1 : c1;
-            const double w = op.gen == GEN_ZZ_PHASE ? (b0 != b1 ? 2.0 : 0.0)
-                             : op.gen == GEN_CPHASE ? (b0 && b1 ? -2.0 : 0.0)
-                                                    : (b0 ? -1.0 : 1.0);
+            const double w = gen == GEN_ZZ_PHASE ? (b0 != b1 ? 2.0 : 0.0)
+                             : gen == GEN_CPHASE ? (b0 && b1 ? -2.0 : 0.0)
+                                                 : (b0 ? -1.0 : 1.0);
             g += w * im_d(y[r], x[r]);
           }
-          add_grad(op.red[0], g);
+          add_grad((int)(w2 >> 8) - 1, g);
         }
         if (two && k0 >= 0 && k1 >= 0) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int b = ((r >> k0) & 1) | (((r >> k1) & 1) << 1);
-            if (PREC == TN_PREC_C64 && ((op.ones >> b) & 1)) continue;
+            if (PREC == TN_PREC_C64 && ((w2 >> b) & 1)) continue;
             const float2 q = b == 0 ? d0 : b == 1 ? d1 : b == 2 ? d2 : d3;
-            mul_gate<PREC>(x[r], q, gf);
+            if (gf) mul_gate<PREC>(x[r], q, true);
+            else mul_gate<PREC>(x[r], q, false);
             if (NS == 2) mul_gate<PREC>(y[r], q, true);
           }
         } else if (two && (k0 >= 0 || k1 >= 0)) {
           const int k = k0 >= 0 ? k0 : k1;
           const float2 e0 = k0 >= 0 ? (c1 ? d2 : d0) : (c0 ? d1 : d0), e1 = k0 >= 0 ? (c1 ? d3 : d1) : (c0 ? d3 : d2);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float2 q = (r >> k) & 1 ? e1 : e0;
-            mul_gate<PREC>(x[r], q, gf);
-            if (NS == 2) mul_gate<PREC>(y[r], q, true);
-          }
+          if (k == 0) { diag_seq<PREC, 0>(x, e0, e1, gf); if (NS == 2) diag_seq<PREC, 0>(y, e0, e1, true); }
+          if (k == 1) { diag_seq<PREC, 1>(x, e0, e1, gf); if (NS == 2) diag_seq<PREC, 1>(y, e0, e1, true); }
+          if (k == 2) { diag_seq<PREC, 2>(x, e0, e1, gf); if (NS == 2) diag_seq<PREC, 2>(y, e0, e1, true); }
+          if (k == 3) { diag_seq<PREC, 3>(x, e0, e1, gf); if (NS == 2) diag_seq<PREC, 3>(y, e0, e1, true); }
         } else {
           const float2 lo = c0 ? d1 : d0, hi = c0 ? d3 : d2;
           const float2 q = two && c1 ? hi : lo;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            mul_gate<PREC>(x[r], q, gf);
-            if (NS == 2) mul_gate<PREC>(y[r], q, true);
-          }
+          diag_seq<PREC, 0>(x, q, q, gf);
+          if (NS == 2) diag_seq<PREC, 0>(y, q, q, true);
         }
       }
-      if (op.type & SEQ_DENSE2) {
-        const float2* u = V + op.src[0];
-        const uint32_t p0 = op.perm[0], p1 = op.perm[1];
-        auto get = [&](int e) {
-          if (NS == 2) {  // U^dagger
-            const float2 w = u[4 * (e & 3) + (e >> 2)];
-            return f2(w.x, -w.y);
-          }
-          return u[((e < 8 ? p0 : p1) >> (4 * (e & 7))) & 15];
-        };
-        const bool gf = NS == 2 || (op.gfirst & 1);
-        if (op.mask == 0) {
+      if (head & SEQ_DENSE2) {
+        auto get = [&](int e) { return vwin[vi + e]; };
+        const bool gf = NS == 2 || ((head >> 12) & 1);
+        if (((head >> 4) & 15) == 0) {
           dense2_seq<PREC, 0>(x, get, gf);
           if (NS == 2) dense2_seq<PREC, 0>(y, get, true);
         } else {
           dense2_seq<PREC, 1>(x, get, gf);
           if (NS == 2) dense2_seq<PREC, 1>(y, get, true);
         }
+        vi += 16;
       }
     }
     if (sg == a.n_segs - 1) {
@@ -406,10 +409,11 @@ void seq_launch(hipStream_t s, const SeqArgs& a, const SeqTables& t, const SeqPa
                 int batch) {
   const dim3 grid(chunks, batch), block(std::max(64, 1 << (ps.l - 4)));
   if (ps.l <= 12)
-    hipLaunchKernelGGL((k_seq_pass<PREC, NS, 12>), grid, block, 0, s, a, t.segs + ps.first_seg, t.ops, t.words, vals);
+    hipLaunchKernelGGL((k_seq_pass<PREC, NS, 12>), grid, block, 0, s, a, t.segs + ps.first_seg, t.wins + ps.first_win,
+                       t.words, t.vals, vals);
   else
     hipLaunchKernelGGL((k_seq_pass<PREC, NS, NS == 2 ? kSeqAdjMaxLocal : kSeqMaxLocal>), grid, block, 0, s, a,
-                       t.segs + ps.first_seg, t.ops, t.words, vals);
+                       t.segs + ps.first_seg, t.wins + ps.first_win, t.words, t.vals, vals);
 }
 
 // the pass's chunk and the bits outside it (out_pos[p]: position of address bit p in the result, NULL: p)

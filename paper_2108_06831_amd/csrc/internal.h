@@ -396,8 +396,10 @@ constexpr int kElemSkinnyBits = 15;
 inline bool elem_group_shape(int out_bits, int m_bits, int n_bits, int k_bits) {
   return out_bits <= kElemSmallBits && k_bits <= kElemKBits && (m_bits < 6 || n_bits < 5 || k_bits <= 5);
 }
-// default launch shape of a product (before any measurement)
-void gemm_default_launch(const GemmDesc& g, int* tile, int* split);
+// default launch shapes of a product's two orientations for a precision (before any measurement);
+// returns the orientation to run
+int gemm_default_launch(GemmDesc (&gm)[2], int prec);
+void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split);
 
 // A small step executed inside the interpreter kernel: every operand and the
 // result fit in a few KB.  C's address bit p comes from A's bit apos[p] and/or

@@ -1170,32 +1170,13 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
         g.a = GA.ref;
         g.b = GB.ref;
         g.c = C.ref;
-        int tile, split;
-        gemm_default_launch(g, &tile, &split);
-        g.tile[0] = g.tile[1] = tile;
-        g.split[0] = g.split[1] = split;
-        // FP32: the three-product form where its 64-column tiles fit
-        if ((tile == 0 || tile == 2) && g.N >= 64) g.tile[TN_PREC_C64] = tile == 0 ? 5 : 6;
-        // room for the autotuner to try K splits of products with a small result
-        g.max_split = split;
+        // scratch for K splits: the autotuner may try up to kGemmMaxSplit where the result is small
+        int tile;
+        gemm_tile_by_blocks(g, &tile, &g.max_split);
         if (tile != kGemmVector && C.elems * kGemmMaxSplit <= ((int64_t)1 << 22) && g.K >= 64)
           g.max_split = kGemmMaxSplit;
       }
-      // a matrix-core tile stores each row of its result as 32 consecutive columns per wave:
-      // for a short sum the stores are the product's time, so take the orientation whose
-      // columns are the result's lowest address bits (the tuner may still choose otherwise)
-      P.orient[0] = P.orient[1] = 0;
-      {
-        auto low_n = [](const GemmDesc& g) {
-          int c = 0;
-          while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
-          return c;
-        };
-        for (int prec = 0; prec < 2; ++prec)
-          if (P.gm[0].K <= 32 && P.gm[0].tile[prec] != kGemmVector && P.gm[1].tile[prec] != kGemmVector &&
-              low_n(P.gm[1]) > low_n(P.gm[0]))
-            P.orient[prec] = 1;
-      }
+      for (int prec = 0; prec < 2; ++prec) P.orient[prec] = gemm_default_launch(P.gm, prec);
       const int max_split = std::max(P.gm[0].max_split, P.gm[1].max_split);
       if (max_split > 1) {
         BufRef tmp;
@@ -1727,7 +1708,8 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
   path->adj_state = 1;
 }
 
-void gemm_default_launch(const GemmDesc& g, int* tile, int* split) {
+// The real-embedding tile with at least two blocks per compute unit, or the vector kernel.
+void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split) {
   *split = 1;
   // narrow products, and small ones with a short sum (latency-bound either way;
   // on the per-output kernel they can share a launch)
@@ -1751,6 +1733,65 @@ void gemm_default_launch(const GemmDesc& g, int* tile, int* split) {
   int sp = 1;
   while (sp < kGemmMaxSplit && blocks * sp * 2 <= 1024 && g.K / (sp * 2) >= 32 && g.K % (sp * 2) == 0) sp *= 2;
   *split = sp;
+}
+
+// Default launch shapes of a product for `prec`, set in both orientations; returns the one to run.
+// Each line below is where whole passes timed the other way (microseconds per pass of the workload
+// named, the products in question changed alone):
+int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
+  const bool c64 = prec == TN_PREC_C64;
+  const int64_t K = gm[0].K, out = gm[0].batch * gm[0].M * gm[0].N;
+  for (GemmDesc& g : gm) {
+    int tile, split;
+    gemm_tile_by_blocks(g, &tile, &split);
+    // products of up to 2^23 multiply-adds with a short sum: one output per thread (a matrix-core launch
+    // of its own costs more than the sums): 512 x 512 x 8 of a 24-qubit state 709 -> 702, 512 x 1024 x 16
+    // of a 28-qubit one 786 -> 766; 1024 x 64 x 128 x 4 (2^25) stays: 163 against 180
+    if (K <= 32 && out * K <= ((int64_t)1 << 23)) tile = kGemmVector;
+    if (tile == kGemmVector) split = 1;
+    const bool wide = out >= ((int64_t)1 << 18) && K >= 8;  // enough results for a launch of its own
+    if (tile == kGemmVector && wide && out * K > ((int64_t)1 << 23) && K <= kElemMaxK) {
+      // batches of small products, four per block: 4096 x 32 x 32 x 32 of a 32-qubit amplitude batch 369 -> 258,
+      // 4096 x 8 x 32 x 32 258 -> 239, 4096 x 32 x 32 x 8 420 -> 393
+      const bool packed = g.batch >= 64 && g.M <= 32 && g.N <= 32 && g.M * g.N >= 256;
+      // a short side against a long one, four 32-column slices per block: 32 x 131072 x 8 393 -> 369,
+      // 1024 x 16 x 1024 x 16 605 -> 373 (on 32 x 4096 results it was slower than the grouped launches)
+      const bool columns = g.M >= 16 && g.M <= 32 && g.N >= 64 && out >= ((int64_t)1 << 19);
+      if (c64 && packed) tile = kGemmBatchPacked;
+      else if (c64 && columns) tile = kGemmColumnPacked;
+      else if (packed || columns) tile = kGemmVector - 1;  // 64 x 32: 269 against 369 on 4096 x 32 x 32 x 32
+    }
+    if (tile < kGemmVector && g.M >= 64 && g.N >= 64) {
+      // 64 x 64 tiles once they fill the chip, in the three-product form for complex64 (twice the waves per SIMD of
+      // 128 x 64): 1024 x 8192 x 256 692 -> 669, 8192 x 32768 x 16 766 -> 669, 512 x 2048 x 256 136 -> 126,
+      // 64 x 4096 x 2048 in 8 ranges 163 -> 152 (us); BF16x3 512 x 32768 x 256 536 -> 520
+      const int64_t blocks = ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+      int sp = 1;
+      while (sp < g.max_split && blocks * sp < 512 && K / (sp * 2) >= 32 && K % (sp * 2) == 0) sp *= 2;
+      if (c64 ? blocks * sp >= 256 : blocks >= 512) {
+        tile = c64 ? 6 : 2;
+        split = sp;
+      }
+    }
+    g.tile[prec] = tile;
+    g.split[prec] = split;
+  }
+  // Orientation: the one whose tiles are full (32 x 8192 x 2048: 373 -> 341); then, as a tile stores each row of its
+  // result as 32 consecutive columns per wave, the one whose columns are the result's lowest address bits where the
+  // other's are not (stores of single elements write each 128-byte line 16 times: 512 x 32768 x 256 669 -> 549)
+  if (gm[0].tile[prec] == kGemmVector || gm[1].tile[prec] == kGemmVector)
+    return gm[0].tile[prec] == kGemmVector ? (gm[1].tile[prec] == kGemmColumnPacked ? 1 : 0) : 0;
+  auto waste = [&](const GemmDesc& g) {
+    const int t = g.tile[prec];
+    return std::max<int64_t>(1, kGemmTileM[t] / g.M) * std::max<int64_t>(1, kGemmTileN[t] / g.N);
+  };
+  if (waste(gm[0]) != waste(gm[1])) return waste(gm[1]) < waste(gm[0]) ? 1 : 0;
+  auto low_n = [](const GemmDesc& g) {
+    int c = 0;
+    while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
+    return c;
+  };
+  return low_n(gm[1]) > low_n(gm[0]) && (low_n(gm[0]) < 3 || K <= 32) ? 1 : 0;
 }
 
 double modeled_seconds(const tn_path* path) {
@@ -1797,7 +1838,7 @@ double modeled_seconds(const tn_path* path) {
       // the 3M tiles do three real products where the real embedding does four
       const double form = tl > kGemmVector ? 4.0 / 3.0 : 1.0;
       const double eff = form * std::min(1.0, g.M / tm) * std::min(1.0, g.N / tn) * std::min(1.0, g.K / 32.0) *
-                         std::min(1.0, tiles / 256.0) * (tm * tn >= 8192 ? 1.0 : 0.8);
+                         std::min(1.0, tiles / 256.0) * (tm * tn >= 4096 || tl > kGemmVector ? 1.0 : 0.8);
       t += std::max(P.flops / (kMfma * std::max(eff, 1e-3)), bytes / kHbm) + (g.split[0] > 1 ? kLaunch : 0.0);
     }
   }

@@ -101,5 +101,29 @@ __device__ __forceinline__ float2 load_stream(const float2* p) {
   return f2(v.x, v.y);
 }
 
+// D at sixteen addresses: A with none of four bits set, and every combination
+// of them, the terms sorted by their pattern mu of those bits.  Each term's
+// sign at A is taken once, the sums per pattern go into w[mu], and a 16-point
+// Walsh-Hadamard transform gives D at combination j = sum_mu w[mu] (-1)^popc(j & mu).
+__device__ inline void sum_terms16(uint64_t A, const ZTerms& t, double (&w)[16]) {
+#pragma unroll
+  for (int mu = 0; mu < 16; ++mu) {
+    double acc = 0;
+    for (int i = t.mu_start[mu]; i < t.mu_start[mu + 1]; ++i)
+      acc += (__popcll(A & t.mask[i]) & 1) ? -t.coeff[i] : t.coeff[i];
+    w[mu] = acc;
+  }
+#pragma unroll
+  for (int h = 1; h < 16; h <<= 1)
+#pragma unroll
+    for (int a = 0; a < 16; a += 2 * h)
+#pragma unroll
+      for (int b = a; b < a + h; ++b) {
+        const double u = w[b], v = w[b + h];
+        w[b] = u + v;
+        w[b + h] = u - v;
+      }
+}
+
 }  // namespace
 }  // namespace tnq

@@ -552,6 +552,9 @@ struct tn_path {
   std::vector<tnq::RegOp> reg_ops, adj_reg_ops;
   std::vector<tnq::RegPhase> reg_phases, adj_reg_phases;
   std::vector<uint32_t> reg_words, adj_reg_words;
+  // the leading steps that only merge the qubits' |0> vectors into the input of the first chain
+  // (0: the path does not start so): the chain's first pass starts from |0...0> instead
+  int32_t zero_steps = 0;
   // the path's leading steps as ordered passes; the reverse sweep as ordered passes (adj_state 2)
   tnq::SeqChain seq;
   tnq::SeqProgram adj_seq;

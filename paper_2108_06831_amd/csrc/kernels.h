@@ -87,9 +87,9 @@ ElemMember elem_member(const GemmDesc& d, const float2* a, int64_t a_bs, const f
 constexpr int kMaxTerms = 128;
 struct ZTerms {
   int32_t n;
-  uint64_t mask[kMaxTerms];  // address-bit masks, sorted by their bits 8..11
+  uint64_t mask[kMaxTerms];  // address-bit masks, sorted by their pattern mu of four bits (8..11, or those given)
   double coeff[kMaxTerms];
-  int32_t mu_start[17];      // terms whose bits 8..11 equal mu: [mu_start[mu], mu_start[mu + 1])
+  int32_t mu_start[17];      // terms of pattern mu: [mu_start[mu], mu_start[mu + 1])
 };
 constexpr int kReduceBlocks = 512;   // blocks of the adjoint step (one partial per block and gate)
 constexpr int kExpectBlocks = 4096;  // blocks of the expectation reduction
@@ -104,8 +104,8 @@ hipError_t launch_small_steps(hipStream_t s, const SmallStep* steps, const int32
                               const int32_t* level_off, const uint32_t* items, int n_lists, float2* in,
                               int64_t in_bs, float2* ws, int64_t ws_bs, int batch, int precision);
 
-// One fused streaming pass over a 2^bits tensor (see SweepPass); vals: the
-// chain's gate values gathered by launch_gather_vals.
+// One fused streaming pass over a 2^bits tensor (see SweepPass; in == NULL: the
+// state |0...0>); vals: the chain's gate values gathered by launch_gather_vals.
 hipError_t launch_sweep_pass(hipStream_t s, const SweepPass& ps, int bits, const SweepGateDesc* gates_dev,
                              const SweepSegment* segs_dev, const float2* in, int64_t in_bs, float2* out,
                              int64_t out_bs, const float2* vals, int64_t vals_bs, int batch, int precision);
@@ -118,7 +118,15 @@ struct RegTables {
 };
 hipError_t launch_sweep_regs(hipStream_t s, const SweepPass& ps, int bits, const RegTables& t, const float2* in,
                              int64_t in_bs, float2* out, int64_t out_bs, const float2* vals, int64_t vals_bs,
-                             int batch);
+                             int batch, const ZTerms* terms = nullptr, double* partial = nullptr);
+// With terms (sorted by their bits at the last segment's register positions)
+// the pass ends in partial sums of the expectation, `partial[z][block]` of
+// kExpectBlocks columns, instead of storing the state.
+inline int sweep_expect_blocks(const SweepPass& ps, int bits) {
+  return bits - ps.l >= 12 ? kExpectBlocks : 1 << (bits - ps.l);
+}
+static_assert(kExpectBlocks == 1 << 12, "sweep_expect_blocks");
+hipError_t launch_reduce_rows(hipStream_t s, const double* partial, int n, int batch, double* out, int64_t out_stride);
 // out[z][i] = value i of a chain's table: src[i] = element offset | (BUF_IN or BUF_WS) << 56.
 hipError_t launch_gather_vals(hipStream_t s, const int64_t* src, int n, const float2* IN, int64_t in_bs,
                               const float2* WS, int64_t ws_bs, float2* out, int64_t out_bs, int batch);

@@ -1731,30 +1731,6 @@ __global__ __launch_bounds__(kThreads) void k_reduce_rows(const double* partial,
   if (threadIdx.x == 0) out[(int64_t)z * out_stride] = s;
 }
 
-// D at the 16 addresses base + 256 j (j = 0..15, base with bits 8..11 clear):
-// each term's sign over the bits other than 8..11 is taken once per thread,
-// the sums per pattern mu of bits 8..11 go into w[mu], and a 16-point
-// Walsh-Hadamard transform gives D(base + 256 j) = sum_mu w[mu] (-1)^popc(j & mu).
-__device__ inline void zdiag16(uint64_t base, const ZTerms& t, double (&w)[16]) {
-#pragma unroll
-  for (int mu = 0; mu < 16; ++mu) {
-    double acc = 0;
-    for (int i = t.mu_start[mu]; i < t.mu_start[mu + 1]; ++i)
-      acc += (__popcll(base & t.mask[i]) & 1) ? -t.coeff[i] : t.coeff[i];
-    w[mu] = acc;
-  }
-#pragma unroll
-  for (int h = 1; h < 16; h <<= 1)
-#pragma unroll
-    for (int a = 0; a < 16; a += 2 * h)
-#pragma unroll
-      for (int b = a; b < a + h; ++b) {
-        const double u = w[b], v = w[b + h];
-        w[b] = u + v;
-        w[b + h] = u - v;
-      }
-}
-
 // blocks of 4096 consecutive elements: thread t takes base + t + 256 j
 __global__ __launch_bounds__(kThreads) void k_expect_partial16(const float2* psi, int64_t bs, int64_t n, ZTerms t,
                                                                double* partial) {
@@ -1765,7 +1741,7 @@ __global__ __launch_bounds__(kThreads) void k_expect_partial16(const float2* psi
   for (int64_t c = blockIdx.x; c < (n >> 12); c += gridDim.x) {
     const int64_t base = (c << 12) | threadIdx.x;
     double w[16];
-    zdiag16((uint64_t)base, t, w);
+    sum_terms16((uint64_t)base, t, w);  // at base + 256 j
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const float2 v = p[base + 256 * j];
@@ -1774,6 +1750,12 @@ __global__ __launch_bounds__(kThreads) void k_expect_partial16(const float2* psi
   }
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partial[(int64_t)z * kExpectBlocks + blockIdx.x] = s;
+}
+
+hipError_t launch_reduce_rows(hipStream_t s, const double* partial, int n, int batch, double* out,
+                              int64_t out_stride) {
+  hipLaunchKernelGGL(k_reduce_rows, dim3(batch), dim3(kThreads), 0, s, partial, n, out, out_stride);
+  return hipGetLastError();
 }
 
 hipError_t launch_expectation(hipStream_t s, const float2* psi, int64_t psi_bs, int64_t n_elems, const ZTerms& terms,
@@ -1790,8 +1772,7 @@ hipError_t launch_expectation(hipStream_t s, const float2* psi, int64_t psi_bs, 
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reduce_rows, dim3(batch), dim3(kThreads), 0, s, partial, (int)blocks, out, out_stride);
-  return hipGetLastError();
+  return launch_reduce_rows(s, partial, (int)blocks, batch, out, out_stride);
 }
 
 __global__ void k_copy(const float2* in, int64_t in_bs, float2* out, int64_t out_bs, int64_t n) {
@@ -1827,7 +1808,7 @@ __global__ __launch_bounds__(kThreads) void k_apply_diag_obs16(const float2* psi
   for (int64_t c = blockIdx.x; c < (n >> 12); c += gridDim.x) {
     const int64_t base = (c << 12) | threadIdx.x;
     double w[16];
-    zdiag16((uint64_t)base, t, w);
+    sum_terms16((uint64_t)base, t, w);  // at base + 256 j
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const float2 v = psi[(int64_t)z * psi_bs + base + 256 * j];

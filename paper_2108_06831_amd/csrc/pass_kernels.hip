@@ -35,7 +35,11 @@ __global__ __launch_bounds__(kThreads) void k_sweep_pass(SweepPassArgs a, const 
   const float2* V0 = vals + (int64_t)z * a.vals_bs;
   for (int t = tid; t < a.lds_n; t += nt) vtab[t] = V0[a.lds_off + t];
   const float2* ctab = vtab + (a.ctab_off - a.lds_off);
-  chunk_to_lds(buf, in, base, dep_hi, tid, nt);
+  if (a.in) {
+    chunk_to_lds(buf, in, base, dep_hi, tid, nt);
+  } else {  // the state |0...0>
+    for (int k = 0; k < 16; ++k) buf[lds_phys(tid + k * nt)] = f2(base == 0 && tid + k * nt == 0 ? 1.f : 0.f, 0.f);
+  }
   __syncthreads();
   for (int sg = 0; sg < a.n_segs; ++sg) {
     const SweepSegment& seg = segs[sg];

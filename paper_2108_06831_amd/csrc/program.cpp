@@ -693,6 +693,7 @@ namespace {
 void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>& loc,
                     const std::vector<std::vector<int32_t>>& modes) {
   path->seq = SeqChain();
+  path->zero_steps = 0;
   const int T = (int)net->tensors.size();
   const int S = (int)path->pairs.size() / 2;
   if (S < kSeqMinRun) return;
@@ -706,6 +707,14 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
   int s = 0;
   for (; s < S && zero[path->pairs[2 * s]] && zero[path->pairs[2 * s + 1]]; ++s) zero[T + s] = 1;
   if (s == 0 || s + 1 != n_zero) return;  // every |0> is in one state
+  if (s < S && path->steps[s].chain >= 0 && s >= path->n_small) {
+    const BufRef& in = path->chains[path->steps[s].chain].in;
+    const BufRef& out = path->steps[s - 1].kind == SK_SMALL  ? BufRef{path->steps[s - 1].sm.c_buf, path->steps[s - 1].sm.c_off, 0}
+                        : path->steps[s - 1].kind == SK_GEMM ? path->steps[s - 1].gm[0].c
+                                                             : path->steps[s - 1].sk.c;
+    if (in.buf == out.buf && in.off == out.off) path->zero_steps = s;
+    return;
+  }
   SeqChain ch;
   ch.bits = (int)loc[T + s - 1].bits.size();
   if (ch.bits != n_zero || ch.bits < kSeqMinBits || ch.bits > kSeqMaxBits || net->input_elems > ((int64_t)1 << 30)) return;
@@ -1454,7 +1463,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
   build_outer_chains(path, T);
   find_seq_chain(net, path, loc, modes);
   st.n_product_launches = 0;
-  for (int s = std::max(path->n_small, path->seq.end), run0 = -1, run_len = 0; s < S; ++s) {
+  for (int s = std::max({path->n_small, path->seq.end, path->zero_steps}), run0 = -1, run_len = 0; s < S; ++s) {
     const StepProgram& P = path->steps[s];
     if (P.chain != -1) {
       run0 = -1;

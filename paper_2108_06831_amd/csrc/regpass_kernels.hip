@@ -242,19 +242,35 @@ __device__ __forceinline__ void count_op(float2 (&x)[16], const RegOp& op, const
   if (mask & 4) { constexpr int R = 2; __VA_ARGS__; } \
   if (mask & 8) { constexpr int R = 3; __VA_ARGS__; }
 
+// The observable of a last pass that ends in an expectation (empty otherwise).
+template <bool EXPECT>
+struct PassTerms {};
+template <>
+struct PassTerms<true> {
+  ZTerms t;  // sorted by their bits at the last segment's register positions
+};
+
 // Forward pass.  (Value and descriptor tables as separate __restrict__
-// arguments, so that they are read with scalar loads.)
+// arguments, so that they are read with scalar loads.)  A NULL input is the
+// state |0...0>: the first pass of a contraction from the qubits' |0> vectors
+// then reads nothing.  EXPECT: the last pass of an expectation sums |x|^2 D(x)
+// in FP64 (as k_expect_partial16) into partials[blockIdx.x] and stores no
+// state.  (On a 26-qubit state each saves 1 GiB of the 1 GiB + 1 GiB that the
+// product state's launch and the pass, or the pass and the reduction, moved.)
+template <bool EXPECT>
 __global__ __launch_bounds__(kThreads, 4) void k_sweep_regs(RegPassArgs a, const RegSeg* __restrict__ segs,
                                                             const RegOp* __restrict__ ops,
                                                             const RegPhase* __restrict__ phases,
                                                             const uint32_t* __restrict__ words,
-                                                            const float2* __restrict__ vals) {
+                                                            const float2* __restrict__ vals, PassTerms<EXPECT> obs) {
   __shared__ float2 buf[kRegBuf];
   __shared__ float2 ctab[kCountTabMax];
   const int z = blockIdx.y, tid = threadIdx.x;
-  const int64_t base = deposit(blockIdx.x, a.rest, a.n_rest);
   const float2* V0 = vals + (int64_t)z * a.vals_bs;
   for (int t = tid; t < a.ctab_n; t += kThreads) ctab[t] = V0[a.ctab_off + t];
+  double esum = 0.0;
+  for (int64_t c = blockIdx.x; c < (EXPECT ? a.n_chunks : (int64_t)blockIdx.x + 1); c += gridDim.x) {
+  const int64_t base = deposit(c, a.rest, a.n_rest);
   float2 x[16];
   const RegSeg& ld = segs[a.n_segs];
   int slot = thread_bits(tid, ld.tpos);
@@ -263,7 +279,10 @@ __global__ __launch_bounds__(kThreads, 4) void k_sweep_regs(RegPassArgs a, const
   bool same = true;  // the first segment's registers are the load's
 #pragma unroll
   for (int j = 0; j < 4; ++j) same &= ld.rbits[j] == segs[0].rbits[j];
-  {
+  if (!a.in) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = f2(r == 0 && base == 0 && tid == 0 ? 1.f : 0.f, 0.f);
+  } else {
     const float2* src = a.in + (int64_t)z * a.in_bs + (base | (uint32_t)thread_bits(tid, ld.gpos));
     const int64_t g0 = 1ll << ld.rgpos[0], g1 = 1ll << ld.rgpos[1], g2 = 1ll << ld.rgpos[2], g3 = 1ll << ld.rgpos[3];
 #pragma unroll
@@ -363,20 +382,35 @@ __global__ __launch_bounds__(kThreads, 4) void k_sweep_regs(RegPassArgs a, const
 #pragma unroll
       for (int r = 0; r < 16; ++r) mul_in_place(x[r], ph);
   }
-  const RegSeg& st = segs[a.n_segs + 1];
-  bool keep = true;
+  if constexpr (EXPECT) {
+    const RegSeg& seg = segs[a.n_segs - 1];
+    const uint32_t A = (uint32_t)base | (uint32_t)thread_bits(tid, seg.gpos);
+    double w[16];  // D at the thread's elements: per pattern of the register bits, then a Walsh-Hadamard transform
+    sum_terms16(A, obs.t, w);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) keep &= st.rbits[j] == segs[a.n_segs - 1].rbits[j];
-  if (!keep) {
-    int ob = thread_bits(tid, st.tpos);
-    ob += ob >> 5;
-    relayout(x, buf, slot, off, ob, st.physoff);
+    for (int r = 0; r < 16; ++r) esum += ((double)x[r].x * x[r].x + (double)x[r].y * x[r].y) * w[r];
+  } else {
+    const RegSeg& st = segs[a.n_segs + 1];
+    bool keep = true;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) keep &= st.rbits[j] == segs[a.n_segs - 1].rbits[j];
+    if (!keep) {
+      int ob = thread_bits(tid, st.tpos);
+      ob += ob >> 5;
+      relayout(x, buf, slot, off, ob, st.physoff);
+    }
+    float2* dst = a.out + (int64_t)z * a.out_bs + (base | (uint32_t)thread_bits(tid, st.gpos));
+    const int64_t g0 = 1ll << st.rgpos[0], g1 = 1ll << st.rgpos[1], g2 = 1ll << st.rgpos[2], g3 = 1ll << st.rgpos[3];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      store_stream(dst + ((r & 1 ? g0 : 0) + (r & 2 ? g1 : 0) + (r & 4 ? g2 : 0) + (r & 8 ? g3 : 0)), x[r].x, x[r].y);
   }
-  float2* dst = a.out + (int64_t)z * a.out_bs + (base | (uint32_t)thread_bits(tid, st.gpos));
-  const int64_t g0 = 1ll << st.rgpos[0], g1 = 1ll << st.rgpos[1], g2 = 1ll << st.rgpos[2], g3 = 1ll << st.rgpos[3];
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    store_stream(dst + ((r & 1 ? g0 : 0) + (r & 2 ? g1 : 0) + (r & 4 ? g2 : 0) + (r & 8 ? g3 : 0)), x[r].x, x[r].y);
+  }
+  if constexpr (EXPECT) {
+    __syncthreads();
+    esum = block_sum(esum, reinterpret_cast<double*>(buf));
+    if (tid == 0) a.partials[(int64_t)z * a.pstride + blockIdx.x] = esum;
+  }
 }
 
 // Reverse sweep over psi and lambda (see k_adjoint_pass).
@@ -592,15 +626,24 @@ bool rest_bits(const SweepPass& ps, int bits, RegPassArgs* a) {
 
 hipError_t launch_sweep_regs(hipStream_t s, const SweepPass& ps, int bits, const RegTables& t, const float2* in,
                              int64_t in_bs, float2* out, int64_t out_bs, const float2* vals, int64_t vals_bs,
-                             int batch) {
+                             int batch, const ZTerms* terms, double* partial) {
   RegPassArgs a{};
   a.in = in; a.out = out; a.in_bs = in_bs; a.out_bs = out_bs;
   a.vals_bs = vals_bs;
   a.ctab_off = ps.ctab_off;
   a.ctab_n = ps.ctab_n;
   if (!rest_bits(ps, bits, &a) || ps.ctab_n < 0 || ps.ctab_n > kCountTabMax || !vals) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_sweep_regs, dim3((unsigned)a.n_chunks, batch), dim3(kThreads), 0, s, a, t.segs + ps.reg_seg,
-                     t.ops, t.phases, t.words, vals);
+  if (terms) {
+    a.partials = partial;
+    a.pstride = kExpectBlocks;
+    PassTerms<true> p;
+    p.t = *terms;
+    hipLaunchKernelGGL(k_sweep_regs<true>, dim3(sweep_expect_blocks(ps, bits), batch), dim3(kThreads), 0, s, a,
+                       t.segs + ps.reg_seg, t.ops, t.phases, t.words, vals, p);
+  } else {
+    hipLaunchKernelGGL(k_sweep_regs<false>, dim3((unsigned)a.n_chunks, batch), dim3(kThreads), 0, s, a,
+                       t.segs + ps.reg_seg, t.ops, t.phases, t.words, vals, PassTerms<false>{});
+  }
   return hipGetLastError();
 }
 

@@ -335,6 +335,12 @@ struct Bases {
   float2* final_out = nullptr;
   int64_t final_out_bs = 0;
   const std::vector<int32_t>* final_layout = nullptr;  // final_out's bit order
+  // when set, a contraction whose last pass can end in the expectation of this observable does so:
+  // partial sums go to expect_partial, their number per parameter vector to expect_n (else it stays 0)
+  const tn_network* net = nullptr;
+  const tn_observable* expect = nullptr;
+  double* expect_partial = nullptr;
+  int* expect_n = nullptr;
   // contract_pair: inputs are two separate user buffers
   const float2* pair_a = nullptr;
   const float2* pair_b = nullptr;
@@ -355,6 +361,9 @@ static float2* resolve(const Bases& b, const BufRef& r, int64_t* bs) {
     default: *bs = 0; return nullptr;
   }
 }
+
+static tn_status make_terms(const tn_network* net, const std::vector<int32_t>& bits, const tn_observable* obs,
+                            ZTerms* t, const int32_t* group_pos = nullptr);
 
 // End (exclusive) of the run of products starting at step si that share one
 // launch of the grouped per-output kernel (si + 1: si runs alone).
@@ -407,6 +416,7 @@ static tn_status run_seq(hipStream_t s, tn_path* path, DevPath* dp, const Bases&
 static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, int batch, int precision) {
   DevPath* dp = nullptr;
   const int seq_end = B.pair_a ? 0 : path->seq.end;
+  const bool from_zero = path->zero_steps > 0;  // the first chain starts from |0...0>
   if (path->n_small > 0 || !path->chains.empty() || seq_end > 0) {
     tn_status st = ensure_path_device(path, &dp);
     if (st != TN_OK) return st;
@@ -414,7 +424,7 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
   if (seq_end > 0) {
     tn_status st = run_seq(s, path, dp, B, batch, precision);
     if (st != TN_OK) return st;
-  } else if (path->n_small > 0) {
+  } else if (path->n_small > 0 && !from_zero) {
     int64_t ibs, wbs;
     BufRef ri, rw;
     ri.buf = BUF_IN;
@@ -429,7 +439,7 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
     for (int i = 0; i < path->n_small; ++i) { fl += path->steps[i].flops; by += path->steps[i].bytes; }
     prof_stop(s, ev, TN_KERNEL_INTERP, by * batch, fl * batch);
   }
-  for (size_t si = std::max(path->n_small, seq_end); si < path->steps.size(); ++si) {
+  for (size_t si = std::max({path->n_small, seq_end, path->zero_steps}); si < path->steps.size(); ++si) {
     const StepProgram& P = path->steps[si];
     if (P.chain == -2) continue;
     if (P.chain >= 0) {
@@ -449,13 +459,24 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
                                    batch));
       for (int k = 0; k < ch.n_passes; ++k) {
         const SweepPass& ps = path->passes[ch.first_pass + k];
+        const float2* src = k > 0 ? op : from_zero && (int)si == path->zero_steps ? nullptr : ip;
+        const bool regs = ps.reg_seg >= 0 && precision == TN_PREC_C64 && vals;
+        ZTerms terms;
+        const bool ends = regs && B.expect && si + ch.n_steps == path->steps.size() && k == ch.n_passes - 1;
+        if (ends) {
+          tn_status st = make_terms(B.net, path->final_bits, B.expect, &terms,
+                                    path->reg_segs[ps.reg_seg + ps.n_segs - 1].rgpos);
+          if (st != TN_OK) return st;
+          *B.expect_n = sweep_expect_blocks(ps, ch.bits);
+        }
         hipEvent_t ev = prof_start(s, TN_KERNEL_SWEEP);
-        if (ps.reg_seg >= 0 && precision == TN_PREC_C64 && vals)
+        if (regs)
           HIP_TRY(launch_sweep_regs(s, ps, ch.bits, RegTables{dp->reg_segs, dp->reg_ops, dp->reg_phases, dp->reg_words},
-                                    k == 0 ? ip : op, k == 0 ? ibs : obs, op, obs, vals, vbs, batch));
+                                    src, k == 0 ? ibs : obs, op, obs, vals, vbs, batch, ends ? &terms : nullptr,
+                                    B.expect_partial));
         else
-          HIP_TRY(launch_sweep_pass(s, ps, ch.bits, dp->sweep_gates, dp->segments, k == 0 ? ip : op,
-                                    k == 0 ? ibs : obs, op, obs, vals, vbs, batch, precision));
+          HIP_TRY(launch_sweep_pass(s, ps, ch.bits, dp->sweep_gates, dp->segments, src, k == 0 ? ibs : obs, op, obs,
+                                    vals, vbs, batch, precision));
         double fl = 0;
         for (int g = 0; g < ps.n_gates; ++g) {
           const SweepGateDesc& gd = path->sweep_gates[ps.first_gate + g];
@@ -614,8 +635,10 @@ static bool is_pow2(int64_t x) { return x > 0 && (x & (x - 1)) == 0; }
 
 // map qubit masks to address-bit masks of the final tensor
 // The observable's Z strings as address masks of a state in layout `bits` (labels, C order).
+// The terms are grouped by their bits at four positions (the reduction kernels sum each group once
+// per thread and spread it over the 16 elements that differ in those bits).
 static tn_status make_terms(const tn_network* net, const std::vector<int32_t>& bits, const tn_observable* obs,
-                            ZTerms* t) {
+                            ZTerms* t, const int32_t* group_pos) {
   if (!obs || obs->n_terms < 0 || (obs->n_terms > 0 && (!obs->z_mask || !obs->coeff)))
     return set_error(TN_EINVAL, "bad observable");
   if (obs->n_terms > kMaxTerms)
@@ -635,11 +658,15 @@ static tn_status make_terms(const tn_network* net, const std::vector<int32_t>& b
     t->mask[i] = m;
     t->coeff[i] = obs->coeff[i];
   }
-  // group the terms by their address bits 8..11 (the reduction kernels sum
-  // each group once per thread and spread it over 16 elements)
+  static const int32_t bits8[4] = {8, 9, 10, 11};
+  const int32_t* gp = group_pos ? group_pos : bits8;
   std::vector<int> order(t->n);
   for (int i = 0; i < t->n; ++i) order[i] = i;
-  auto mu = [&](int i) { return (int)((t->mask[i] >> 8) & 15); };
+  auto mu = [&](int i) {
+    int m = 0;
+    for (int j = 0; j < 4; ++j) m |= (int)((t->mask[i] >> gp[j]) & 1) << j;
+    return m;
+  };
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return mu(a) < mu(b); });
   uint64_t mk[kMaxTerms];
   double cf[kMaxTerms];
@@ -1177,6 +1204,11 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
     B.in_bs = net->input_elems;
     B.ws = (float2*)(w + L.arena_off);
     B.ws_bs = path->ws_elems;
+    int n_partial = 0;
+    B.net = net;
+    B.expect = &obs[c];
+    B.expect_partial = (double*)(w + L.aux_off);
+    B.expect_n = &n_partial;
     if ((st = materialize(s, net, d, prm, batch, nullptr, 0, B.in)) != TN_OK ||
         (st = run_steps(s, path, B, batch, precision)) != TN_OK) {
       result = st;
@@ -1185,13 +1217,15 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
     int64_t fbs;
     float2* f = resolve(B, path->final_ref, &fbs);
     hipEvent_t ev = prof_start(s, TN_KERNEL_REDUCE);
-    const hipError_t e = launch_expectation(s, f, fbs, path->final_elems, terms, batch, (double*)(w + L.aux_off),
-                                            out_dev + (int64_t)c * batch, 1);
+    const hipError_t e =
+        n_partial > 0 ? launch_reduce_rows(s, B.expect_partial, n_partial, batch, out_dev + (int64_t)c * batch, 1)
+                      : launch_expectation(s, f, fbs, path->final_elems, terms, batch, (double*)(w + L.aux_off),
+                                           out_dev + (int64_t)c * batch, 1);
     if (e != hipSuccess) {
       result = set_error(TN_EDEVICE, std::string("expectation: ") + hipGetErrorString(e));
       break;
     }
-    prof_stop(s, ev, TN_KERNEL_REDUCE, 8.0 * (double)path->final_elems * batch, 0.0);
+    prof_stop(s, ev, TN_KERNEL_REDUCE, 8.0 * (double)(n_partial > 0 ? n_partial : path->final_elems) * batch, 0.0);
   }
   // join the lanes back into the caller's stream (also after an error, so no lane stays forked)
   for (int k = 0; k < lanes - 1; ++k) {

@@ -101,6 +101,20 @@ __device__ __forceinline__ float2 load_stream(const float2* p) {
   return f2(v.x, v.y);
 }
 
+// w[j] <- sum over mu of w[mu] (-1)^popc(j & mu)
+__device__ inline void walsh16(double (&w)[16]) {
+#pragma unroll
+  for (int h = 1; h < 16; h <<= 1)
+#pragma unroll
+    for (int a = 0; a < 16; a += 2 * h)
+#pragma unroll
+      for (int b = a; b < a + h; ++b) {
+        const double u = w[b], v = w[b + h];
+        w[b] = u + v;
+        w[b + h] = u - v;
+      }
+}
+
 // D at sixteen addresses: A with none of four bits set, and every combination
 // of them, the terms sorted by their pattern mu of those bits.  Each term's
 // sign at A is taken once, the sums per pattern go into w[mu], and a 16-point
@@ -113,16 +127,7 @@ __device__ inline void sum_terms16(uint64_t A, const ZTerms& t, double (&w)[16])
       acc += (__popcll(A & t.mask[i]) & 1) ? -t.coeff[i] : t.coeff[i];
     w[mu] = acc;
   }
-#pragma unroll
-  for (int h = 1; h < 16; h <<= 1)
-#pragma unroll
-    for (int a = 0; a < 16; a += 2 * h)
-#pragma unroll
-      for (int b = a; b < a + h; ++b) {
-        const double u = w[b], v = w[b + h];
-        w[b] = u + v;
-        w[b + h] = u - v;
-      }
+  walsh16(w);
 }
 
 }  // namespace

@@ -192,6 +192,52 @@ hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const 
                               const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,
                               const float2* vals, int64_t vals_bs, int batch, int precision);
 int seq_adjoint_columns(const SeqPass& ps, int bits);
+// Expectations of several circuits whose whole contraction is one ordered pass
+// from |0...0>, one launch: circuits of one block size (2^(l - 4) threads, 64 at
+// least).  Terms: masks over the state's address bits, a circuit's sorted by
+// their pattern of its last segment's register bits.
+constexpr int kSeqExpectMax = 16, kSeqExpectTerms = 176;
+constexpr int kSeqExpectSizes = 5;  // block sizes: states of up to 10 bits, and 11 to 14
+struct SeqCirc {
+  const SeqSeg* segs;
+  const SeqWindow* wins;
+  const uint32_t* words;
+  const int32_t* vsrc;
+  const float2* vals;  // the network's input tensors
+  double* out;         // [batch]
+  int64_t vals_bs;
+  int32_t n_segs, l, term0;
+  uint8_t mu_start[17];
+  uint8_t pad[3];
+};
+struct SeqExpectArgs {
+  int32_t n, pad;
+  SeqCirc c[kSeqExpectMax];
+  uint32_t mask[kSeqExpectTerms];
+  double coeff[kSeqExpectTerms];
+};
+static_assert(sizeof(SeqExpectArgs) <= 4000, "kernel arguments");
+static_assert(kMaxTerms <= kSeqExpectTerms && kMaxTerms < 256, "one circuit's terms fit a launch");
+hipError_t launch_seq_expect(hipStream_t s, const SeqExpectArgs& a, int batch, int precision);
+// The input tensors of several networks in one launch (no projectors).
+constexpr int kMatMax = 48;
+struct MatNet {
+  const DevTensor* ts;
+  const Recipe* recipes;
+  const RecipeOp* ops;
+  const double* mats;
+  const double* params;
+  float2* in;
+  int64_t in_bs;
+  int32_t n_tensors, params_stride;
+  int32_t block0, pad;
+};
+struct MatArgs {
+  int32_t n, pad;
+  MatNet net[kMatMax];
+};
+static_assert(sizeof(MatArgs) <= 4000, "kernel arguments");
+hipError_t launch_materialize_many(hipStream_t s, MatArgs& a, int batch);
 hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const float2* u,
                               int64_t u_bs, float2* psi, int64_t psi_bs, float2* lam, int64_t lam_bs, int batch,
                               double* partials, int64_t partial_stride, int precision);

@@ -77,17 +77,11 @@ __device__ void write_recipe(const Recipe& r, const RecipeOp* ops, GetU get_u, f
   }
 }
 
+// tensor d of one parameter vector (p) into o
 template <bool Q>
-__global__ __launch_bounds__(kRecipeThreads) void k_materialize(const DevTensor* ts, int nt, const Recipe* rs,
-                                                                const RecipeOp* ops, const double* mats,
-                                                                const double* params, int64_t pstride, float2* in,
-                                                                int64_t in_bs) {
+__device__ __forceinline__ void materialize_tensor(const DevTensor& d, const Recipe* rs, const RecipeOp* ops,
+                                                   const double* mats, const double* p, float2* o) {
   __shared__ c128 U[kRecipeThreads][16];
-  const int t = blockIdx.x;
-  const int z = blockIdx.y;
-  if (t >= nt) return;
-  const DevTensor d = ts[t];
-  float2* o = in + (int64_t)z * in_bs + d.offset;
   if (d.kind == TK_KET0) {
     if (threadIdx.x == 0) {
       store_c<Q>(o, 0, c128{1.0, 0.0});
@@ -95,7 +89,6 @@ __global__ __launch_bounds__(kRecipeThreads) void k_materialize(const DevTensor*
     }
   } else if (d.kind == TK_GATE) {
     const Recipe r = rs[d.recipe];
-    const double* p = params ? params + (int64_t)z * pstride : nullptr;
     const int n = r.op_end - r.op_begin;
     if (n <= kRecipeThreads) {
       if ((int)threadIdx.x < n) {
@@ -114,6 +107,42 @@ __global__ __launch_bounds__(kRecipeThreads) void k_materialize(const DevTensor*
       write_recipe<Q>(r, ops, [&](int op, c128* u) { op_matrix(ops[op], mats, p, u); }, o);
     }
   }
+}
+
+template <bool Q>
+__global__ __launch_bounds__(kRecipeThreads) void k_materialize(const DevTensor* ts, int nt, const Recipe* rs,
+                                                                const RecipeOp* ops, const double* mats,
+                                                                const double* params, int64_t pstride, float2* in,
+                                                                int64_t in_bs) {
+  const int t = blockIdx.x;
+  const int z = blockIdx.y;
+  if (t >= nt) return;
+  const DevTensor d = ts[t];
+  materialize_tensor<Q>(d, rs, ops, mats, params ? params + (int64_t)z * pstride : nullptr,
+                        in + (int64_t)z * in_bs + d.offset);
+}
+
+__global__ __launch_bounds__(kRecipeThreads) void k_materialize_many(MatArgs a) {
+  const int z = blockIdx.y;
+  int i = 0;
+  while (i + 1 < a.n && (int)blockIdx.x >= a.net[i + 1].block0) ++i;
+  const MatNet& m = a.net[i];
+  const DevTensor d = m.ts[(int)blockIdx.x - m.block0];
+  materialize_tensor<false>(d, m.recipes, m.ops, m.mats,
+                            m.params ? m.params + (int64_t)z * m.params_stride : nullptr,
+                            m.in + (int64_t)z * m.in_bs + d.offset);
+}
+
+hipError_t launch_materialize_many(hipStream_t s, MatArgs& a, int batch) {
+  if (a.n < 1 || a.n > kMatMax) return hipErrorInvalidValue;
+  int blocks = 0;
+  for (int i = 0; i < a.n; ++i) {
+    if (a.net[i].n_tensors < 1) return hipErrorInvalidValue;
+    a.net[i].block0 = blocks;
+    blocks += a.net[i].n_tensors;
+  }
+  hipLaunchKernelGGL(k_materialize_many, dim3(blocks, batch), dim3(kRecipeThreads), 0, s, a);
+  return hipGetLastError();
 }
 
 // one_bits: the 32-bit pattern of the value 1 (1.0f, or 2^28 in Q3.28)

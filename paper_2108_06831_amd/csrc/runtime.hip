@@ -1095,6 +1095,7 @@ extern "C" size_t tn_expectation_workspace_bytes(tn_network* const* nets, tn_pat
 struct SideLanes {
   hipStream_t stream[kExpLanes - 1] = {};
   hipEvent_t fork = nullptr, join[kExpLanes - 1] = {};
+  std::mutex mu;
 };
 static std::mutex g_lanes_mu;
 static SideLanes* g_lanes[64];
@@ -1114,6 +1115,121 @@ static tn_status side_lanes(SideLanes** out) {
     g_lanes[dev] = L;
   }
   *out = g_lanes[dev];
+  return TN_OK;
+}
+
+// A circuit whose whole contraction is one ordered pass from |0...0>: several such run in one launch.
+static bool one_seq_pass(const tn_path* path) {
+  return path->slice_bits == 0 && path->seq.last && path->seq.prog.passes.size() == 1 &&
+         path->seq.bits == path->seq.prog.passes[0].l;
+}
+
+// The expectations of the circuits `which` (all one_seq_pass) in launches of several, on the lanes
+// lane0 .. lane0 + n_lanes - 1 (lane 0: the caller's stream): their input tensors, then one launch per
+// block size, the sizes on different lanes, joined into lane0.  Circuits go together as long as their
+// input tensors fit `ws_bytes`.
+static tn_status expect_seq(hipStream_t s_call, SideLanes* SL, int lane0, int n_lanes, int precision,
+                            const std::vector<int>& which, tn_network* const* nets, tn_path* const* paths,
+                            const double* const* params_dev, int batch, const tn_observable* obs,
+                            const std::vector<DevNet*>& devs, char* w, size_t ws_bytes, double* out_dev) {
+  auto stream = [&](int k) { return lane0 + k == 0 ? s_call : SL->stream[lane0 + k - 1]; };
+  auto event = [&](int k) { return lane0 + k == 0 ? SL->fork : SL->join[lane0 + k - 1]; };
+  hipStream_t s0 = stream(0);
+  for (size_t i0 = 0; i0 < which.size();) {
+    MatArgs mat;
+    mat.n = 0;
+    std::vector<int> group;
+    std::vector<float2*> in;
+    size_t used = 0;
+    for (; i0 < which.size() && mat.n < kMatMax; ++i0) {
+      const int c = which[i0];
+      const size_t bytes = align256(sizeof(float2) * (size_t)nets[c]->input_elems * batch);
+      if (!group.empty() && used + bytes > ws_bytes) break;
+      MatNet& m = mat.net[mat.n++];
+      const DevNet* d = devs[c];
+      m.ts = d->tensors; m.recipes = d->recipes; m.ops = d->ops; m.mats = d->mats;
+      m.params = params_dev ? params_dev[c] : nullptr;
+      m.params_stride = nets[c]->n_params;
+      m.in = (float2*)(w + used);
+      m.in_bs = nets[c]->input_elems;
+      m.n_tensors = (int)nets[c]->tensors.size();
+      group.push_back(c);
+      in.push_back(m.in);
+      used += bytes;
+    }
+    hipEvent_t ev = prof_start(s0, TN_KERNEL_MATERIALIZE);
+    HIP_TRY(launch_materialize_many(s0, mat, batch));
+    prof_stop(s0, ev, TN_KERNEL_MATERIALIZE, (double)used, 0.0);
+    // launches by block size, the largest states first
+    std::vector<SeqExpectArgs> launches;
+    std::vector<int> size;
+    std::vector<double> flops;
+    for (int l = kSeqMaxLocal; l >= 10; --l) {  // (chunks of up to 2^10 elements share a size)
+      SeqExpectArgs a;
+      a.n = 0;
+      int terms = 0;
+      double fl = 0;
+      auto flush = [&]() {
+        if (a.n == 0) return;
+        launches.push_back(a);
+        size.push_back(l);
+        flops.push_back(fl);
+        a.n = terms = 0;
+        fl = 0;
+      };
+      for (size_t k = 0; k < group.size(); ++k) {
+        const int c = group[k];
+        const SeqChain& ch = paths[c]->seq;
+        if (std::max(ch.bits, 10) != l) continue;
+        const SeqPass& ps = ch.prog.passes[0];
+        ZTerms t;
+        tn_status st = make_terms(nets[c], ch.in_bits, &obs[c], &t, ch.prog.segs[ps.first_seg + ps.n_segs - 1].rgpos);
+        if (st != TN_OK) return st;
+        if (a.n == kSeqExpectMax || terms + t.n > kSeqExpectTerms) flush();
+        const DevPath* dp = (const DevPath*)paths[c]->dev;
+        SeqCirc& q = a.c[a.n++];
+        q.segs = dp->seq_segs + ps.first_seg;
+        q.wins = dp->seq_wins + ps.first_win;
+        q.words = dp->seq_words;
+        q.vsrc = dp->seq_vals;
+        q.vals = in[k];
+        q.out = out_dev + (int64_t)c * batch;
+        q.vals_bs = nets[c]->input_elems;
+        q.n_segs = ps.n_segs;
+        q.l = ch.bits;
+        q.term0 = terms;
+        for (int m = 0; m <= 16; ++m) q.mu_start[m] = (uint8_t)t.mu_start[m];
+        for (int j = 0; j < t.n; ++j) {
+          a.mask[terms + j] = (uint32_t)t.mask[j];
+          a.coeff[terms + j] = t.coeff[j];
+        }
+        terms += t.n;
+        fl += ch.flops * batch;
+      }
+      flush();
+    }
+    const int lanes = std::min((int)launches.size(), n_lanes);
+    if (lanes > 1) {
+      HIP_TRY(hipEventRecord(event(0), s0));
+      for (int k = 1; k < lanes; ++k) HIP_TRY(hipStreamWaitEvent(stream(k), event(0), 0));
+    }
+    tn_status result = TN_OK;
+    for (size_t k = 0; k < launches.size() && result == TN_OK; ++k) {
+      hipStream_t s = stream((int)k % lanes);
+      ev = prof_start(s, TN_KERNEL_SWEEP);
+      const hipError_t e = launch_seq_expect(s, launches[k], batch, precision);
+      if (e != hipSuccess) result = set_error(TN_EDEVICE, std::string("expectation: ") + hipGetErrorString(e));
+      prof_stop(s, ev, TN_KERNEL_SWEEP, 0.0, flops[k]);
+    }
+    for (int k = 1; k < lanes; ++k) {
+      const hipError_t e1 = hipEventRecord(event(k), stream(k));
+      const hipError_t e2 = hipStreamWaitEvent(s0, event(k), 0);
+      if (result == TN_OK && (e1 != hipSuccess || e2 != hipSuccess))
+        result = set_error(TN_EDEVICE, std::string("joining the expectation lanes: ") +
+                                           hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+    }
+    if (result != TN_OK) return result;
+  }
   return TN_OK;
 }
 
@@ -1144,24 +1260,33 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
   }
   hipStream_t s0 = (hipStream_t)stream;
   // kernel timing measures per stream: with it on, every circuit runs on the caller's stream
-  const int lanes = g_prof ? 1 : expect_lanes(n_circuits);
+  const int max_lanes = g_prof ? 1 : expect_lanes(n_circuits);
   SideLanes* SL_ = nullptr;
-  if (lanes > 1) {
+  if (max_lanes > 1) {
     tn_status st = side_lanes(&SL_);
     if (st != TN_OK) return st;
+  }
+  // Circuits that are one ordered pass each run together, on the lanes that the others leave (in those
+  // lanes' part of the workspace), or before them on the caller's stream if they leave none.
+  std::vector<int> together, rest;
+  for (int c = 0; c < n_circuits; ++c) (one_seq_pass(paths[c]) ? together : rest).push_back(c);
+  const int lanes = std::min(max_lanes, (int)rest.size());
+  const int seq_lane0 = lanes < max_lanes ? lanes : 0;
+  const int seq_lanes = together.empty() ? 0 : lanes < max_lanes ? std::min(max_lanes - lanes, kSeqExpectSizes) : 1;
+  const int used = std::max(lanes, seq_lane0 + seq_lanes);
+  std::unique_lock<std::mutex> lanes_lock;  // (another thread's fork event must not come between ours and its waits)
+  if (used > 1) {
+    lanes_lock = std::unique_lock<std::mutex>(SL_->mu);
     HIP_TRY(hipEventRecord(SL_->fork, s0));
-    for (int k = 0; k < lanes - 1; ++k) HIP_TRY(hipStreamWaitEvent(SL_->stream[k], SL_->fork, 0));
+    for (int k = 0; k < used - 1; ++k) HIP_TRY(hipStreamWaitEvent(SL_->stream[k], SL_->fork, 0));
   }
   // circuits to lanes by the planner's run-time model, largest first, each to the lane with the
   // least work so far (ties: the lower lane), so that the lanes finish close together
   std::vector<int> lane_of(n_circuits, 0);
   if (lanes > 1) {
-    std::vector<int> order(n_circuits);
+    std::vector<int> order = rest;
     std::vector<double> cost(n_circuits);
-    for (int c = 0; c < n_circuits; ++c) {
-      order[c] = c;
-      cost[c] = paths[c]->stats.modeled_seconds * std::ldexp(1.0, paths[c]->slice_bits);
-    }
+    for (int c : rest) cost[c] = paths[c]->stats.modeled_seconds * std::ldexp(1.0, paths[c]->slice_bits);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     std::vector<double> load(lanes, 0.0);
     for (int c : order) {
@@ -1171,7 +1296,11 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
     }
   }
   tn_status result = TN_OK;
-  for (int c = 0; c < n_circuits && result == TN_OK; ++c) {
+  if (!together.empty())
+    result = expect_seq(s0, SL_, seq_lane0, seq_lanes, precision, together, nets, paths, params_dev, batch, obs, devs,
+                        (char*)workspace_dev + (size_t)seq_lane0 * slot, (size_t)seq_lanes * slot, out_dev);
+  for (int c : rest) {
+    if (result != TN_OK) break;
     tn_network* net = nets[c];
     tn_path* path = paths[c];
     const double* prm = params_dev ? params_dev[c] : nullptr;
@@ -1228,7 +1357,7 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
     prof_stop(s, ev, TN_KERNEL_REDUCE, 8.0 * (double)(n_partial > 0 ? n_partial : path->final_elems) * batch, 0.0);
   }
   // join the lanes back into the caller's stream (also after an error, so no lane stays forked)
-  for (int k = 0; k < lanes - 1; ++k) {
+  for (int k = 0; k < used - 1; ++k) {
     const hipError_t e1 = hipEventRecord(SL_->join[k], SL_->stream[k]);
     const hipError_t e2 = hipStreamWaitEvent(s0, SL_->join[k], 0);
     if (result == TN_OK && (e1 != hipSuccess || e2 != hipSuccess))

@@ -197,41 +197,21 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-// NS = 1: forward, from the state `in` (or |0...0>) to `out`; vals: the network's
-// input tensors.  NS = 2: reverse sweep over psi and lambda; vals: U of every
-// gate; gradient slot s of wave w of chunk c into partials[s][c * waves + w].
-template <int PREC, int NS, int LMAX>
-__global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const SeqSeg* __restrict__ segs,
-                                                              const SeqWindow* __restrict__ wins,
-                                                              const uint32_t* __restrict__ words,
-                                                              const int32_t* __restrict__ vsrc,
-                                                              const float2* __restrict__ vals) {
-  constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
-  __shared__ float2 bx[kBuf];
-  __shared__ float2 by[NS == 2 ? kBuf : 1];
-  __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];  // the window's values (a reverse sweep's conjugated)
-  __shared__ uint32_t wwin[kSeqWinWords];
-  const int z = blockIdx.y, lane = threadIdx.x & 63;
-  // chunks of fewer than 2^10 elements leave threads of the wave without elements: they repeat others
-  const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
-  const bool active = (int)threadIdx.x < n_thr;
-  const uint32_t base = (uint32_t)deposit(blockIdx.x, a.rest, a.n_rest);
-  const float2* V = vals + (int64_t)z * a.vals_bs;
-  float2* P = const_cast<float2*>(a.in) + (int64_t)z * a.in_bs;
-  float2* O = a.out + (int64_t)z * a.out_bs;
-  const int col = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  double* part = a.partials + (int64_t)z * a.pstride + col;
-  auto add_grad = [&](int slot, double v) {
-    v = wave_sum_d(active ? v : 0.0);
-    if (lane == 63) part[(int64_t)slot * kReduceBlocks] = v;
-  };
-  float2 x[16], y[16];  // psi (or the state), lambda
+// The gates of a pass on the thread's sixteen elements of the state x (and of y
+// where NS = 2).  load(seg, A) fills them in the first segment's layout, A the
+// address of the thread's combination 0; they are left in the last one's.
+template <int PREC, int NS, class Load, class Grad>
+__device__ __forceinline__ void seq_run(float2 (&x)[16], float2 (&y)[16], float2* bx, float2* by, float2* vwin,
+                                        uint32_t* wwin, int n_segs, const SeqSeg* __restrict__ segs,
+                                        const SeqWindow* __restrict__ wins, const uint32_t* __restrict__ words,
+                                        const int32_t* __restrict__ vsrc, const float2* V, uint32_t base, int tid,
+                                        Load load, Grad add_grad) {
   int slot = 0;
   const int32_t* off = nullptr;
   int win = 0, win_end = 0;  // the window's number and the end of its segments
   int wi = 0, vi = 0;        // the next operation's word and value
   auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)wwin[i]); };
-  for (int sg = 0; sg < a.n_segs; ++sg) {
+  for (int sg = 0; sg < n_segs; ++sg) {
     if (sg == win_end) {
       const SeqWindow w = wins[win++];
       __syncthreads();  // the window before is no longer read
@@ -248,17 +228,7 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
     const int ob = bits10(tid, seg.tpos), ns = ob + (ob >> 5);
     const uint32_t A = base | (uint32_t)bits10(tid, seg.gpos);
     if (sg == 0) {
-      const uint32_t g0 = 1u << seg.rgpos[0], g1 = 1u << seg.rgpos[1], g2 = 1u << seg.rgpos[2], g3 = 1u << seg.rgpos[3];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t e = A | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0);
-        if (NS == 1 && a.from_zero) {
-          x[r] = f2(e == 0 ? 1.f : 0.f, 0.f);
-        } else {
-          x[r] = P[e];
-          if (NS == 2) y[r] = O[e];
-        }
-      }
+      load(seg, A);
     } else {
       // each thread writes the slots it read last, so one barrier separates the layouts
 #pragma unroll
@@ -384,24 +354,112 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
         vi += 16;
       }
     }
-    if (sg == a.n_segs - 1) {
-      if (NS == 1) {
-        const uint32_t e0 = (uint32_t)deposit(blockIdx.x, a.rest_out, a.n_rest) | (uint32_t)bits10(tid, a.out_t);
-        const uint32_t g0 = 1u << a.out_r[0], g1 = 1u << a.out_r[1], g2 = 1u << a.out_r[2], g3 = 1u << a.out_r[3];
+  }
+}
+
+// address of register combination r of a segment, from its combination 0
+__device__ __forceinline__ uint32_t seg_addr(const SeqSeg& seg, uint32_t A, int r) {
+  return A | (r & 1 ? 1u << seg.rgpos[0] : 0) | (r & 2 ? 1u << seg.rgpos[1] : 0) | (r & 4 ? 1u << seg.rgpos[2] : 0) |
+         (r & 8 ? 1u << seg.rgpos[3] : 0);
+}
+
+// NS = 1: forward, from the state `in` (or |0...0>) to `out`; vals: the network's
+// input tensors.  NS = 2: reverse sweep over psi and lambda; vals: U of every
+// gate; gradient slot s of wave w of chunk c into partials[s][c * waves + w].
+template <int PREC, int NS, int LMAX>
+__global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const SeqSeg* __restrict__ segs,
+                                                              const SeqWindow* __restrict__ wins,
+                                                              const uint32_t* __restrict__ words,
+                                                              const int32_t* __restrict__ vsrc,
+                                                              const float2* __restrict__ vals) {
+  constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
+  __shared__ float2 bx[kBuf];
+  __shared__ float2 by[NS == 2 ? kBuf : 1];
+  __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];  // the window's values (a reverse sweep's conjugated)
+  __shared__ uint32_t wwin[kSeqWinWords];
+  const int z = blockIdx.y, lane = threadIdx.x & 63;
+  // chunks of fewer than 2^10 elements leave threads of the wave without elements: they repeat others
+  const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
+  const bool active = (int)threadIdx.x < n_thr;
+  const uint32_t base = (uint32_t)deposit(blockIdx.x, a.rest, a.n_rest);
+  const float2* V = vals + (int64_t)z * a.vals_bs;
+  float2* P = const_cast<float2*>(a.in) + (int64_t)z * a.in_bs;
+  float2* O = a.out + (int64_t)z * a.out_bs;
+  const int col = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  double* part = a.partials + (int64_t)z * a.pstride + col;
+  auto add_grad = [&](int slot, double v) {
+    v = wave_sum_d(active ? v : 0.0);
+    if (lane == 63) part[(int64_t)slot * kReduceBlocks] = v;
+  };
+  float2 x[16], y[16];  // psi (or the state), lambda
+  seq_run<PREC, NS>(x, y, bx, by, vwin, wwin, a.n_segs, segs, wins, words, vsrc, V, base, tid,
+                    [&](const SeqSeg& seg, uint32_t A) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          O[e0 | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0)] = x[r];
-      } else {
-        const uint32_t g0 = 1u << seg.rgpos[0], g1 = 1u << seg.rgpos[1], g2 = 1u << seg.rgpos[2], g3 = 1u << seg.rgpos[3];
+                      for (int r = 0; r < 16; ++r) {
+                        const uint32_t e = seg_addr(seg, A, r);
+                        if (NS == 1 && a.from_zero) {
+                          x[r] = f2(e == 0 ? 1.f : 0.f, 0.f);
+                        } else {
+                          x[r] = P[e];
+                          if (NS == 2) y[r] = O[e];
+                        }
+                      }
+                    },
+                    add_grad);
+  if (NS == 1) {
+    const uint32_t e0 = (uint32_t)deposit(blockIdx.x, a.rest_out, a.n_rest) | (uint32_t)bits10(tid, a.out_t);
+    const uint32_t g0 = 1u << a.out_r[0], g1 = 1u << a.out_r[1], g2 = 1u << a.out_r[2], g3 = 1u << a.out_r[3];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const uint32_t e = A | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0);
-          P[e] = x[r];
-          O[e] = y[r];
-        }
-      }
+    for (int r = 0; r < 16; ++r)
+      O[e0 | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0)] = x[r];
+  } else {
+    const SeqSeg& seg = segs[a.n_segs - 1];
+    const uint32_t A = base | (uint32_t)bits10(tid, seg.gpos);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      P[seg_addr(seg, A, r)] = x[r];
+      O[seg_addr(seg, A, r)] = y[r];
     }
   }
+}
+
+// Expectations of several circuits, one block per circuit and parameter vector:
+// each state from |0...0> through its gates, then sum |x|^2 D(x) in FP64.  (16
+// circuits of 8 to 14 qubits as launches of their own took 493 us, most of it
+// four blocks at a time on the runtime's four queues.)
+template <int PREC, int LMAX>
+__global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_expect(SeqExpectArgs a) {
+  constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
+  __shared__ float2 bx[kBuf];
+  __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];
+  __shared__ uint32_t wwin[kSeqWinWords];
+  const SeqCirc& c = a.c[blockIdx.x];
+  const int z = blockIdx.y;
+  const int n_thr = 1 << (c.l - 4), tid = threadIdx.x & (n_thr - 1);
+  float2 x[16], y[16];
+  seq_run<PREC, 1>(x, y, bx, nullptr, vwin, wwin, c.n_segs, c.segs, c.wins, c.words, c.vsrc,
+                   c.vals + (int64_t)z * c.vals_bs, 0, tid,
+                   [&](const SeqSeg& seg, uint32_t A) {
+#pragma unroll
+                     for (int r = 0; r < 16; ++r) x[r] = f2(seg_addr(seg, A, r) == 0 ? 1.f : 0.f, 0.f);
+                   },
+                   [](int, double) {});
+  const uint32_t A = (uint32_t)bits10(tid, c.segs[c.n_segs - 1].gpos);
+  double w[16];
+#pragma unroll
+  for (int mu = 0; mu < 16; ++mu) {
+    double acc = 0;
+    for (int i = c.term0 + c.mu_start[mu]; i < c.term0 + c.mu_start[mu + 1]; ++i)
+      acc += (__popc(A & a.mask[i]) & 1) ? -a.coeff[i] : a.coeff[i];
+    w[mu] = acc;
+  }
+  walsh16(w);
+  double s = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s += ((double)x[r].x * x[r].x + (double)x[r].y * x[r].y) * w[r];
+  __syncthreads();  // vwin is no longer read
+  s = block_sum((int)threadIdx.x < n_thr ? s : 0.0, reinterpret_cast<double*>(vwin));
+  if (threadIdx.x == 0) c.out[z] = s;
 }
 
 template <int PREC, int NS>
@@ -436,6 +494,26 @@ bool seq_args(const SeqPass& ps, int bits, int lmax, const int8_t* out_pos, SeqA
 }
 
 }  // namespace
+
+hipError_t launch_seq_expect(hipStream_t s, const SeqExpectArgs& a, int batch, int precision) {
+  if (a.n < 1 || a.n > kSeqExpectMax) return hipErrorInvalidValue;
+  const int l = a.c[0].l, threads = std::max(64, 1 << (l - 4));
+  for (int i = 0; i < a.n; ++i) {
+    const SeqCirc& c = a.c[i];
+    if (c.l < kSeqMinBits || c.l > kSeqMaxLocal || std::max(64, 1 << (c.l - 4)) != threads || c.n_segs < 1 ||
+        c.term0 < 0 || c.term0 + c.mu_start[16] > kSeqExpectTerms)
+      return hipErrorInvalidValue;
+  }
+  const dim3 grid(a.n, batch), block(threads);
+  if (precision == TN_PREC_BF16X3) {
+    if (l <= 12) hipLaunchKernelGGL((k_seq_expect<TN_PREC_BF16X3, 12>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_seq_expect<TN_PREC_BF16X3, kSeqMaxLocal>), grid, block, 0, s, a);
+  } else {
+    if (l <= 12) hipLaunchKernelGGL((k_seq_expect<TN_PREC_C64, 12>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_seq_expect<TN_PREC_C64, kSeqMaxLocal>), grid, block, 0, s, a);
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const SeqSeg& last,
                               const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,

@@ -793,37 +793,80 @@ struct GemmArgs {
   float2* C;
   int64_t a_bs, b_bs, c_bs;
   int64_t batch, M, N, K;
-  int64_t tiles_m, tiles_n;
-  int64_t band_n;   // tile columns per band of the tile order (divides tiles_n)
-  int64_t c_elems;  // elements of C per parameter vector (split-K partial stride)
-  int32_t nbb, nbm, nbn, nbk, split, xcd;
+  int32_t nbb, nbm, nbn, nbk;
   int8_t a_b[kGemmMaxBits], a_m[kGemmMaxBits], a_k[kGemmMaxBits];
   int8_t b_b[kGemmMaxBits], b_k[kGemmMaxBits], b_n[kGemmMaxBits];
   int8_t c_b[kGemmMaxBits], c_m[kGemmMaxBits], c_n[kGemmMaxBits];
 };
 
+// The matrix-core tiles' view of a product.  Every size is a power of two.
+constexpr int kTileBits = 12;
+struct TileArgs {
+  const float2* A;
+  const float2* B;
+  float2* C;
+  int64_t a_bs, b_bs, c_bs;
+  int64_t M, N, K;
+  int64_t c_elems;  // elements of C per parameter vector (split-K partial stride)
+  int32_t xcd;
+  int32_t lg_tm, lg_tn, lg_band, lg_split, lg_batch;  // tile rows, tile columns, columns per band, ranges of K, batch groups
+  // the bits of a block's result tile (64 x 64, or 64 x 32, at a time), ascending by their
+  // address in C: address bit, place in LDS (linear over XOR), m (low byte) and n (high byte)
+  int32_t st_pos[kTileBits], st_lds[kTileBits], st_mn[kTileBits];
+  int32_t lines;   // a tile holds whole 128-byte lines of C (else several blocks write to a line, which may meet in L2)
+  int32_t c_next;  // address bit of C between the rounds of a 128-row tile
+  // address bits of a tile's rows of A, columns of B, and of the low 10 bits of k (a K tile's, then the tile's number)
+  int32_t a_row[7], b_col[7], a_k[10], b_k[10];
+  // which index bit each address bit of an operand is: source (1 the batch; A: 2 m, 3 k; B: 2 n, 3 k; C: 2 m, 3 n)
+  // times 64, plus the bit
+  uint8_t from_a[64], from_b[64], from_c[64];
+};
+
+// An address from its indices: lane p decides address bit p, and the wave's vote is the address.  (A loop over the
+// index's bits waits for each four positions in turn; with those, and 64-bit divisions by the tile counts, the kernels'
+// first load came after some 2000 scalar instructions: a launch of small products took 9.2 us, now 5.6; 8192 x 32768 x
+// 16 for a 28-qubit state, 65536 blocks of one K tile, 700 us, now 490.)
+__device__ __forceinline__ int64_t gather_bits(unsigned from, int64_t x1, int64_t x2, int64_t x3) {
+  const unsigned src = from >> 6;
+  const int64_t x = src == 1 ? x1 : src == 2 ? x2 : x3;
+  return (int64_t)__ballot(src != 0 && ((x >> (from & 63)) & 1));
+}
+
+// the low n bits of x to the given places
+template <int N>
+__device__ __forceinline__ int64_t place_bits(int x, const int32_t* pos) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const uint64_t at = (uint64_t)1 << pos[j];
+    const uint32_t on = 0u - ((unsigned)(x >> j) & 1u);
+    lo |= on & (uint32_t)at;
+    hi |= on & (uint32_t)(at >> 32);
+  }
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // Tile order of the matrix-product kernels.  The GPU hands consecutive
 // workgroup ids to its eight XCDs in turn, and each XCD has its own L2.  With
 // xcd set (the grid is a multiple of 8), workgroup h takes logical id
 // (h mod 8) * (grid / 8) + h / 8, so each XCD runs one contiguous range of
-// logical ids, in order.  Logical ids walk the tile grid in bands of band_n
-// tile columns, n fastest inside a band: an XCD's range then covers a block of
-// rows of one band, whose B column tiles stay in its L2 while the rows pass
-// and whose A row tiles are used band_n times in a row.
+// logical ids, in order.  Logical ids walk the tile grid in bands of
+// 2^lg_band tile columns, n fastest inside a band: an XCD's range then covers a
+// block of rows of one band, whose B column tiles stay in its L2 while the rows
+// pass and whose A row tiles are used 2^lg_band times in a row.
 struct TileCoord {
-  int64_t tm, tn, rest;  // rest: the split, batch and parameter-vector index
+  int64_t tm, tn;
+  uint32_t ks, gb, z;  // range of K, batch group, parameter vector
 };
 
-__device__ inline TileCoord tile_coord(const GemmArgs& g) {
-  int64_t bid = blockIdx.x;
-  if (g.xcd) {
-    const int64_t per = (int64_t)gridDim.x >> 3;
-    bid = (bid & 7) * per + (bid >> 3);
-  }
-  const int64_t tmn = g.tiles_m * g.tiles_n;
-  const int64_t r = bid % tmn, band_tiles = g.tiles_m * g.band_n;
-  const int64_t band = r / band_tiles, q = r - band * band_tiles;
-  return {q / g.band_n, band * g.band_n + q % g.band_n, bid / tmn};
+__device__ inline TileCoord tile_coord(const TileArgs& g) {
+  uint32_t bid = blockIdx.x;
+  if (g.xcd) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  const uint32_t r = bid & ((1u << (g.lg_tm + g.lg_tn)) - 1), rest = bid >> (g.lg_tm + g.lg_tn);
+  const uint32_t band = r >> (g.lg_tm + g.lg_band), q = r & ((1u << (g.lg_tm + g.lg_band)) - 1);
+  return {(int64_t)(q >> g.lg_band), (int64_t)((band << g.lg_band) + (q & ((1u << g.lg_band) - 1))),
+          rest & ((1u << g.lg_split) - 1), (rest >> g.lg_split) & ((1u << g.lg_batch) - 1),
+          rest >> (g.lg_split + g.lg_batch)};
 }
 
 // BF16x3 split precision: x_hi = bf16(x), x_lo = bf16(x - x_hi), both round
@@ -847,6 +890,60 @@ __device__ inline bf16x8 b_embed(uint4 w, int d) {
   return __builtin_bit_cast(bf16x8, r);
 }
 
+// Result tiles go through LDS so that a wave stores along C's lowest address
+// bits, whichever of m and n they are: a matrix-core result holds 32 columns
+// of one row per half-wave, and stored from there a line of C is written in up
+// to 16 pieces (complex64, 8 x 1024 x 1024 x 4 with C's bits alternating
+// between m and n: 87 us, 30 through LDS; a line's pieces do not meet in L2
+// again before they are written).  Element (r, c) of the 64 x 64 (64 x 32) elements
+// is at place r BN + (c ^ reversed low bits of r): C's lowest five tile bits
+// are the lowest a of n and b of m, so 32 lanes read 32 distinct bank pairs.
+__host__ __device__ __forceinline__ int tile_place(int r, int c, int bn) {
+  return r * bn + (c ^ ((r & 1) << 4 | (r & 2) << 2 | (r & 4) | (r & 8) >> 2 | (r & 16) >> 4));
+}
+
+// Elements of T (2^nb of them) to C: thread t and round e hold element e 256 + t
+// in the order of the tile's bits; limits: m and n that exist beyond the tile's
+// origin (whole: no guards).
+template <int NB>
+__device__ __forceinline__ void store_tile(const TileArgs& g, const float2* T, float2* C, bool whole, int64_t m_left,
+                                           int64_t n_left) {
+  const int t = threadIdx.x;
+  const int64_t at = place_bits<8>(t, g.st_pos);
+  int lt = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lt ^= (0 - ((t >> j) & 1)) & g.st_lds[j];
+  constexpr int kRounds = 1 << (NB - 8);
+  int64_t ae[kRounds];
+  int le[kRounds];
+  float2 v[kRounds];
+  ae[0] = 0;
+  le[0] = 0;
+#pragma unroll
+  for (int e = 1; e < kRounds; ++e) {
+    const int j = 8 + __builtin_ctz(e), e1 = e & (e - 1);
+    ae[e] = ae[e1] | (int64_t)1 << g.st_pos[j];
+    le[e] = le[e1] ^ g.st_lds[j];
+  }
+#pragma unroll
+  for (int e = 0; e < kRounds; ++e) v[e] = T[lt ^ le[e]];
+  if (whole && g.lines) {
+#pragma unroll
+    for (int e = 0; e < kRounds; ++e) store_stream(C + ae[e] + at, v[e].x, v[e].y);
+    return;
+  }
+  int mt = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) mt |= (0 - ((t >> j) & 1)) & g.st_mn[j];
+#pragma unroll
+  for (int e = 0; e < kRounds; ++e) {
+    int mn = mt;
+#pragma unroll
+    for (int j = 8; j < NB; ++j) mn |= (e >> (j - 8)) & 1 ? g.st_mn[j] : 0;
+    if ((mn & 255) < m_left && (mn >> 8) < n_left) C[ae[e] + at] = v[e];
+  }
+}
+
 // Complex GEMM on the matrix cores.
 //
 // With complex64 stored as interleaved (re, im), A (M x K complex) is read as
@@ -865,14 +962,13 @@ __device__ inline bf16x8 b_embed(uint4 w, int d) {
 // or four complex values of one B column turned into B' entries (b_embed).
 // Operands are split into hi/lo once, while a tile is staged into LDS.
 template <int AK, int BNF, int TM, int TN, int F>
-__global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
+__global__ __launch_bounds__(kThreads) void k_gemm(TileArgs g) {
   constexpr int BM = 64 * TM, BN = 32 * TN;
   constexpr int kPA = (BM * kBK) / kThreads, kPB = (BN * kBK) / kThreads;
   constexpr int kF32Bytes = 2 * kBK * (BM + 1) * 4 + kBK * (BN + 1) * 8;
   constexpr int kB3Bytes = 2 * BM * kB3Row * 2 + 2 * BN * kB3Row * 2;
-  constexpr int kSmem = F == 0 ? kF32Bytes : kB3Bytes;
+  constexpr int kSmem = std::max(F == 0 ? kF32Bytes : kB3Bytes, 64 * BN * 8);
   __shared__ __attribute__((aligned(16))) char smem[kSmem];
-  __shared__ int64_t TAm[BM], TCm[BM], TBn[BN], TCn[BN], TAk[kBK], TBk[kBK];
   constexpr int kKt = 64;  // K tiles whose origin deposits are tabulated (the rest computed on the fly)
   __shared__ int64_t TAt[kKt], TBt[kKt];
   float (*As_re)[BM + 1] = reinterpret_cast<float (*)[BM + 1]>(smem);
@@ -885,42 +981,26 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
 
   const TileCoord tc = tile_coord(g);
   const int64_t tn = tc.tn, tm = tc.tm;
-  int64_t bid = tc.rest;
-  const int64_t ks = bid % g.split;
-  bid /= g.split;
-  const int64_t gb = bid % g.batch;
-  const int64_t z = bid / g.batch;
+  const int64_t ks = tc.ks, z = tc.z;
+  const int64_t gb = tc.gb;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const unsigned from_a = g.from_a[lane], from_b = g.from_b[lane], from_c = g.from_c[lane];
   const float2* A = g.A + z * g.a_bs;
   const float2* B = g.B + z * g.b_bs;
   float2* C = g.C + z * g.c_bs + ks * g.c_elems;
   const int64_t m0 = tm * BM, n0 = tn * BN;
-  const int64_t kchunk = g.K / g.split;
+  const int64_t kchunk = g.K >> g.lg_split;
   const int64_t kbeg = ks * kchunk, kend = kbeg + kchunk;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const int64_t base_a = deposit(gb, g.a_b, g.nbb) | deposit(m0, g.a_m, g.nbm);
-  const int64_t base_b = deposit(gb, g.b_b, g.nbb) | deposit(n0, g.b_n, g.nbn);
-  const int64_t base_c = deposit(gb, g.c_b, g.nbb) | deposit(m0, g.c_m, g.nbm) | deposit(n0, g.c_n, g.nbn);
-  constexpr int kLogBM = 6 + (TM == 2), kLogBN = 5 + (TN == 2);
-  if (tid < BM) {
-    const int nb = min(g.nbm, kLogBM);
-    TAm[tid] = deposit(tid, g.a_m, nb);
-    TCm[tid] = deposit(tid, g.c_m, nb);
+  const int64_t base_a = gather_bits(from_a, gb, m0, 0);
+  const int64_t base_b = gather_bits(from_b, gb, n0, 0);
+  const int64_t base_c = gather_bits(from_c, gb, m0, n0);
+  const int64_t beg_a = gather_bits(from_a, 0, 0, kbeg), beg_b = gather_bits(from_b, 0, 0, kbeg);
+  if (tid < kKt) {
+    TAt[tid] = beg_a | place_bits<6>(tid, g.a_k + 4);
+    TBt[tid] = beg_b | place_bits<6>(tid, g.b_k + 4);
   }
-  if (tid < BN) {
-    const int nb = min(g.nbn, kLogBN);
-    TBn[tid] = deposit(tid, g.b_n, nb);
-    TCn[tid] = deposit(tid, g.c_n, nb);
-  }
-  if (tid < kBK) {
-    const int nb = min(g.nbk, 4);
-    TAk[tid] = deposit(tid, g.a_k, nb);
-    TBk[tid] = deposit(tid, g.b_k, nb);
-  }
-  if (tid < kKt && kbeg + (int64_t)tid * kBK < kend) {
-    TAt[tid] = deposit(kbeg + (int64_t)tid * kBK, g.a_k, g.nbk);
-    TBt[tid] = deposit(kbeg + (int64_t)tid * kBK, g.b_k, g.nbk);
-  }
+  constexpr int kLogBN = 5 + (TN == 2);
   floatx16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -946,11 +1026,16 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
   const float2* pb[kPB];
   bool va[kPA], vb[kPB];
   int ka_e[kPA], kb_e[kPB];
+  int a_m0, a_k0, b_n0, b_k0;  // element 0's; the others' differ by bits of their own
+  a_elem(0, a_m0, a_k0);
+  b_elem(0, b_n0, b_k0);
+  const int64_t at_a = base_a | place_bits<7>(a_m0, g.a_row) | place_bits<4>(a_k0, g.a_k);
+  const int64_t at_b = base_b | place_bits<6>(b_n0, g.b_col) | place_bits<4>(b_k0, g.b_k);
 #pragma unroll
   for (int e = 0; e < kPA; ++e) {
     int mm, kk;
     a_elem(e, mm, kk);
-    pa[e] = A + (base_a | TAm[mm] | TAk[kk]);
+    pa[e] = A + (at_a | place_bits<7>(mm ^ a_m0, g.a_row) | place_bits<4>(kk ^ a_k0, g.a_k));
     va[e] = m0 + mm < g.M;
     ka_e[e] = kk;
   }
@@ -958,7 +1043,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
   for (int e = 0; e < kPB; ++e) {
     int nn, kk;
     b_elem(e, nn, kk);
-    pb[e] = B + (base_b | TBn[nn] | TBk[kk]);
+    pb[e] = B + (at_b | place_bits<6>(nn ^ b_n0, g.b_col) | place_bits<4>(kk ^ b_k0, g.b_k));
     vb[e] = n0 + nn < g.N;
     kb_e[e] = kk;
   }
@@ -966,8 +1051,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
   float2 ra[kPA], rb[kPB];
   auto fetch = [&](int64_t k0) {
     const int64_t t = (k0 - kbeg) / kBK;
-    const int64_t ka = t < kKt ? TAt[t] : deposit(k0, g.a_k, g.nbk);
-    const int64_t kb = t < kKt ? TBt[t] : deposit(k0, g.b_k, g.nbk);
+    const int64_t ka = t < kKt ? TAt[t] : gather_bits(from_a, 0, 0, k0);
+    const int64_t kb = t < kKt ? TBt[t] : gather_bits(from_b, 0, 0, k0);
     const int64_t rem = kend - k0;
     const int kleft = rem < kBK ? (int)rem : kBK;  // valid k of this tile
     if (interior && kleft == kBK) {  // whole tile inside the operands: no guards
@@ -1074,19 +1159,21 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
     }
     __syncthreads();
   }
-  float* Cf = reinterpret_cast<float*>(C);
+  const bool whole = m0 + BM <= g.M && n0 + BN <= g.N;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i) {
+    if (i > 0) __syncthreads();
+    const int own = tile_place(wm * 32 + 4 * (lane >> 5), wn * 16 * TN + ((lane & 31) >> 1), BN);
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int rl = wm * 32 * TM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int jj = lane & 31;
-        const int cl = wn * 16 * TN + j * 16 + (jj >> 1);
-        if (m0 + rl < g.M && n0 + cl < g.N)
-          __builtin_nontemporal_store(acc[i][j][v], &Cf[(base_c | TCm[rl] | TCn[cl]) * 2 + (jj & 1)]);
-      }
+      for (int v = 0; v < 16; ++v)
+        reinterpret_cast<float*>(smem)[2 * (own ^ tile_place(8 * (v >> 2) + (v & 3), j * 16, BN)) + (lane & 1)] =
+            acc[i][j][v];
+    __syncthreads();
+    store_tile<6 + kLogBN>(g, reinterpret_cast<const float2*>(smem), C + (base_c | (i ? (int64_t)1 << g.c_next : 0)),
+                           whole, g.M - m0 - 32 * i, g.N - n0);
+  }
 }
 
 // 3M form on the FP32 matrix cores: with A = Ar + i Ai and B = Br + i Bi,
@@ -1099,7 +1186,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g) {
 // P3 = (Ar + Ai)(Br + Bi)).  Four waves in a 2 x 2 arrangement, each owning
 // TM tiles of 32 x 32 complex: the block computes (64 TM) x 64.
 template <int AK, int BNF, int TM, int BK, int NW, int BP>
-__global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(GemmArgs g) {
+__global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(TileArgs g) {
   // BP = 1 (batch-packed): four batch items of at most 32 x 32 per block, wave
   // w computing item w; operand "rows" are (item, m) for A and (item, n) for
   // B.  BP = 2 (column-packed): M <= 32 and four 32-column slices of N per
@@ -1115,66 +1202,32 @@ __global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(Gem
   // rows start on distinct multiples of 4 banks (36 r mod 64)
   static_assert(BK % 8 == 0, "whole 16-byte operand reads");
   constexpr int kRow = 2 * BK + 4;
-  __shared__ __attribute__((aligned(16))) float As[BM * kRow], Bs[BN * kRow];
-  __shared__ int64_t TAm[BM], TCm[BM], TBn[BN], TCn[BN], TAk[BK], TBk[BK];
+  constexpr int kStage = (BM + BN) * kRow, kTile = 64 * 64 * 2;
+  __shared__ __attribute__((aligned(16))) float smem[kStage > kTile ? kStage : kTile];
+  float* const As = smem;
+  float* const Bs = smem + BM * kRow;
   constexpr int kKt = 64;  // K tiles whose origin deposits are tabulated (the rest computed on the fly)
   __shared__ int64_t TAt[kKt], TBt[kKt];
   const TileCoord tc = tile_coord(g);
   const int64_t tn = tc.tn, tm = tc.tm;
-  int64_t bid = tc.rest;
-  const int64_t ks = bid % g.split;
-  bid /= g.split;
-  const int64_t n_bgroups = BP == 1 ? g.batch / 4 : g.batch;
-  const int64_t gb = (bid % n_bgroups) * (BP == 1 ? 4 : 1);
-  const int64_t z = bid / n_bgroups;
+  const int64_t ks = tc.ks, z = tc.z;
+  const int64_t gb = (int64_t)tc.gb << (BP == 1 ? 2 : 0);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const unsigned from_a = g.from_a[lane], from_b = g.from_b[lane], from_c = g.from_c[lane];
   const float2* A = g.A + z * g.a_bs;
   const float2* B = g.B + z * g.b_bs;
   float2* C = g.C + z * g.c_bs + ks * g.c_elems;
   const int64_t m0 = tm * BM, n0 = tn * BN;
-  const int64_t kchunk = g.K / g.split;
+  const int64_t kchunk = g.K >> g.lg_split;
   const int64_t kbeg = ks * kchunk, kend = kbeg + kchunk;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const int64_t base_a = deposit(gb, g.a_b, g.nbb) | deposit(m0, g.a_m, g.nbm);
-  const int64_t base_b = deposit(gb, g.b_b, g.nbb) | deposit(n0, g.b_n, g.nbn);
-  const int64_t base_c = deposit(gb, g.c_b, g.nbb) | deposit(m0, g.c_m, g.nbm) | deposit(n0, g.c_n, g.nbn);
-  constexpr int kLogBM = 6 + (TM == 2);
-  if constexpr (BP == 1) {
-    if (tid < 128) {  // row tid: item tid >> 5 (the two lowest batch bits), m or n tid & 31
-      const int it = tid >> 5, r = tid & 31, nbi = min(g.nbb, 2);
-      TAm[tid] = deposit(r, g.a_m, min(g.nbm, 5)) | deposit(it, g.a_b, nbi);
-      TCm[tid] = deposit(r, g.c_m, min(g.nbm, 5)) | deposit(it, g.c_b, nbi);
-      TBn[tid] = deposit(r, g.b_n, min(g.nbn, 5)) | deposit(it, g.b_b, nbi);
-      TCn[tid] = deposit(r, g.c_n, min(g.nbn, 5));
-    }
-  } else if constexpr (BP == 2) {
-    if (tid < 128) {  // row tid of A: slice tid >> 5, m tid & 31; row tid of B: n - n0 = tid
-      const int r = tid & 31;
-      TAm[tid] = deposit(r, g.a_m, min(g.nbm, 5));
-      TCm[tid] = deposit(r, g.c_m, min(g.nbm, 5)) | deposit(tid & ~31, g.c_n, min(g.nbn, 7));
-      TBn[tid] = deposit(tid, g.b_n, min(g.nbn, 7));
-      TCn[tid] = deposit(r, g.c_n, min(g.nbn, 5));
-    }
-  } else {
-    if (tid < BM) {
-      const int nb = min(g.nbm, kLogBM);
-      TAm[tid] = deposit(tid, g.a_m, nb);
-      TCm[tid] = deposit(tid, g.c_m, nb);
-    }
-    if (tid < BN) {
-      const int nb = min(g.nbn, 6);
-      TBn[tid] = deposit(tid, g.b_n, nb);
-      TCn[tid] = deposit(tid, g.c_n, nb);
-    }
-  }
-  if (tid < BK) {
-    const int nb = min(g.nbk, kLogBK);
-    TAk[tid] = deposit(tid, g.a_k, nb);
-    TBk[tid] = deposit(tid, g.b_k, nb);
-  }
-  if (tid < kKt && kbeg + (int64_t)tid * BK < kend) {
-    TAt[tid] = deposit(kbeg + (int64_t)tid * BK, g.a_k, g.nbk);
-    TBt[tid] = deposit(kbeg + (int64_t)tid * BK, g.b_k, g.nbk);
+  const int64_t base_a = gather_bits(from_a, gb, m0, 0);
+  const int64_t base_b = gather_bits(from_b, gb, n0, 0);
+  const int64_t base_c = gather_bits(from_c, gb, m0, n0);
+  const int64_t beg_a = gather_bits(from_a, 0, 0, kbeg), beg_b = gather_bits(from_b, 0, 0, kbeg);
+  if (tid < kKt) {
+    TAt[tid] = beg_a | place_bits<6>(tid, g.a_k + 4);
+    TBt[tid] = beg_b | place_bits<6>(tid, g.b_k + 4);
   }
   floatx16 p1[TM], p2[TM], p3[TM];
 #pragma unroll
@@ -1214,15 +1267,19 @@ __global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(Gem
   const float2* pa[NW ? 1 : kPA];
   const float2* pb[NW ? 1 : kPB];
   uint32_t oa[NW ? kPA : 1], ob[NW ? kPB : 1];
+  // (column-packed: A's rows repeat per slice)
+  const int64_t thr_a = place_bits<7>(BP == 2 ? a_rt & 31 : a_rt, g.a_row) | place_bits<4>(a_kt, g.a_k);
+  const int64_t thr_b = place_bits<7>(b_rt, g.b_col) | place_bits<4>(b_kt, g.b_k);
 #pragma unroll
   for (int e = 0; e < kPA; ++e) {
-    const int64_t off = TAm[a_rt + row_e(kfa, e)] | TAk[a_kt + k_e(kfa, e)];
+    const int re = row_e(kfa, e);
+    const int64_t off = thr_a | place_bits<7>(BP == 2 ? re & 31 : re, g.a_row) | place_bits<4>(k_e(kfa, e), g.a_k);
     if constexpr (NW) oa[e] = (uint32_t)off * (uint32_t)sizeof(float2);
     else pa[e] = A + (base_a | off);
   }
 #pragma unroll
   for (int e = 0; e < kPB; ++e) {
-    const int64_t off = TBn[b_rt + row_e(kfb, e)] | TBk[b_kt + k_e(kfb, e)];
+    const int64_t off = thr_b | place_bits<7>(row_e(kfb, e), g.b_col) | place_bits<4>(k_e(kfb, e), g.b_k);
     if constexpr (NW) ob[e] = (uint32_t)off * (uint32_t)sizeof(float2);
     else pb[e] = B + (base_b | off);
   }
@@ -1235,8 +1292,8 @@ __global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(Gem
   float2 ra[kPA], rb[kPB];
   auto fetch = [&](int64_t k0) {
     const int64_t t = (k0 - kbeg) / BK;
-    int64_t ka = t < kKt ? TAt[t] : deposit(k0, g.a_k, g.nbk);
-    int64_t kb = t < kKt ? TBt[t] : deposit(k0, g.b_k, g.nbk);
+    int64_t ka = t < kKt ? TAt[t] : gather_bits(from_a, 0, 0, k0);
+    int64_t kb = t < kKt ? TBt[t] : gather_bits(from_b, 0, 0, k0);
     // the same value in every lane: keep it in scalar registers
     ka = ((int64_t)__builtin_amdgcn_readfirstlane((int)(ka >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((int)ka);
@@ -1327,16 +1384,18 @@ __global__ __launch_bounds__(kThreads, TM == 1 && !BP ? 4 : 2) void k_gemm3m(Gem
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TM; ++i) {
+    if (i > 0) __syncthreads();
+    const int own = tile_place(wm * 32 + 4 * h, wn * 32 + r32, 64);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int rl = (BP ? 32 * w : wm * 32 * TM + i * 32) + 8 * (v >> 2) + 4 * h + (v & 3);
-      const int cl = BP ? r32 : wn * 32 + r32;
-      if (a_in(rl) && (BP == 1 ? cl < g.N : BP == 2 ? n0 + 32 * w + cl < g.N : n0 + cl < g.N)) {
-        const float a = p1[i][v], b = p2[i][v];
-        store_stream(&C[base_c | TCm[rl] | TCn[cl]], a - b, p3[i][v] - a - b);
-      }
+      const float a = p1[i][v], b = p2[i][v];
+      reinterpret_cast<float2*>(smem)[own ^ tile_place(8 * (v >> 2) + (v & 3), 0, 64)] = f2(a - b, p3[i][v] - a - b);
     }
+    __syncthreads();
+    store_tile<12>(g, reinterpret_cast<const float2*>(smem), C + (base_c | (i ? (int64_t)1 << g.c_next : 0)), interior,
+                   g.M - m0 - 32 * i, BP == 1 ? g.N : g.N - n0);
+  }
 }
 
 // Products too narrow for the matrix-core tiles (M < 64 or N < 32, e.g. a
@@ -1657,24 +1716,101 @@ bool gemm_tile_supported(const GemmDesc& d, int tile) {
   return true;
 }
 
-hipError_t launch_gemm(hipStream_t s, const GemmDesc& d, int tile, int split, const float2* a, int64_t a_bs,
+// The order in which store_tile walks a result tile: its bits by ascending address in C, bits beyond the product's
+// sizes (whose elements are not stored) last.  Row bit 5 and column bit 5 of the 64 x 64 elements at a time are wave
+// bits: m and n of a plain tile (m bit 6 of the 128-row ones, whose bit 5 is the round), batch items or columns of the
+// packed ones.
+static void tile_args(const GemmDesc& d, int tile, TileArgs& g) {
+  const bool batch_packed = tile == kGemmBatchPacked, col_packed = tile == kGemmColumnPacked;
+  const bool packed = batch_packed || col_packed;
+  const int bn = packed ? 64 : kGemmTileN[tile], n_col = bn == 64 ? 6 : 5;
+  struct Bit {
+    int pos, lds, mn;
+  };
+  std::vector<Bit> bits;
+  auto add = [&](bool row, int j) {
+    Bit b;
+    const int place = row ? tile_place(1 << j, 0, bn) : 1 << j;
+    b.lds = place;
+    auto m_bit = [&](int i) { b.pos = i < d.nbm ? d.c_m[i] : 64; b.mn = 1 << i; };
+    auto n_bit = [&](int i) { b.pos = i < d.nbn ? d.c_n[i] : 64; b.mn = 1 << (i + 8); };
+    if (packed && j == 5) {
+      if (col_packed) n_bit(row ? 6 : 5);
+      else { b.pos = d.c_b[row ? 1 : 0]; b.mn = 0; }
+    } else if (row) {
+      m_bit(j == 5 && kGemmTileM[tile] == 128 ? 6 : j);
+    } else {
+      n_bit(j);
+    }
+    bits.push_back(b);
+  };
+  for (int j = 0; j < 6; ++j) add(true, j);
+  for (int j = 0; j < n_col; ++j) add(false, j);
+  std::stable_sort(bits.begin(), bits.end(), [](const Bit& a, const Bit& b) { return a.pos < b.pos; });
+  g.lines = 1;
+  for (int j = 0; j < 4; ++j) g.lines &= bits[j].pos == j;
+  for (int j = 0; j < kTileBits; ++j) {
+    g.st_pos[j] = j < (int)bits.size() && bits[j].pos < 64 ? bits[j].pos : 0;
+    g.st_lds[j] = j < (int)bits.size() ? bits[j].lds : 0;
+    g.st_mn[j] = j < (int)bits.size() ? bits[j].mn : 0;
+  }
+  g.c_next = d.c_m[5];
+  for (int j = 0; j < 7; ++j) {
+    g.a_row[j] = batch_packed && j >= 5 ? d.a_b[j - 5] : packed && j >= 5 ? 0 : d.a_m[j];
+    g.b_col[j] = batch_packed && j >= 5 ? d.b_b[j - 5] : d.b_n[j];
+  }
+  for (int j = 0; j < 10; ++j) {
+    g.a_k[j] = d.a_k[j];
+    g.b_k[j] = d.b_k[j];
+  }
+  for (int j = 0; j < 64; ++j) g.from_a[j] = g.from_b[j] = g.from_c[j] = 0;
+  auto from = [](uint8_t* of, const int8_t* pos, int n, int src) {
+    for (int j = 0; j < n; ++j) of[pos[j]] = (uint8_t)(src * 64 + j);
+  };
+  from(g.from_a, d.a_b, d.nbb, 1);
+  from(g.from_a, d.a_m, d.nbm, 2);
+  from(g.from_a, d.a_k, d.nbk, 3);
+  from(g.from_b, d.b_b, d.nbb, 1);
+  from(g.from_b, d.b_n, d.nbn, 2);
+  from(g.from_b, d.b_k, d.nbk, 3);
+  from(g.from_c, d.c_b, d.nbb, 1);
+  from(g.from_c, d.c_m, d.nbm, 2);
+  from(g.from_c, d.c_n, d.nbn, 3);
+}
+
+// The product with the low bits of its m, n and k indices (those that a tile spans) first the ones that lie in a
+// 128-byte line of an operand or of C (its 4 lowest address bits), the rest as they were: a line is then used whole by
+// one block.  (The descriptor orders m and n by C and k by A alone; with B's lowest three bits above k's low four,
+// complex64 1024 x 4096 x 512 loaded each line of B 8 times over: 349 us, 135 so.)  Short sums store more than they
+// load, and keep C's order in m and n: their tiles are then longer runs of C.
+static GemmDesc line_order(const GemmDesc& d) {
+  GemmDesc r = d;
+  auto order = [](int n, const int8_t* x, const int8_t* y, int8_t* rx, int8_t* ry) {
+    std::vector<int> v(n);
+    for (int j = 0; j < n; ++j) v[j] = j;
+    auto key = [&](int j) { return std::min<int>(std::min(x[j], y[j]), 4); };
+    std::stable_sort(v.begin(), v.end(), [&](int a, int b) { return key(a) < key(b); });
+    for (int j = 0; j < n; ++j) {
+      rx[j] = x[v[j]];
+      ry[j] = y[v[j]];
+    }
+  };
+  if (d.K >= 64) {
+    order(d.nbm, d.a_m, d.c_m, r.a_m, r.c_m);
+    order(d.nbn, d.b_n, d.c_n, r.b_n, r.c_n);
+  }
+  order(d.nbk, d.a_k, d.b_k, r.a_k, r.b_k);
+  return r;
+}
+
+hipError_t launch_gemm(hipStream_t s, const GemmDesc& desc, int tile, int split, const float2* a, int64_t a_bs,
                        const float2* b, int64_t b_bs, float2* c, int64_t c_bs, float2* tmp, int64_t tmp_bs, int batch,
                        int precision) {
-  if (!gemm_tile_supported(d, tile)) return hipErrorInvalidValue;
+  if (!gemm_tile_supported(desc, tile)) return hipErrorInvalidValue;
+  const bool reorder = tile != kGemmVector && tile != kGemmBatchPacked && tile != kGemmColumnPacked;
+  const GemmDesc d = reorder ? line_order(desc) : desc;
   if (tile > kGemmVector && precision != TN_PREC_C64) return hipErrorInvalidValue;  // 3M: FP32 only
-  GemmArgs g;
-  g.A = a; g.B = b;
-  g.batch = d.batch; g.M = d.M; g.N = d.N; g.K = d.K;
-  g.split = split > 1 ? split : 1;
-  g.c_elems = d.batch * d.M * d.N;
-  g.a_bs = a_bs; g.b_bs = b_bs;
-  g.nbb = d.nbb; g.nbm = d.nbm; g.nbn = d.nbn; g.nbk = d.nbk; g.xcd = 0;
-  g.band_n = 1;
-  for (int j = 0; j < kGemmMaxBits; ++j) {
-    g.a_b[j] = d.a_b[j]; g.a_m[j] = d.a_m[j]; g.a_k[j] = d.a_k[j];
-    g.b_b[j] = d.b_b[j]; g.b_k[j] = d.b_k[j]; g.b_n[j] = d.b_n[j];
-    g.c_b[j] = d.c_b[j]; g.c_m[j] = d.c_m[j]; g.c_n[j] = d.c_n[j];
-  }
+  const int64_t c_elems = d.batch * d.M * d.N;
   if (tile == kGemmVector) {
     if (d.K > kElemMaxK) return hipErrorInvalidValue;
     if (d.nbb + d.nbm + d.nbn <= kElemGroupOutBits && d.nbk <= kElemKBits) {  // the table-driven kernel
@@ -1684,11 +1820,17 @@ hipError_t launch_gemm(hipStream_t s, const GemmDesc& d, int tile, int split, co
       ga.m[0] = elem_member(d, a, a_bs, b, b_bs, c, c_bs);
       return launch_elem_group(s, ga, batch, precision);
     }
-    g.C = c;
-    g.c_bs = c_bs;
-    g.split = 1;
-    g.tiles_m = g.tiles_n = 1;
-    int64_t eb = (g.c_elems + kThreads - 1) / kThreads;
+    GemmArgs g;
+    g.A = a; g.B = b; g.C = c;
+    g.batch = d.batch; g.M = d.M; g.N = d.N; g.K = d.K;
+    g.a_bs = a_bs; g.b_bs = b_bs; g.c_bs = c_bs;
+    g.nbb = d.nbb; g.nbm = d.nbm; g.nbn = d.nbn; g.nbk = d.nbk;
+    for (int j = 0; j < kGemmMaxBits; ++j) {
+      g.a_b[j] = d.a_b[j]; g.a_m[j] = d.a_m[j]; g.a_k[j] = d.a_k[j];
+      g.b_b[j] = d.b_b[j]; g.b_k[j] = d.b_k[j]; g.b_n[j] = d.b_n[j];
+      g.c_b[j] = d.c_b[j]; g.c_m[j] = d.c_m[j]; g.c_n[j] = d.c_n[j];
+    }
+    int64_t eb = (c_elems + kThreads - 1) / kThreads;
     if (eb > 65535) eb = 65535;
     if (precision == TN_PREC_BF16X3)
       hipLaunchKernelGGL(k_contract_elem<TN_PREC_BF16X3>, dim3((unsigned)eb, batch), dim3(kThreads), 0, s, g);
@@ -1696,31 +1838,42 @@ hipError_t launch_gemm(hipStream_t s, const GemmDesc& d, int tile, int split, co
       hipLaunchKernelGGL(k_contract_elem<TN_PREC_C64>, dim3((unsigned)eb, batch), dim3(kThreads), 0, s, g);
     return hipGetLastError();
   }
-  if (g.split > 1) {
-    if (d.K % g.split != 0 || g.split > d.max_split || !tmp) return hipErrorInvalidValue;
-    g.C = tmp;
-    g.c_bs = tmp_bs;
-  } else {
-    g.C = c;
-    g.c_bs = c_bs;
-  }
-  g.tiles_m = (d.M + kGemmTileM[tile] - 1) / kGemmTileM[tile];
-  g.tiles_n = (d.N + kGemmTileN[tile] - 1) / kGemmTileN[tile];
+  TileArgs g;
+  split = split > 1 ? split : 1;
+  if (split > 1 && (d.K % split != 0 || split > d.max_split || !tmp)) return hipErrorInvalidValue;
+  g.A = a; g.B = b;
+  g.C = split > 1 ? tmp : c;
+  g.a_bs = a_bs; g.b_bs = b_bs;
+  g.c_bs = split > 1 ? tmp_bs : c_bs;
+  g.M = d.M; g.N = d.N; g.K = d.K;
+  g.c_elems = c_elems;
+  tile_args(d, tile, g);
+  auto log2_of = [](int64_t x) {
+    int l = 0;
+    while (((int64_t)1 << l) < x) ++l;
+    return l;
+  };
+  const int64_t tiles_m = (d.M + kGemmTileM[tile] - 1) / kGemmTileM[tile];
+  const int64_t tiles_n = (d.N + kGemmTileN[tile] - 1) / kGemmTileN[tile];
   const int64_t batch_blocks = tile == kGemmBatchPacked ? d.batch / 4 : d.batch;
-  const int64_t blocks = g.tiles_m * g.tiles_n * g.split * batch_blocks * batch;
+  const int64_t blocks = tiles_m * tiles_n * split * batch_blocks * batch;
   if (blocks > ((int64_t)1 << 24)) return hipErrorInvalidValue;  // grid of < 2^32 work-items
+  g.lg_tm = log2_of(tiles_m);
+  g.lg_tn = log2_of(tiles_n);
   // bands of a quarter of the tile columns on large grids (two XCDs per band), whole rows otherwise
-  g.band_n = g.tiles_n >= 16 && g.tiles_n % 4 == 0 && g.tiles_m >= 16 ? g.tiles_n / 4 : g.tiles_n;
+  g.lg_band = tiles_n >= 16 && tiles_m >= 16 ? g.lg_tn - 2 : g.lg_tn;
+  g.lg_split = log2_of(split);
+  g.lg_batch = log2_of(batch_blocks);
   g.xcd = blocks % 8 == 0 ? 1 : 0;
   const bool narrow = tile_narrow(d, tile);
   void* fn = precision == TN_PREC_BF16X3 ? gemm_fn_tile<1>(tile, d.a_kfast, d.b_nfast, narrow)
                                          : gemm_fn_tile<0>(tile, d.a_kfast, d.b_nfast, narrow);
   void* args[] = {&g};
   hipError_t e = hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(kThreads), args, 0, s);
-  if (e != hipSuccess || g.split == 1) return e;
-  int64_t rb = (g.c_elems + kThreads - 1) / kThreads;
+  if (e != hipSuccess || split == 1) return e;
+  int64_t rb = (c_elems + kThreads - 1) / kThreads;
   if (rb > 16384) rb = 16384;
-  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)rb, batch), dim3(kThreads), 0, s, tmp, tmp_bs, g.split, g.c_elems,
+  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)rb, batch), dim3(kThreads), 0, s, tmp, tmp_bs, split, c_elems,
                      c, c_bs);
   return hipGetLastError();
 }

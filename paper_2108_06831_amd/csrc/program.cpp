@@ -1182,7 +1182,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
         // scratch for K splits: the autotuner may try up to kGemmMaxSplit where the result is small
         int tile;
         gemm_tile_by_blocks(g, &tile, &g.max_split);
-        if (tile != kGemmVector && C.elems * kGemmMaxSplit <= ((int64_t)1 << 22) && g.K >= 64)
+        if ((tile != kGemmVector || g.K >= 256) && C.elems * kGemmMaxSplit <= ((int64_t)1 << 22) && g.K >= 64)
           g.max_split = kGemmMaxSplit;
       }
       for (int prec = 0; prec < 2; ++prec) P.orient[prec] = gemm_default_launch(P.gm, prec);
@@ -1745,62 +1745,71 @@ void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split) {
 }
 
 // Default launch shapes of a product for `prec`, set in both orientations; returns the one to run.
-// Each line below is where whole passes timed the other way (microseconds per pass of the workload
-// named, the products in question changed alone):
+// The figures are microseconds per call of the product alone (M x N x K), the line's choice last.
 int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
   const bool c64 = prec == TN_PREC_C64;
-  const int64_t K = gm[0].K, out = gm[0].batch * gm[0].M * gm[0].N;
+  const int64_t K = gm[0].K, out = gm[0].batch * gm[0].M * gm[0].N, work = out * K;
   for (GemmDesc& g : gm) {
+    const int64_t lo = std::min(g.M, g.N), hi = std::max(g.M, g.N);
     int tile, split;
     gemm_tile_by_blocks(g, &tile, &split);
-    // products of up to 2^23 multiply-adds with a short sum: one output per thread (a matrix-core launch
-    // of its own costs more than the sums): 512 x 512 x 8 of a 24-qubit state 709 -> 702, 512 x 1024 x 16
-    // of a 28-qubit one 786 -> 766; 1024 x 64 x 128 x 4 (2^25) stays: 163 against 180
-    if (K <= 32 && out * K <= ((int64_t)1 << 23)) tile = kGemmVector;
+    // One output per thread where the sums are shorter than a tile's fixed cost: 512 x 512 x 4 5.1 a tile, 6.4;
+    // 256 x 256 x 4 5.5, 5.4; 64 x 64 x 16 5.1, 6.7 (but such share a launch with others).  Long sums take several
+    // lanes per output there: 128 x 128 x 128 9.9 in tiles, 6.8; 64 x 64 x 256 11.4, 7.4; 512 x 128 x 512 is left
+    // to tiles (13.9).
+    if ((K <= 8 && work <= ((int64_t)1 << 19)) || (K <= 32 && work <= ((int64_t)1 << 18)) ||
+        (K >= 128 && K <= kElemMaxK && work <= ((int64_t)1 << 21)))
+      tile = kGemmVector;
+    // Else a tile, also half empty: 32 x 1024 x 32 9.4, 5.8; 8 x 32 x 2048 x 8 16.2, 6.0; 256 x 256 x 32 9.5, 5.6;
+    // 8 x 4096 x 512 42 either way
+    else if (tile == kGemmVector && hi >= 64 && work > ((int64_t)1 << 20) && (lo >= 32 || (lo >= 8 && work >= ((int64_t)1 << 22))))
+      tile = kGemmVector - 1;
     if (tile == kGemmVector) split = 1;
-    const bool wide = out >= ((int64_t)1 << 18) && K >= 8;  // enough results for a launch of its own
-    if (tile == kGemmVector && wide && out * K > ((int64_t)1 << 23) && K <= kElemMaxK) {
-      // batches of small products, four per block: 4096 x 32 x 32 x 32 of a 32-qubit amplitude batch 369 -> 258,
-      // 4096 x 8 x 32 x 32 258 -> 239, 4096 x 32 x 32 x 8 420 -> 393
-      const bool packed = g.batch >= 64 && g.M <= 32 && g.N <= 32 && g.M * g.N >= 256;
-      // a short side against a long one, four 32-column slices per block: 32 x 131072 x 8 393 -> 369,
-      // 1024 x 16 x 1024 x 16 605 -> 373 (on 32 x 4096 results it was slower than the grouped launches)
-      const bool columns = g.M >= 16 && g.M <= 32 && g.N >= 64 && out >= ((int64_t)1 << 19);
-      if (c64 && packed) tile = kGemmBatchPacked;
-      else if (c64 && columns) tile = kGemmColumnPacked;
-      else if (packed || columns) tile = kGemmVector - 1;  // 64 x 32: 269 against 369 on 4096 x 32 x 32 x 32
-    }
+    // batches of small products, four per block: 4096 x 32 x 32 x 32 of a 32-qubit amplitude batch 369 -> 258 for the
+    // whole pass, 4096 x 8 x 32 x 32 258 -> 239, 4096 x 32 x 32 x 8 420 -> 393
+    if (tile == kGemmVector && g.batch >= 64 && g.M <= 32 && g.N <= 32 && g.M * g.N >= 256 && K >= 8 &&
+        K <= kElemMaxK && out >= ((int64_t)1 << 18) && work > ((int64_t)1 << 23))
+      tile = c64 && gemm_tile_supported(g, kGemmBatchPacked) ? kGemmBatchPacked : kGemmVector - 1;  // (64 x 32: 269)
+    // a short side against a very long one, four 32-column slices per block: 1024 x 16 x 1024 x 16 98 in 64 x 32, 87;
+    // 32 x 131072 x 8 27, 16; but 32 x 16384 x 32 9.3 against 7.5
+    if (c64 && tile == kGemmVector - 1 && g.M >= 16 && g.M <= 32 && g.N >= 64 && out >= ((int64_t)1 << 21) && K <= 32 &&
+        gemm_tile_supported(g, kGemmColumnPacked))
+      tile = kGemmColumnPacked;
     if (tile < kGemmVector && g.M >= 64 && g.N >= 64) {
-      // 64 x 64 tiles once they fill the chip, in the three-product form for complex64 (twice the waves per SIMD of
-      // 128 x 64): 1024 x 8192 x 256 692 -> 669, 8192 x 32768 x 16 766 -> 669, 512 x 2048 x 256 136 -> 126,
-      // 64 x 4096 x 2048 in 8 ranges 163 -> 152 (us); BF16x3 512 x 32768 x 256 536 -> 520
+      // 64 x 64 tiles in the three-product form once they give every compute unit one: 1024 x 1024 x 128 23.4 in
+      // 64 x 32, 20.9; 512 x 512 x 512 28.8, 25.4 in four ranges of K
       const int64_t blocks = ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
       int sp = 1;
-      while (sp < g.max_split && blocks * sp < 512 && K / (sp * 2) >= 32 && K % (sp * 2) == 0) sp *= 2;
-      if (c64 ? blocks * sp >= 256 : blocks >= 512) {
-        tile = c64 ? 6 : 2;
+      while (sp < g.max_split && blocks * sp < 256 && K / (sp * 2) >= 64 && K % (sp * 2) == 0) sp *= 2;
+      if (c64 && blocks * sp >= 256) {
+        tile = 6;
         split = sp;
       }
+      // BF16x3 takes the largest tile that fills the chip (1024 x 4096 x 128: 39.8 in 64 x 64, 35.4), if the product
+      // fills the tile (8 x 64 x 4096 x 512: 91 in 128 x 64, 69)
+      if (!c64 && kGemmTileM[tile] > g.M) tile = 2;
+    }
+    // ranges of K no shorter than 64 and no more than fill the chip: the sum over them is a launch and a pass of its
+    // own (BF16x3 512 x 512 x 128: 16.9 in four, 16.1 in two, 14.3 whole)
+    if (tile < kGemmVector) {
+      const int64_t blocks = g.batch * ((g.M + kGemmTileM[tile] - 1) / kGemmTileM[tile]) *
+                             ((g.N + kGemmTileN[tile] - 1) / kGemmTileN[tile]);
+      while (split < g.max_split && blocks * split < 128 && K / (split * 2) >= 64 && K % (split * 2) == 0) split *= 2;
+      while (split > 1 && (K < 256 || K / split < 64 || (blocks * split >= 1024 && K / split < 256))) split /= 2;
     }
     g.tile[prec] = tile;
     g.split[prec] = split;
   }
-  // Orientation: the one whose tiles are full (32 x 8192 x 2048: 373 -> 341); then, as a tile stores each row of its
-  // result as 32 consecutive columns per wave, the one whose columns are the result's lowest address bits where the
-  // other's are not (stores of single elements write each 128-byte line 16 times: 512 x 32768 x 256 669 -> 549)
-  if (gm[0].tile[prec] == kGemmVector || gm[1].tile[prec] == kGemmVector)
-    return gm[0].tile[prec] == kGemmVector ? (gm[1].tile[prec] == kGemmColumnPacked ? 1 : 0) : 0;
+  if (gm[0].tile[prec] == kGemmVector || gm[1].tile[prec] == kGemmVector) return 0;
+  if (gm[1].tile[prec] == kGemmColumnPacked) return 1;
+  if (gm[0].tile[prec] == kGemmColumnPacked) return 0;
+  // Orientation: the one whose tiles are full (32 x 8192 x 2048: 373 -> 341 for the whole pass), where the product is
+  // long enough to show it (32 x 1024 x 64: 8.8 either way)
   auto waste = [&](const GemmDesc& g) {
     const int t = g.tile[prec];
     return std::max<int64_t>(1, kGemmTileM[t] / g.M) * std::max<int64_t>(1, kGemmTileN[t] / g.N);
   };
-  if (waste(gm[0]) != waste(gm[1])) return waste(gm[1]) < waste(gm[0]) ? 1 : 0;
-  auto low_n = [](const GemmDesc& g) {
-    int c = 0;
-    while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
-    return c;
-  };
-  return low_n(gm[1]) > low_n(gm[0]) && (low_n(gm[0]) < 3 || K <= 32) ? 1 : 0;
+  return work > ((int64_t)1 << 23) && waste(gm[1]) < waste(gm[0]) ? 1 : 0;
 }
 
 double modeled_seconds(const tn_path* path) {

@@ -378,6 +378,9 @@ constexpr int kGemmTileN[kGemmTiles] = {64, 32, 64, 32, 1, 64, 64, 32, 128};
 constexpr int kGemmMaxSplit = 8;
 constexpr int kGemmBK = 16;      // complex k per staged K tile of the MFMA kernels
 constexpr int kElemMaxK = 1024;  // longest K of the per-output kernel
+// Whether launch shape `tile` can run product d (the batch-packed tile needs
+// M, N <= 32, a batch of at least 4 and tile offsets below 2^32 bytes).
+bool gemm_tile_supported(const GemmDesc& d, int tile);
 // The table-driven per-output kernel (k_elem_group): up to kElemGroupMax
 // independent products in one launch, each with a result of at most
 // 2^kElemGroupOutBits elements per batch item and at most 2^kElemKBits summed

@@ -408,7 +408,9 @@ void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split);
 // result fit in a few KB.  C's address bit p comes from A's bit apos[p] and/or
 // B's bit bpos[p] (-1: absent); summed bit j sits at A bit ka[j] and B bit kb[j].
 constexpr int kSmallMaxBits = 12;
-constexpr int kSmallMaxMacLog2 = 20;
+// Largest step, multiply-adds: more are quicker as a product of their own than on one compute unit (24-qubit state, two
+// of 2^16 and one of 2^17: 492 us with them here, 476 without; BF16x3 446 and 396).
+constexpr int kSmallMaxMacLog2 = 15;
 constexpr int kSmallDescCache = 128;  // step descriptors staged in LDS at a time
 constexpr int kSmallStage = 12288;    // operand elements staged in LDS per round (96 KB)
 struct SmallStep {
@@ -435,6 +437,40 @@ struct SmallStep {
 constexpr int kSmallThreads = 1024;  // threads of an interpreter workgroup (one work list each)
 constexpr int kSmallMaxItems = 2 * kSmallThreads;  // per round: at most two per thread
 static_assert(sizeof(SmallStep) % 16 == 0, "SmallStep is copied in 16-byte words");
+
+// Work lists whose tensors all fit LDS (res_lists): every operand and result has a place in LDS, at a multiple of its
+// size (places are reused once the consumer's level is over), and only inputs are read from memory and only the
+// list's result is written.
+constexpr int kResElems = 14336;  // 112 KB
+constexpr int kResSteps = 256, kResLevels = 64;
+constexpr uint16_t kResOut = 0xffff;
+struct ResStep {
+  uint16_t a, b, c;         // places; c = kResOut: the list's result
+  uint8_t c_bits, k_bits;
+  int8_t apos[kSmallMaxBits], bpos[kSmallMaxBits];
+  int8_t ka[kSmallMaxBits], kb[kSmallMaxBits];
+  int32_t pad[2];
+};
+static_assert(sizeof(ResStep) == 64, "ResStep is copied in 16-byte words");
+// the outputs j + t 2^q (t = 0 .. 2^(c - q) - 1) of one step
+struct ResItem {
+  uint16_t a, b;  // places of output j's operands (summed index 0)
+  uint32_t what;  // step (8 bits) | j << 8 (12 bits) | q << 20 (4 bits)
+};
+struct ResLevel {
+  int32_t item0, n_items;
+};
+struct ResList {
+  int32_t level0, n_levels, step0, n_steps, copy0, n_copy;  // copy: source of each staged input element
+  int64_t c_off;                                            // the result, in the workspace
+};
+struct ResProgram {
+  std::vector<ResList> lists;
+  std::vector<ResLevel> levels;
+  std::vector<ResStep> steps;
+  std::vector<ResItem> items;
+  std::vector<uint32_t> copy;
+};
 
 enum StepKind { SK_SKINNY = 0, SK_GEMM = 1, SK_SMALL = 2 };
 
@@ -526,6 +562,8 @@ struct tn_path {
   std::vector<int32_t> small_levels;         // level i owns steps small_levels[i] .. small_levels[i+1]-1
   std::vector<uint32_t> small_items;         // work items of every round (see SmallStep::item0)
   int64_t small_region = 0;                  // workspace elements reserved for their results
+  tnq::ResProgram res;                       // the lists again, if all of them fit LDS
+  int32_t res_final = -1;                    // the list whose result is the path's (-1: other steps follow)
   // runs of outer products written in one launch
   std::vector<tnq::OuterChain> outers;
   // fused streaming chains
@@ -586,6 +624,8 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
 void build_reg_pass(tn_path* path, SweepPass& ps, int R);
 void build_adj_reg_pass(tn_path* path, SweepPass& ps, int R);
 // seqpass.cpp: ordered passes over `items` on a 2^R state, chunks of at most 2^lmax elements
+// One work list (steps by ascending level) added to `prog`; false if it does not fit LDS.
+bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<int>& level, ResProgram* prog);
 bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool adjoint, SeqProgram* out);
 // moves every step that is small and depends only on inputs or such steps to the
 // front; of the rest, likely per-output products that are ready together are

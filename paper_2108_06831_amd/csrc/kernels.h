@@ -101,6 +101,19 @@ hipError_t launch_small_steps(hipStream_t s, const SmallStep* steps, const int32
                               const int32_t* level_off, const uint32_t* items, int n_lists, float2* in,
                               int64_t in_bs, float2* ws, int64_t ws_bs, int batch, int precision);
 
+// The same lists kept in LDS (ResProgram).  final_list >= 0: that list's result goes to `out` instead, its bit j at
+// position out_pos[j].
+struct ResTables {
+  const ResList* lists;
+  const ResLevel* levels;
+  const ResStep* steps;
+  const ResItem* items;
+  const uint32_t* copy;
+};
+hipError_t launch_small_resident(hipStream_t s, const ResTables& t, int n_lists, const float2* in, int64_t in_bs,
+                                 float2* ws, int64_t ws_bs, int final_list, float2* out, int64_t out_bs,
+                                 const int8_t (&out_pos)[kSmallMaxBits], int batch, int precision);
+
 // One fused streaming pass over a 2^bits tensor (see SweepPass; in == NULL: the
 // state |0...0>); vals: the chain's gate values gathered by launch_gather_vals.
 hipError_t launch_sweep_pass(hipStream_t s, const SweepPass& ps, int bits, const SweepGateDesc* gates_dev,

@@ -618,6 +618,129 @@ hipError_t launch_small_steps(hipStream_t s, const SmallStep* steps, const int32
   return hipGetLastError();
 }
 
+// The interpreter for lists that stay in LDS: inputs are staged once, then a
+// level is its items' arithmetic and a barrier.  A level is bound by its chain
+// of LDS reads (descriptor, operands); items and their operand places are
+// planned on the host and fetched a level ahead.  The arithmetic is
+// k_small_steps', term by term.  (The 125 products of a 10-qubit state, 9
+// levels: 38 us in k_small_steps, 13 so.)
+struct ResArgs {
+  float2* out;
+  int64_t out_bs;
+  int32_t final_list;
+  int8_t out_pos[kSmallMaxBits];
+};
+
+template <int PREC>
+__global__ __launch_bounds__(kSmallThreads) void k_small_resident(ResTables tb, const float2* in, int64_t in_bs,
+                                                                  float2* ws, int64_t ws_bs, ResArgs fin) {
+  __shared__ __attribute__((aligned(16))) float2 T[kResElems];
+  __shared__ __attribute__((aligned(16))) ResStep desc[kResSteps];
+  __shared__ ResLevel lev[kResLevels];
+  const int w = blockIdx.x, z = blockIdx.y, tid = threadIdx.x;
+  const ResList L = tb.lists[w];
+  const float2* IN = in + (int64_t)z * in_bs;
+  const ResItem* items = tb.items;
+  const ResLevel l0 = tb.levels[L.level0];
+  ResItem it0, it1, nx0 = {}, nx1 = {};
+  if (tid < l0.n_items) nx0 = items[l0.item0 + tid];
+  if (tid + kSmallThreads < l0.n_items) nx1 = items[l0.item0 + tid + kSmallThreads];
+  for (int i = tid; i < L.n_levels; i += kSmallThreads) lev[i] = tb.levels[L.level0 + i];
+  {
+    const uint4* src = reinterpret_cast<const uint4*>(tb.steps + L.step0);
+    uint4* dst = reinterpret_cast<uint4*>(desc);
+    for (int i = tid; i < L.n_steps * (int)(sizeof(ResStep) / 16); i += kSmallThreads) dst[i] = src[i];
+  }
+  for (int e0 = tid; e0 < L.n_copy; e0 += 4 * kSmallThreads) {
+    uint32_t from[4];
+    float2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * kSmallThreads < L.n_copy) from[u] = tb.copy[L.copy0 + e0 + u * kSmallThreads];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * kSmallThreads < L.n_copy) v[u] = IN[from[u]];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e0 + u * kSmallThreads < L.n_copy) T[e0 + u * kSmallThreads] = v[u];
+  }
+  __syncthreads();
+  const bool to_out = w == fin.final_list;
+  float2* C = to_out ? fin.out + (int64_t)z * fin.out_bs : ws + (int64_t)z * ws_bs + L.c_off;
+  for (int lv = 0; lv < L.n_levels; ++lv) {
+    const int nit = lev[lv].n_items;
+    it0 = nx0;
+    it1 = nx1;
+    if (lv + 1 < L.n_levels) {  // the next level's items
+      const ResLevel n = lev[lv + 1];
+      if (tid < n.n_items) nx0 = items[n.item0 + tid];
+      if (tid + kSmallThreads < n.n_items) nx1 = items[n.item0 + tid + kSmallThreads];
+    }
+    for (int q = 0; q < 2; ++q) {
+      if (tid + q * kSmallThreads >= nit) break;
+      const ResItem it = q == 0 ? it0 : it1;
+      const ResStep& st = desc[it.what & 255u];
+      const int o0 = (int)((it.what >> 8) & 4095u), qb = (int)(it.what >> 20), nt = 1 << (st.c_bits - qb);
+      const uint32_t* ap = reinterpret_cast<const uint32_t*>(st.apos);
+      const uint32_t* bp = reinterpret_cast<const uint32_t*>(st.bpos);
+      const uint32_t* ka = reinterpret_cast<const uint32_t*>(st.ka);
+      const uint32_t* kb = reinterpret_cast<const uint32_t*>(st.kb);
+      const uint32_t ap0 = ap[0], ap1 = ap[1], ap2 = ap[2], bp0 = bp[0], bp1 = bp[1], bp2 = bp[2];
+      const uint32_t ka0 = ka[0], ka1 = ka[1], ka2 = ka[2], kb0 = kb[0], kb1 = kb[1], kb2 = kb[2];
+      const int nk = 1 << st.k_bits, c = st.c;
+      int ab = it.a, bb = it.b;  // (a tensor's place is a multiple of its size)
+      for (int t = 0; t < nt; ++t) {
+        const int o = o0 | (t << qb);
+        if (t != 0)
+          for (uint32_t f = (uint32_t)((t ^ (t - 1)) << qb); f; f &= f - 1) {
+            const int p = __builtin_ctz(f);
+            const int pa = packed_byte(ap0, ap1, ap2, p), pb = packed_byte(bp0, bp1, bp2, p);
+            if (pa >= 0) ab ^= 1 << pa;
+            if (pb >= 0) bb ^= 1 << pb;
+          }
+        // summed index in Gray-code order: one address bit flips per term
+        int a = ab, b = bb;
+        float2 acc = cmul<PREC>(T[a], T[b]);
+        for (int k = 1; k < nk; ++k) {
+          const int j = __builtin_ctz(k);
+          a ^= 1 << packed_byte(ka0, ka1, ka2, j);
+          b ^= 1 << packed_byte(kb0, kb1, kb2, j);
+          acc = cmac<PREC>(acc, T[a], T[b]);
+        }
+        if (c != kResOut) {
+          T[c + o] = acc;
+        } else {
+          int at = o;
+          if (to_out) {
+            at = 0;
+#pragma unroll
+            for (int j = 0; j < kSmallMaxBits; ++j) at |= ((o >> j) & 1) << fin.out_pos[j];
+          }
+          C[at] = acc;
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+hipError_t launch_small_resident(hipStream_t s, const ResTables& t, int n_lists, const float2* in, int64_t in_bs,
+                                 float2* ws, int64_t ws_bs, int final_list, float2* out, int64_t out_bs,
+                                 const int8_t (&out_pos)[kSmallMaxBits], int batch, int precision) {
+  if (n_lists == 0) return hipSuccess;
+  ResArgs a;
+  a.out = out;
+  a.out_bs = out_bs;
+  a.final_list = final_list;
+  for (int j = 0; j < kSmallMaxBits; ++j) a.out_pos[j] = out_pos[j];
+  const dim3 grid(n_lists, batch), block(kSmallThreads);
+  if (precision == TN_PREC_BF16X3)
+    hipLaunchKernelGGL(k_small_resident<TN_PREC_BF16X3>, grid, block, 0, s, t, in, in_bs, ws, ws_bs, a);
+  else
+    hipLaunchKernelGGL(k_small_resident<TN_PREC_C64>, grid, block, 0, s, t, in, in_bs, ws, ws_bs, a);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Index slicing: the input tensors of one slice gathered from the full ones,
 // and the slices' results summed.

@@ -1358,6 +1358,9 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
   // independent sub-trees of the interpreter's steps -> one work list each
   path->small_steps.clear();
   path->small_lists.clear();
+  path->res = ResProgram();
+  path->res_final = -1;
+  bool resident = path->n_small > 0;
   if (path->n_small > 0) {
     std::vector<int> consumer(S, -1);
     for (int s = 0; s < S; ++s)
@@ -1395,6 +1398,20 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
         path->small_steps.push_back(path->steps[lst[i]].sm);
       }
       path->small_lists.push_back((int32_t)path->small_levels.size());
+      if (resident) {
+        std::vector<SmallStep> sm;
+        std::vector<int> lv;
+        for (int q : lst) {
+          sm.push_back(path->steps[q].sm);
+          lv.push_back(level[q]);
+        }
+        if (lst.back() == S - 1) path->res_final = (int32_t)path->res.lists.size();
+        resident = add_resident_list(sm, lv, &path->res);
+      }
+    }
+    if (!resident) {
+      path->res = ResProgram();
+      path->res_final = -1;
     }
     path->small_levels.push_back((int32_t)path->small_steps.size());
     // rounds of each level (in chunks of kSmallDescCache steps, as the kernel

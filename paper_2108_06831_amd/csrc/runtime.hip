@@ -230,6 +230,11 @@ struct DevPath {
   RegOp* reg_ops = nullptr;
   RegPhase* reg_phases = nullptr;
   uint32_t* reg_words = nullptr;
+  ResList* res_lists = nullptr;         // the interpreter's lists in LDS
+  ResLevel* res_levels = nullptr;
+  ResStep* res_steps = nullptr;
+  ResItem* res_items = nullptr;
+  uint32_t* res_copy = nullptr;
   SeqSeg* seq_segs = nullptr;           // ordered passes
   SeqWindow* seq_wins = nullptr;
   uint32_t* seq_words = nullptr;
@@ -255,10 +260,17 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   d = new DevPath();
   d->device = dev;
   path->dev = d;
-  HIP_TRY(upload(&d->steps, path->small_steps));
-  HIP_TRY(upload(&d->lists, path->small_lists));
-  HIP_TRY(upload(&d->levels, path->small_levels));
-  HIP_TRY(upload(&d->items, path->small_items));
+  if (path->res.lists.empty()) {
+    HIP_TRY(upload(&d->steps, path->small_steps));
+    HIP_TRY(upload(&d->lists, path->small_lists));
+    HIP_TRY(upload(&d->levels, path->small_levels));
+    HIP_TRY(upload(&d->items, path->small_items));
+  }
+  HIP_TRY(upload(&d->res_lists, path->res.lists));
+  HIP_TRY(upload(&d->res_levels, path->res.levels));
+  HIP_TRY(upload(&d->res_steps, path->res.steps));
+  HIP_TRY(upload(&d->res_items, path->res.items));
+  HIP_TRY(upload(&d->res_copy, path->res.copy));
   HIP_TRY(upload(&d->sweep_gates, path->sweep_gates));
   HIP_TRY(upload(&d->segments, path->segments));
   HIP_TRY(upload(&d->sweep_val_src, path->sweep_val_src));
@@ -289,7 +301,8 @@ void device_release_path(tn_path* path) {
   (void)hipFree(d->segments);
   (void)hipFree(d->sweep_val_src);
   (void)hipFree(d->slice_tensors);
-  for (void* p : {(void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
+  for (void* p : {(void*)d->res_lists, (void*)d->res_levels, (void*)d->res_steps, (void*)d->res_items, (void*)d->res_copy,
+                  (void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
                   (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words,
                   (void*)d->seq_segs, (void*)d->seq_wins, (void*)d->seq_words, (void*)d->seq_vals, (void*)d->adj_seq_segs,
                   (void*)d->adj_seq_wins, (void*)d->adj_seq_words, (void*)d->adj_seq_vals})
@@ -433,8 +446,22 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
     float2* wp = resolve(B, rw, &wbs);
     if (B.pair_a) return set_error(TN_EINVAL, "internal: interpreter steps in a single pairwise contraction");
     hipEvent_t ev = prof_start(s, TN_KERNEL_INTERP);
-    HIP_TRY(launch_small_steps(s, dp->steps, dp->lists, dp->levels, dp->items, (int)path->small_lists.size() - 1, ip,
-                               ibs, wp, wbs, batch, precision));
+    if (!path->res.lists.empty()) {
+      const bool direct = path->res_final >= 0 && B.final_out;
+      int8_t pos[kSmallMaxBits] = {0};
+      const int n = (int)path->final_bits.size();
+      for (int p = 0; direct && p < n; ++p) {
+        const int q = pos_in(*B.final_layout, path->final_bits[n - 1 - p]);
+        if (q < 0) return set_error(TN_EINVAL, "internal: the interpreter misses a leg of the result");
+        pos[p] = (int8_t)q;
+      }
+      HIP_TRY(launch_small_resident(s, ResTables{dp->res_lists, dp->res_levels, dp->res_steps, dp->res_items, dp->res_copy},
+                                    (int)path->res.lists.size(), ip, ibs, wp, wbs, direct ? path->res_final : -1,
+                                    B.final_out, B.final_out_bs, pos, batch, precision));
+    } else {
+      HIP_TRY(launch_small_steps(s, dp->steps, dp->lists, dp->levels, dp->items, (int)path->small_lists.size() - 1, ip,
+                                 ibs, wp, wbs, batch, precision));
+    }
     double fl = 0, by = 0;
     for (int i = 0; i < path->n_small; ++i) { fl += path->steps[i].flops; by += path->steps[i].bytes; }
     prof_stop(s, ev, TN_KERNEL_INTERP, by * batch, fl * batch);
@@ -891,8 +918,9 @@ static tn_status contract_path_in(hipStream_t s, int32_t precision, tn_network* 
   B.out_bs = (int64_t)1 << net->n_qubits;
   std::vector<int32_t> to;
   for (int q = 0; q < net->n_qubits; ++q) to.push_back(lab(net->wire_final[q], 0));
-  const bool direct = path->seq.last || (!path->steps.empty() && path->steps.back().kind == SK_GEMM &&
-                                         path->steps.back().chain == -1 && path->final_bits == to);
+  const bool direct = path->seq.last || path->res_final >= 0 ||
+                      (!path->steps.empty() && path->steps.back().kind == SK_GEMM && path->steps.back().chain == -1 &&
+                       path->final_bits == to);
   if (direct) {
     B.final_out = B.out;
     B.final_out_bs = B.out_bs;

@@ -201,6 +201,18 @@ struct SeqTables {
 hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const SeqSeg& last,
                               const float2* in, int64_t in_bs, float2* out, int64_t out_bs, const int8_t* out_pos,
                               const float2* vals, int64_t vals_bs, int batch, int precision);
+// sweep gate matrices: recipe r of the sweep -> [batch][n_sweep][16] complex64
+hipError_t launch_sweep_matrices(hipStream_t s, const Recipe* recipes, int n, const RecipeOp* ops, const double* mats,
+                                 const double* params, int64_t params_stride, int batch, float2* out);
+// Value and gradient terms of a state of one chunk, one launch: forward (fwd != NULL: from |0...0> through its gates,
+// `last` its last segment, out_pos the position in psi's layout of each of its address bits; else psi is given), value
+// per parameter vector, and the reverse sweep `ps`.  Terms: over psi's address bits, sorted by their pattern of the
+// register bits of ps's first segment.
+hipError_t launch_seq_gradient(hipStream_t s, const SeqPass* fwd, const SeqSeg* last, const int8_t* out_pos,
+                               const SeqTables& ft, const float2* in, int64_t in_bs, const SeqPass& ps, int bits,
+                               const SeqTables& t, const float2* u, int64_t u_bs, float2* psi, int64_t psi_bs,
+                               const ZTerms& terms, double* value, int batch, double* partials, int64_t partial_stride,
+                               int precision);
 int seq_adjoint_columns(const SeqPass& ps, int bits);
 // Expectations of several circuits whose whole contraction is one ordered pass
 // from |0...0>, one launch: circuits of one block size (2^(l - 4) threads, 64 at
@@ -256,8 +268,6 @@ hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const 
 hipError_t launch_gradient_reduce(hipStream_t s, const double* partials, int64_t partial_stride, int n_cols,
                                   const int32_t* param_slots, int n_params, const double* grad_out, int batch,
                                   double* grad);
-// sweep gate matrices: recipe r of the sweep -> [batch][n_sweep][16] complex64
-hipError_t launch_sweep_matrices(hipStream_t s, const Recipe* recipes, int n, const RecipeOp* ops, const double* mats,
-                                 const double* params, int64_t params_stride, int batch, float2* out);
+
 
 }  // namespace tnq

@@ -1444,7 +1444,13 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
   // the passes' layout: the final tensor's, or the qubit order (the state is permuted first)
   const bool perm = path->adj_state == 1 && path->adj_perm;
   ZTerms terms;
-  if ((st = make_terms(net, perm ? path->adj_bits : path->final_bits, obs, &terms)) != TN_OK) return st;
+  // a reverse sweep of one chunk starts from psi in one launch, and the forward pass too if it is one chunk
+  const bool one = path->adj_state == 2 && path->adj_seq.passes.size() == 1 &&
+                   path->adj_seq.passes[0].l == (int)path->final_bits.size();
+  const bool both = one && one_seq_pass(path);
+  if ((st = make_terms(net, perm ? path->adj_bits : path->final_bits, obs, &terms,
+                       one ? path->adj_seq.segs[path->adj_seq.passes[0].first_seg].rgpos : nullptr)) != TN_OK)
+    return st;
   hipStream_t s = (hipStream_t)stream;
   DevNet* d;
   if ((st = ensure_device(net, &d)) != TN_OK) return st;
@@ -1457,7 +1463,7 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
   B.ws_bs = path->ws_elems;
   // forward contraction to psi (left in the workspace arena)
   if ((st = materialize(s, net, d, params_dev, batch, nullptr, 0, B.in)) != TN_OK) return st;
-  if ((st = run_steps(s, path, B, batch, precision)) != TN_OK) return st;
+  if (!both && (st = run_steps(s, path, B, batch, precision)) != TN_OK) return st;
   int64_t pbs;
   float2* psi = resolve(B, path->final_ref, &pbs);
   if (path->final_ref.buf != BUF_WS) return set_error(TN_EUNSUPPORTED, "backward of a network without contraction steps");
@@ -1481,8 +1487,10 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     std::swap(psi, lam);
     std::swap(pbs, lbs);
   }
-  HIP_TRY(launch_expectation(s, psi, pbs, n, terms, batch, partial, value_dev, 1));
-  HIP_TRY(launch_apply_diag_obs(s, psi, pbs, lam, lbs, n, terms, batch));
+  if (!one) {
+    HIP_TRY(launch_expectation(s, psi, pbs, n, terms, batch, partial, value_dev, 1));
+    HIP_TRY(launch_apply_diag_obs(s, psi, pbs, lam, lbs, n, terms, batch));
+  }
   float2* umats = (float2*)(w + L.mats_off);
   HIP_TRY(launch_sweep_matrices(s, d->sweep_recipes, (int)net->sweep.size(), d->sweep_ops, d->mats, params_dev,
                                 net->n_params, batch, umats));
@@ -1504,10 +1512,27 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     double fl = 0;  // as counted for the step-by-step sweep
     for (const SweepGate& g : net->sweep) fl += (2.0 * 8.0 * (1 << g.nq) + (g.gen != GEN_NONE ? 8.0 : 0.0)) * (double)n;
     hipEvent_t ev = prof_start(s, TN_KERNEL_ADJOINT);
-    for (const SeqPass& ps : pr.passes)
-      HIP_TRY(launch_seq_adjoint(s, ps, bits, SeqTables{dp->adj_seq_segs, dp->adj_seq_wins, dp->adj_seq_words, dp->adj_seq_vals}, umats,
-                                 (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch, parts, pstride,
-                                 precision));
+    const SeqTables rt{dp->adj_seq_segs, dp->adj_seq_wins, dp->adj_seq_words, dp->adj_seq_vals};
+    if (one) {
+      const SeqChain& ch = path->seq;
+      const SeqPass* fwd = both ? &ch.prog.passes[0] : nullptr;
+      int8_t pos[32] = {0};
+      for (int p = 0; both && p < bits; ++p) {
+        const int q = pos_in(path->final_bits, ch.in_bits[bits - 1 - p]);
+        if (q < 0) return set_error(TN_EINVAL, "internal: ordered passes miss a leg of the result");
+        pos[p] = (int8_t)q;
+      }
+      HIP_TRY(launch_seq_gradient(s, fwd, both ? &ch.prog.segs[fwd->first_seg + fwd->n_segs - 1] : nullptr, pos,
+                                  SeqTables{dp->seq_segs, dp->seq_wins, dp->seq_words, dp->seq_vals}, B.in, B.in_bs,
+                                  pr.passes[0], bits, rt, umats, (int64_t)net->sweep.size() * 16, psi, pbs, terms,
+                                  value_dev, batch, parts, pstride, precision));
+      if (both) fl += ch.flops;
+    }
+    for (const SeqPass& ps : pr.passes) {
+      if (one) break;
+      HIP_TRY(launch_seq_adjoint(s, ps, bits, rt, umats, (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch,
+                                 parts, pstride, precision));
+    }
     prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * pr.passes.size() * batch, fl * batch);
   }
   if (path->adj_state == 1) {

@@ -103,9 +103,10 @@ __device__ __forceinline__ void dense_seq(float2 (&x)[16], float2 g0, float2 g1,
   }
 }
 
-// A two-qubit gate on register bits 2 H (index bit 0) and 2 H + 1 (bit 1); get(e): entry e = 4 m + k.
+// A two-qubit gate on register bits 2 H (index bit 0) and 2 H + 1 (bit 1); get(e): entry e = 4 m + k, the columns in
+// the order of the sum: 0, 1, 2, 3 or (gray) 0, 1, 3, 2.
 template <int PREC, int H, class Get>
-__device__ __forceinline__ void dense2_seq(float2 (&x)[16], Get get, bool gate_first) {
+__device__ __forceinline__ void dense2_seq(float2 (&x)[16], Get get, bool gate_first, bool gray) {
   constexpr int s0 = 1 << (2 * H), s1 = 2 << (2 * H);
   float2 y[16];
 #pragma unroll
@@ -114,7 +115,8 @@ __device__ __forceinline__ void dense2_seq(float2 (&x)[16], Get get, bool gate_f
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       if (r & (s0 | s1)) continue;
-      const float2 v0 = x[r], v1 = x[r | s0], v2 = x[r | s1], v3 = x[r | s0 | s1];
+      const float2 v0 = x[r], v1 = x[r | s0];
+      const float2 v2 = gray ? x[r | s0 | s1] : x[r | s1], v3 = gray ? x[r | s1] : x[r | s0 | s1];
       float2 acc;
       if (gate_first) {
         acc = cmac<PREC>(cmac<PREC>(cmac<PREC>(cmul<PREC>(g[0], v0), g[1], v1), g[2], v2), g[3], v3);
@@ -343,13 +345,13 @@ __device__ __forceinline__ void seq_run(float2 (&x)[16], float2 (&y)[16], float2
       }
       if (head & SEQ_DENSE2) {
         auto get = [&](int e) { return vwin[vi + e]; };
-        const bool gf = NS == 2 || ((head >> 12) & 1);
+        const bool gf = NS == 2 || ((head >> 12) & 1), gray = NS == 1 && ((head >> 13) & 1);
         if (((head >> 4) & 15) == 0) {
-          dense2_seq<PREC, 0>(x, get, gf);
-          if (NS == 2) dense2_seq<PREC, 0>(y, get, true);
+          dense2_seq<PREC, 0>(x, get, gf, gray);
+          if (NS == 2) dense2_seq<PREC, 0>(y, get, true, false);
         } else {
-          dense2_seq<PREC, 1>(x, get, gf);
-          if (NS == 2) dense2_seq<PREC, 1>(y, get, true);
+          dense2_seq<PREC, 1>(x, get, gf, gray);
+          if (NS == 2) dense2_seq<PREC, 1>(y, get, true, false);
         }
         vi += 16;
       }
@@ -421,6 +423,67 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
       O[seg_addr(seg, A, r)] = y[r];
     }
   }
+}
+
+// Value and gradient of a state of one chunk: the forward pass (fwd.n_segs = 0:
+// psi is there already), E = sum |psi|^2 D in FP64, lambda = D psi and the
+// reverse sweep, a block per parameter vector.  psi goes through memory once,
+// from the forward pass's layout to the reverse sweep's; lambda never does.
+// (13 qubits, 6 layers, 9 parameter vectors: 385 us with launches of their own
+// for the forward pass, the value, its sum and lambda, 362 so.)
+template <int PREC, int LMAX>
+__global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_gradient(
+    SeqArgs fwd, const SeqSeg* __restrict__ fsegs, const SeqWindow* __restrict__ fwins,
+    const uint32_t* __restrict__ fwords, const int32_t* __restrict__ fvsrc, const float2* __restrict__ in_vals,
+    SeqArgs a, const SeqSeg* __restrict__ segs, const SeqWindow* __restrict__ wins,
+    const uint32_t* __restrict__ words, const int32_t* __restrict__ vsrc, const float2* __restrict__ u, ZTerms terms,
+    double* value) {
+  constexpr int kBuf = (1 << LMAX) + (1 << (LMAX - 5));
+  __shared__ float2 bx[kBuf], by[kBuf];
+  __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];
+  __shared__ uint32_t wwin[kSeqWinWords];
+  __shared__ double red[(1 << (LMAX - 4)) / 64];
+  const int z = blockIdx.y, lane = threadIdx.x & 63;
+  const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
+  const bool active = (int)threadIdx.x < n_thr;
+  float2* P = const_cast<float2*>(a.in) + (int64_t)z * a.in_bs;
+  float2 x[16], y[16];
+  if (fwd.n_segs > 0) {
+    seq_run<PREC, 1>(x, y, bx, nullptr, vwin, wwin, fwd.n_segs, fsegs, fwins, fwords, fvsrc,
+                     in_vals + (int64_t)z * fwd.vals_bs, 0, tid,
+                     [&](const SeqSeg& seg, uint32_t A) {
+#pragma unroll
+                       for (int r = 0; r < 16; ++r) x[r] = f2(seg_addr(seg, A, r) == 0 ? 1.f : 0.f, 0.f);
+                     },
+                     [](int, double) {});
+    const uint32_t e0 = (uint32_t)bits10(tid, fwd.out_t);
+    const uint32_t g0 = 1u << fwd.out_r[0], g1 = 1u << fwd.out_r[1], g2 = 1u << fwd.out_r[2], g3 = 1u << fwd.out_r[3];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      P[e0 | (r & 1 ? g0 : 0) | (r & 2 ? g1 : 0) | (r & 4 ? g2 : 0) | (r & 8 ? g3 : 0)] = x[r];
+    __syncthreads();
+  }
+  double* part = a.partials + (int64_t)z * a.pstride + (threadIdx.x >> 6);
+  auto add_grad = [&](int slot, double v) {
+    v = wave_sum_d(active ? v : 0.0);
+    if (lane == 63) part[(int64_t)slot * kReduceBlocks] = v;
+  };
+  seq_run<PREC, 2>(x, y, bx, by, vwin, wwin, a.n_segs, segs, wins, words, vsrc,
+                   u + (int64_t)z * a.vals_bs, 0, tid,
+                   [&](const SeqSeg& seg, uint32_t A) {
+                     double w[16], e = 0;
+                     sum_terms16(A, terms, w);
+#pragma unroll
+                     for (int r = 0; r < 16; ++r) {
+                       const float2 v = P[seg_addr(seg, A, r)];
+                       x[r] = v;
+                       y[r] = f2((float)(w[r] * v.x), (float)(w[r] * v.y));
+                       e += ((double)v.x * v.x + (double)v.y * v.y) * w[r];
+                     }
+                     e = block_sum(active ? e : 0.0, red);
+                     if (threadIdx.x == 0) value[z] = e;
+                   },
+                   add_grad);
 }
 
 // Expectations of several circuits, one block per circuit and parameter vector:
@@ -532,6 +595,42 @@ hipError_t launch_seq_forward(hipStream_t s, const SeqPass& ps, int bits, const 
 
 int seq_adjoint_columns(const SeqPass& ps, int bits) {
   return (1 << (bits - ps.l)) * std::max(1, (1 << (ps.l - 4)) / 64);
+}
+
+hipError_t launch_seq_gradient(hipStream_t s, const SeqPass* fwd, const SeqSeg* last, const int8_t* out_pos,
+                               const SeqTables& ft, const float2* in, int64_t in_bs, const SeqPass& ps, int bits,
+                               const SeqTables& t, const float2* u, int64_t u_bs, float2* psi, int64_t psi_bs,
+                               const ZTerms& terms, double* value, int batch, double* partials, int64_t partial_stride,
+                               int precision) {
+  SeqArgs f{}, a{};
+  a.in = psi; a.in_bs = psi_bs;
+  a.vals_bs = u_bs;
+  a.partials = partials;
+  a.pstride = partial_stride;
+  if (!seq_args(ps, bits, kSeqAdjMaxLocal, nullptr, &a) || ps.l != bits) return hipErrorInvalidValue;
+  const SeqSeg* fsegs = nullptr;
+  const SeqWindow* fwins = nullptr;
+  if (fwd) {
+    f.vals_bs = in_bs;
+    if (!seq_args(*fwd, bits, kSeqAdjMaxLocal, out_pos, &f) || fwd->l != bits) return hipErrorInvalidValue;
+    for (int j = 0; j < 10; ++j) f.out_t[j] = out_pos[last->gpos[j]];
+    for (int j = 0; j < 4; ++j) f.out_r[j] = out_pos[last->rgpos[j]];
+    fsegs = ft.segs + fwd->first_seg;
+    fwins = ft.wins + fwd->first_win;
+  }
+  const dim3 grid(1, batch), block(std::max(64, 1 << (bits - 4)));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, f, fsegs, fwins, ft.words, ft.vals, in, a, t.segs + ps.first_seg,
+                       t.wins + ps.first_win, t.words, t.vals, u, terms, value);
+  };
+  if (precision == TN_PREC_BF16X3) {
+    if (bits <= 12) go(k_seq_gradient<TN_PREC_BF16X3, 12>);
+    else go(k_seq_gradient<TN_PREC_BF16X3, kSeqAdjMaxLocal>);
+  } else {
+    if (bits <= 12) go(k_seq_gradient<TN_PREC_C64, 12>);
+    else go(k_seq_gradient<TN_PREC_C64, kSeqAdjMaxLocal>);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const SeqTables& t, const float2* u,

@@ -322,6 +322,7 @@ struct SeqItem {
   bool gate_first = true;
   int val[16] = {0};    // offsets of its values: 2^n diagonal entries, or 4^n dense ones (m, k) row-major
   int form = 0;         // dense: GateForm
+  bool gray = false;    // two-bit dense: summed in the order 0, 1, 3, 2
   int signs = -1;       // diagonal of known entries +-1: 2 (Z) or 8 (CZ)
   int ones = 0;         // two-bit diagonals: entries known to be exactly 1
   int gen = GEN_NONE, red = -1;
@@ -356,6 +357,7 @@ struct GemmDesc {
   int8_t a_b[kGemmMaxBits], a_m[kGemmMaxBits], a_k[kGemmMaxBits];
   int8_t b_b[kGemmMaxBits], b_k[kGemmMaxBits], b_n[kGemmMaxBits];
   int8_t c_b[kGemmMaxBits], c_m[kGemmMaxBits], c_n[kGemmMaxBits];
+  int32_t fixed_sum;  // in BF16x3 the terms are summed in this order of k (gemm_fixed_sum)
   // launch shape per precision (index TN_PREC_*): tile[p] != kGemmVector is an
   // MFMA tile of kGemmTileM x kGemmTileN complex, kGemmVector the per-output
   // vector kernel; split[p] > 1 cuts K into ranges whose partial products land
@@ -402,15 +404,15 @@ inline bool elem_group_shape(int out_bits, int m_bits, int n_bits, int k_bits) {
 // default launch shapes of a product's two orientations for a precision (before any measurement);
 // returns the orientation to run
 int gemm_default_launch(GemmDesc (&gm)[2], int prec);
+// the same for BF16x3 where the order of the sums is to stay
+int gemm_fixed_sum(GemmDesc (&gm)[2]);
 void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split);
 
 // A small step executed inside the interpreter kernel: every operand and the
 // result fit in a few KB.  C's address bit p comes from A's bit apos[p] and/or
 // B's bit bpos[p] (-1: absent); summed bit j sits at A bit ka[j] and B bit kb[j].
 constexpr int kSmallMaxBits = 12;
-// Largest step, multiply-adds: more are quicker as a product of their own than on one compute unit (24-qubit state, two
-// of 2^16 and one of 2^17: 492 us with them here, 476 without; BF16x3 446 and 396).
-constexpr int kSmallMaxMacLog2 = 15;
+constexpr int kSmallMaxMacLog2 = 20;
 constexpr int kSmallDescCache = 128;  // step descriptors staged in LDS at a time
 constexpr int kSmallStage = 12288;    // operand elements staged in LDS per round (96 KB)
 struct SmallStep {

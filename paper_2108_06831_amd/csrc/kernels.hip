@@ -1906,7 +1906,7 @@ static void tile_args(const GemmDesc& d, int tile, TileArgs& g) {
 // one block.  (The descriptor orders m and n by C and k by A alone; with B's lowest three bits above k's low four,
 // complex64 1024 x 4096 x 512 loaded each line of B 8 times over: 349 us, 135 so.)  Short sums store more than they
 // load, and keep C's order in m and n: their tiles are then longer runs of C.
-static GemmDesc line_order(const GemmDesc& d) {
+static GemmDesc line_order(const GemmDesc& d, int precision) {
   GemmDesc r = d;
   auto order = [](int n, const int8_t* x, const int8_t* y, int8_t* rx, int8_t* ry) {
     std::vector<int> v(n);
@@ -1922,7 +1922,7 @@ static GemmDesc line_order(const GemmDesc& d) {
     order(d.nbm, d.a_m, d.c_m, r.a_m, r.c_m);
     order(d.nbn, d.b_n, d.c_n, r.b_n, r.c_n);
   }
-  order(d.nbk, d.a_k, d.b_k, r.a_k, r.b_k);
+  if (precision != TN_PREC_BF16X3 || !d.fixed_sum) order(d.nbk, d.a_k, d.b_k, r.a_k, r.b_k);
   return r;
 }
 
@@ -1931,7 +1931,7 @@ hipError_t launch_gemm(hipStream_t s, const GemmDesc& desc, int tile, int split,
                        int precision) {
   if (!gemm_tile_supported(desc, tile)) return hipErrorInvalidValue;
   const bool reorder = tile != kGemmVector && tile != kGemmBatchPacked && tile != kGemmColumnPacked;
-  const GemmDesc d = reorder ? line_order(desc) : desc;
+  const GemmDesc d = reorder ? line_order(desc, precision) : desc;
   if (tile > kGemmVector && precision != TN_PREC_C64) return hipErrorInvalidValue;  // 3M: FP32 only
   const int64_t c_elems = d.batch * d.M * d.N;
   if (tile == kGemmVector) {

@@ -784,6 +784,17 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
           std::swap(kpos[0], kpos[1]);
           std::swap(kaddr[0], kaddr[1]);
         }
+        // Gates of at most 2^kSmallMaxBits elements are the interpreter's when they run one by one, which sums in
+        // Gray-code order from the first operand's most significant bit: the same order here.
+        if (ch.bits <= kSmallMaxBits) {
+          it.gray = true;
+          if (!it.gate_first || kaddr[1] > kaddr[0]) {
+            std::swap(kpos[0], kpos[1]);
+            std::swap(kaddr[0], kaddr[1]);
+            std::swap(maddr[0], maddr[1]);
+            std::swap(mlab[0], mlab[1]);
+          }
+        }
         it.pos[0] = kpos[0];
         it.pos[1] = kpos[1];
       }
@@ -1145,6 +1156,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
                                    lk = by_pos(GA.bits, C_K);
         GemmDesc& g = P.gm[o];
         g.swapped = o;
+        g.fixed_sum = 0;
         g.batch = bsz; g.M = swap ? nsz : msz; g.N = swap ? msz : nsz; g.K = ksz;
         g.nbb = (int32_t)lb_.size(); g.nbm = (int32_t)lm.size(); g.nbn = (int32_t)ln.size();
         g.nbk = (int32_t)lk.size();
@@ -1189,6 +1201,9 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
           g.max_split = kGemmMaxSplit;
       }
       for (int prec = 0; prec < 2; ++prec) P.orient[prec] = gemm_default_launch(P.gm, prec);
+      // BF16x3: a product that others take up rounds its result to two parts, so another order of its sums shows in
+      // the last of them (2^-17), and is not averaged out where few paths lead to a result
+      if (s + 1 < S) P.orient[TN_PREC_BF16X3] = gemm_fixed_sum(P.gm);
       const int max_split = std::max(P.gm[0].max_split, P.gm[1].max_split);
       if (max_split > 1) {
         BufRef tmp;
@@ -1832,6 +1847,43 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
   return work > ((int64_t)1 << 23) && waste(gm[1]) < waste(gm[0]) ? 1 : 0;
 }
 
+// how many of C's lowest five address bits are column bits, in order
+static int low_columns(const GemmDesc& g) {
+  int c = 0;
+  while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
+  return c;
+}
+
+// One output per thread or tiles, ranges of K and orientation by the sizes alone, with k in its own order.  (A tile's
+// size does not change a sum.)
+int gemm_fixed_sum(GemmDesc (&gm)[2]) {
+  for (GemmDesc& g : gm) {
+    int tile, split;
+    gemm_tile_by_blocks(g, &tile, &split);
+    g.fixed_sum = 1;
+    g.tile[TN_PREC_BF16X3] = tile;
+    g.split[TN_PREC_BF16X3] = split;
+  }
+  return gm[0].K <= 32 && gm[0].tile[TN_PREC_BF16X3] != kGemmVector && gm[1].tile[TN_PREC_BF16X3] != kGemmVector &&
+                 low_columns(gm[1]) > low_columns(gm[0])
+             ? 1
+             : 0;
+}
+
+// The launch shape that the planner's model prices: by the sizes alone, so that a plan does not move with the rules
+// above (another plan is another order of sums, which a BF16x3 result shows).
+static int model_shape(const GemmDesc (&gm)[2], int* tile, int* split) {
+  int tl[2], sp[2];
+  for (int o = 0; o < 2; ++o) {
+    gemm_tile_by_blocks(gm[o], &tl[o], &sp[o]);
+    if ((tl[o] == 0 || tl[o] == 2) && gm[o].N >= 64) tl[o] = tl[o] == 0 ? 5 : 6;
+  }
+  const int o = gm[0].K <= 32 && tl[0] != kGemmVector && tl[1] != kGemmVector && low_columns(gm[1]) > low_columns(gm[0]) ? 1 : 0;
+  *tile = tl[o];
+  *split = sp[o];
+  return o;
+}
+
 double modeled_seconds(const tn_path* path) {
   constexpr double kLaunch = 5e-6, kHbm = 6.0e12, kPerm = 1.6e12, kMfma = 95e12;
   double t = 0;
@@ -1853,31 +1905,34 @@ double modeled_seconds(const tn_path* path) {
   for (int s = 0; s < (int)path->steps.size(); ++s) {
     const StepProgram& P = path->steps[s];
     if (P.kind == SK_SMALL || P.chain != -1) continue;
-    if (elem_groupable(P, TN_PREC_C64) && run0 >= 0 && P.grp_from <= run0 && run_len < kElemGroupMax) {
+    int tl = 0, split = 1, orient = 0;
+    if (P.kind == SK_GEMM) orient = model_shape(P.gm, &tl, &split);
+    const GemmDesc& g = P.gm[orient];
+    const bool groupable = P.kind == SK_GEMM && P.pre.empty() && tl == kGemmVector &&
+                           g.nbb + g.nbm + g.nbn <= kElemGroupOutBits && g.nbk <= kElemKBits;
+    if (groupable && run0 >= 0 && P.grp_from <= run0 && run_len < kElemGroupMax) {
       ++run_len;  // joins the previous launch
     } else {
       t += kLaunch;
-      run0 = elem_groupable(P, TN_PREC_C64) ? s : -1;
+      run0 = groupable ? s : -1;
       run_len = 1;
     }
     for (const PermuteDesc& pd : P.pre) t += kLaunch + 16.0 * std::ldexp(1.0, pd.bits) / kPerm;
     if (P.kind == SK_SKINNY) {
       t += P.bytes / kHbm;
     } else {
-      const GemmDesc& g = P.gm[P.orient[0]];
       const double bytes = 8.0 * (double)g.batch * (double)(g.M * g.K + g.K * g.N + g.M * g.N);
-      const int tl = g.tile[0];
       if (tl == kGemmVector) {  // per-output vector kernel
         t += std::max(P.flops / 20e12, bytes / kHbm);
         continue;
       }
       const double tm = kGemmTileM[tl], tn = kGemmTileN[tl];
-      const double tiles = std::ceil(g.M / tm) * std::ceil(g.N / tn) * (double)g.batch * g.split[0];
+      const double tiles = std::ceil(g.M / tm) * std::ceil(g.N / tn) * (double)g.batch * split;
       // the 3M tiles do three real products where the real embedding does four
       const double form = tl > kGemmVector ? 4.0 / 3.0 : 1.0;
       const double eff = form * std::min(1.0, g.M / tm) * std::min(1.0, g.N / tn) * std::min(1.0, g.K / 32.0) *
-                         std::min(1.0, tiles / 256.0) * (tm * tn >= 4096 || tl > kGemmVector ? 1.0 : 0.8);
-      t += std::max(P.flops / (kMfma * std::max(eff, 1e-3)), bytes / kHbm) + (g.split[0] > 1 ? kLaunch : 0.0);
+                         std::min(1.0, tiles / 256.0) * (tm * tn >= 8192 ? 1.0 : 0.8);
+      t += std::max(P.flops / (kMfma * std::max(eff, 1e-3)), bytes / kHbm) + (split > 1 ? kLaunch : 0.0);
     }
   }
   return t;

@@ -119,7 +119,8 @@ bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool 
       const size_t w0 = out->words.size(), v0 = out->vals.size();
       auto emit = [&](uint32_t w) { out->words.push_back(w); };
       auto values = [&](const SeqItem& it) {
-        for (int j = 0; j < vals_of(it); ++j) out->vals.push_back(it.val[j]);
+        for (int j = 0; j < vals_of(it); ++j)  // (columns 2 and 3 in the order they are summed)
+          out->vals.push_back(it.val[it.gray && (j & 2) ? j ^ 1 : j]);
       };
       auto slot_word = [](const SeqItem& it) { return (uint32_t)it.gen | ((uint32_t)(it.red + 1) << 8); };
       for (size_t x = 0; x < s.items.size();) {
@@ -173,7 +174,7 @@ bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool 
           ++x;
         } else {
           if (it.red >= 0 || !((k0 == 0 && k1 == 1) || (k0 == 2 && k1 == 3))) return false;
-          emit(SEQ_DENSE2 | ((uint32_t)(k0 / 2) << 4) | (it.gate_first ? 1u << 12 : 0));
+          emit(SEQ_DENSE2 | ((uint32_t)(k0 / 2) << 4) | (it.gate_first ? 1u << 12 : 0) | (it.gray ? 1u << 13 : 0));
           values(it);
           ++x;
         }

@@ -78,11 +78,14 @@ def host_description():
 def stored_traffic(config, precision, kernel, alg_bytes_per_launch):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 counter
     summaries (FETCH_SIZE and WRITE_SIZE, scaled by a plain copy's reading),
-    if they were taken on the current kernel source and on launches of the
+    if they were taken on the current kernel sources and on launches of the
     same plan (the same algorithmic bytes per launch); else None."""
     import glob
     import hashlib
-    src = hashlib.sha256(open(os.path.join(ROOT, "paper_2108_06831_amd", "csrc", "kernels.hip"), "rb").read())
+    csrc = os.path.join(ROOT, "paper_2108_06831_amd", "csrc")
+    src = hashlib.sha256(open(os.path.join(csrc, "kernels.hip"), "rb").read())
+    for f in sorted(glob.glob(os.path.join(csrc, "*_kernels.hip"))):
+        src.update(open(f, "rb").read())
     want = {"config": str(config), "precision": precision, "kernel": kernel, "kernels_hip_sha256": src.hexdigest()[:16]}
     for f in sorted(glob.glob(os.path.join(ROOT, "profiles", "*.md"))):
         for line in open(f):

@@ -422,7 +422,8 @@ static tn_status run_seq(hipStream_t s, tn_path* path, DevPath* dp, const Bases&
                                last && direct ? B.final_out : out, last && direct ? B.final_out_bs : obs,
                                last ? pos : nullptr, in, ibs, batch, precision));
   }
-  prof_stop(s, ev, TN_KERNEL_SWEEP, 16.0 * std::ldexp(1.0, ch.bits) * n * batch, ch.flops * batch);
+  // (the first pass reads no state)
+  prof_stop(s, ev, TN_KERNEL_SWEEP, (16.0 * n - 8.0) * std::ldexp(1.0, ch.bits) * batch, ch.flops * batch);
   return TN_OK;
 }
 
@@ -510,7 +511,7 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
           if (gd.form == kFormCount) continue;  // its member gates are counted
           fl += gd.diag ? 8.0 : 8.0 * (1 << gd.n);
         }
-        prof_stop(s, ev, TN_KERNEL_SWEEP, 16.0 * std::ldexp(1.0, ch.bits) * batch,
+        prof_stop(s, ev, TN_KERNEL_SWEEP, ((src ? 8.0 : 0.0) + (ends ? 0.0 : 8.0)) * std::ldexp(1.0, ch.bits) * batch,
                   fl * std::ldexp(1.0, ch.bits) * batch);
       }
       continue;
@@ -1152,17 +1153,38 @@ static bool one_seq_pass(const tn_path* path) {
          path->seq.bits == path->seq.prog.passes[0].l;
 }
 
-// The expectations of the circuits `which` (all one_seq_pass) in launches of several, on the lanes
-// lane0 .. lane0 + n_lanes - 1 (lane 0: the caller's stream): their input tensors, then one launch per
-// block size, the sizes on different lanes, joined into lane0.  Circuits go together as long as their
-// input tensors fit `ws_bytes`.
-static tn_status expect_seq(hipStream_t s_call, SideLanes* SL, int lane0, int n_lanes, int precision,
-                            const std::vector<int>& which, tn_network* const* nets, tn_path* const* paths,
-                            const double* const* params_dev, int batch, const tn_observable* obs,
-                            const std::vector<DevNet*>& devs, char* w, size_t ws_bytes, double* out_dev) {
-  auto stream = [&](int k) { return lane0 + k == 0 ? s_call : SL->stream[lane0 + k - 1]; };
-  auto event = [&](int k) { return lane0 + k == 0 ? SL->fork : SL->join[lane0 + k - 1]; };
-  hipStream_t s0 = stream(0);
+// Lanes [first, first + n) but lane 0 wait for the caller's stream; and the caller's stream for them.  (Lanes fork from
+// and join into the caller's stream only.  In a capture a stream that waits for a forked one becomes that one's child;
+// two forked streams that wait for each other are each other's, and the runtime does not come back from ending the
+// capture: the process ended with a segmentation fault there.)
+static tn_status fork_lanes(hipStream_t s0, SideLanes* SL, int first, int n) {
+  if (first + n <= 1) return TN_OK;
+  HIP_TRY(hipEventRecord(SL->fork, s0));
+  for (int k = std::max(first, 1); k < first + n; ++k) HIP_TRY(hipStreamWaitEvent(SL->stream[k - 1], SL->fork, 0));
+  return TN_OK;
+}
+
+static tn_status join_lanes(hipStream_t s0, SideLanes* SL, int first, int n) {
+  tn_status result = TN_OK;
+  for (int k = std::max(first, 1); k < first + n; ++k) {
+    const hipError_t e1 = hipEventRecord(SL->join[k - 1], SL->stream[k - 1]);
+    const hipError_t e2 = hipStreamWaitEvent(s0, SL->join[k - 1], 0);
+    if (result == TN_OK && (e1 != hipSuccess || e2 != hipSuccess))
+      result = set_error(TN_EDEVICE, std::string("joining the expectation lanes: ") +
+                                         hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+  }
+  return result;
+}
+
+// The expectations of the circuits `which` (all one_seq_pass) in launches of several: their input tensors on the
+// caller's stream s0, then one launch per block size on the lanes lane0 .. lane0 + n_lanes - 1 (lane 0: s0).  Circuits
+// go together as long as their input tensors fit `ws_bytes`; a group that others follow is joined into s0.  The last
+// one forks all `used` lanes (*forked) and is joined by the caller.
+static tn_status expect_seq(hipStream_t s0, SideLanes* SL, int lane0, int n_lanes, int used_lanes, bool* forked,
+                            int precision, const std::vector<int>& which, tn_network* const* nets,
+                            tn_path* const* paths, const double* const* params_dev, int batch,
+                            const tn_observable* obs, const std::vector<DevNet*>& devs, char* w, size_t ws_bytes,
+                            double* out_dev) {
   for (size_t i0 = 0; i0 < which.size();) {
     MatArgs mat;
     mat.n = 0;
@@ -1236,25 +1258,20 @@ static tn_status expect_seq(hipStream_t s_call, SideLanes* SL, int lane0, int n_
       }
       flush();
     }
-    const int lanes = std::min((int)launches.size(), n_lanes);
-    if (lanes > 1) {
-      HIP_TRY(hipEventRecord(event(0), s0));
-      for (int k = 1; k < lanes; ++k) HIP_TRY(hipStreamWaitEvent(stream(k), event(0), 0));
-    }
-    tn_status result = TN_OK;
+    const bool last = i0 >= which.size();
+    tn_status result = last ? fork_lanes(s0, SL, 0, used_lanes) : fork_lanes(s0, SL, lane0, n_lanes);
+    if (last) *forked = true;
     for (size_t k = 0; k < launches.size() && result == TN_OK; ++k) {
-      hipStream_t s = stream((int)k % lanes);
+      const int lane = lane0 + (int)k % n_lanes;
+      hipStream_t s = lane == 0 ? s0 : SL->stream[lane - 1];
       ev = prof_start(s, TN_KERNEL_SWEEP);
       const hipError_t e = launch_seq_expect(s, launches[k], batch, precision);
       if (e != hipSuccess) result = set_error(TN_EDEVICE, std::string("expectation: ") + hipGetErrorString(e));
       prof_stop(s, ev, TN_KERNEL_SWEEP, 0.0, flops[k]);
     }
-    for (int k = 1; k < lanes; ++k) {
-      const hipError_t e1 = hipEventRecord(event(k), stream(k));
-      const hipError_t e2 = hipStreamWaitEvent(s0, event(k), 0);
-      if (result == TN_OK && (e1 != hipSuccess || e2 != hipSuccess))
-        result = set_error(TN_EDEVICE, std::string("joining the expectation lanes: ") +
-                                           hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+    if (!last) {
+      const tn_status st = join_lanes(s0, SL, lane0, n_lanes);
+      if (result == TN_OK) result = st;
     }
     if (result != TN_OK) return result;
   }
@@ -1303,10 +1320,11 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
   const int seq_lanes = together.empty() ? 0 : lanes < max_lanes ? std::min(max_lanes - lanes, kSeqExpectSizes) : 1;
   const int used = std::max(lanes, seq_lane0 + seq_lanes);
   std::unique_lock<std::mutex> lanes_lock;  // (another thread's fork event must not come between ours and its waits)
-  if (used > 1) {
-    lanes_lock = std::unique_lock<std::mutex>(SL_->mu);
-    HIP_TRY(hipEventRecord(SL_->fork, s0));
-    for (int k = 0; k < used - 1; ++k) HIP_TRY(hipStreamWaitEvent(SL_->stream[k], SL_->fork, 0));
+  if (used > 1) lanes_lock = std::unique_lock<std::mutex>(SL_->mu);
+  bool forked = together.empty();
+  if (forked) {
+    tn_status st = fork_lanes(s0, SL_, 0, used);
+    if (st != TN_OK) return st;
   }
   // circuits to lanes by the planner's run-time model, largest first, each to the lane with the
   // least work so far (ties: the lower lane), so that the lanes finish close together
@@ -1325,8 +1343,9 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
   }
   tn_status result = TN_OK;
   if (!together.empty())
-    result = expect_seq(s0, SL_, seq_lane0, seq_lanes, precision, together, nets, paths, params_dev, batch, obs, devs,
-                        (char*)workspace_dev + (size_t)seq_lane0 * slot, (size_t)seq_lanes * slot, out_dev);
+    result = expect_seq(s0, SL_, seq_lane0, seq_lanes, used, &forked, precision, together, nets, paths, params_dev,
+                        batch, obs, devs, (char*)workspace_dev + (size_t)seq_lane0 * slot, (size_t)seq_lanes * slot,
+                        out_dev);
   for (int c : rest) {
     if (result != TN_OK) break;
     tn_network* net = nets[c];
@@ -1385,12 +1404,9 @@ extern "C" tn_status tn_expectation(void* stream, int32_t precision, tn_network*
     prof_stop(s, ev, TN_KERNEL_REDUCE, 8.0 * (double)(n_partial > 0 ? n_partial : path->final_elems) * batch, 0.0);
   }
   // join the lanes back into the caller's stream (also after an error, so no lane stays forked)
-  for (int k = 0; k < used - 1; ++k) {
-    const hipError_t e1 = hipEventRecord(SL_->join[k], SL_->stream[k]);
-    const hipError_t e2 = hipStreamWaitEvent(s0, SL_->join[k], 0);
-    if (result == TN_OK && (e1 != hipSuccess || e2 != hipSuccess))
-      result = set_error(TN_EDEVICE, std::string("joining the expectation lanes: ") +
-                                         hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+  if (forked && used > 1) {
+    const tn_status st = join_lanes(s0, SL_, 0, used);
+    if (result == TN_OK) result = st;
   }
   return result;
 }

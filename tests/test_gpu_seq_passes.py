@@ -104,3 +104,40 @@ def test_long_ansatz_takes_several_windows():
     got = grad.cpu().numpy()[0]
     assert np.max(np.abs(got[which] - g[which])) < 1e-5 * max(np.linalg.norm(got), 1.0)
     assert abs(float(value[0]) - oracle.circuit_expectation(circ, params[0], m, c)) < 1e-5 * n
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_captured_expectations_of_many_sizes(batch):
+    """Circuits of one chunk and larger ones in one captured call, so that both have stream lanes of their own, and
+    more of one chunk than one launch fills: replays, with new parameters between them, against the eager call."""
+    import torch
+    from paper_2108_06831_amd import Graph, Network, Observable, expectation
+    nets, paths, params, obs = [], [], [], []
+    for i in range(26):
+        n = [10, 12, 14, 16, 8, 10][i % 6]
+        rng = np.random.default_rng(i)
+        edges = workloads.random_regular_graph(n, 3, rng)
+        circ = workloads.qaoa_circuit(n, edges, 2)
+        nets.append(Network.from_circuit(circ))
+        paths.append(nets[-1].plan("sequential"))
+        params.append(torch.as_tensor(rng.uniform(0, 2, size=(batch, circ.n_params)), device="cuda"))
+        obs.append(Observable(*workloads.maxcut_observable(n, edges)))
+    want = expectation(nets, paths, params, obs, batch=batch).clone()
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    ws = torch.empty(1 << 28, dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(want)
+    expectation(nets, paths, params, obs, batch=batch, workspace=ws, out=out, stream=stream)
+    torch.cuda.synchronize()
+    graph = Graph(stream)
+    with graph.capture():
+        expectation(nets, paths, params, obs, batch=batch, workspace=ws, out=out, stream=stream)
+    for k in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        for p in params:
+            p.add_(0.1)
+        want = expectation(nets, paths, params, obs, batch=batch).clone()

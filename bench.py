@@ -75,18 +75,27 @@ def host_description():
             "host_mem_gib": round(mem_kib / 2 ** 20, 1) if mem_kib else None}
 
 
+def device_source_key(csrc):
+    """Key of the sources that device code is compiled from: kernels.hip, then every other .hip
+    file and header under its name (kernel bodies and launch descriptors live in headers too)."""
+    import glob
+    import hashlib
+    first = os.path.join(csrc, "kernels.hip")
+    key = hashlib.sha256(open(first, "rb").read())
+    for f in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.h"))):
+        if f != first:
+            key.update(os.path.basename(f).encode() + b"\0" + open(f, "rb").read())
+    return key.hexdigest()[:16]
+
+
 def stored_traffic(config, precision, kernel, alg_bytes_per_launch):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 counter
     summaries (FETCH_SIZE and WRITE_SIZE, scaled by a plain copy's reading),
-    if they were taken on the current kernel sources and on launches of the
+    if they were taken on the current device sources and on launches of the
     same plan (the same algorithmic bytes per launch); else None."""
     import glob
-    import hashlib
-    csrc = os.path.join(ROOT, "paper_2108_06831_amd", "csrc")
-    src = hashlib.sha256(open(os.path.join(csrc, "kernels.hip"), "rb").read())
-    for f in sorted(glob.glob(os.path.join(csrc, "*_kernels.hip"))):
-        src.update(open(f, "rb").read())
-    want = {"config": str(config), "precision": precision, "kernel": kernel, "kernels_hip_sha256": src.hexdigest()[:16]}
+    want = {"config": str(config), "precision": precision, "kernel": kernel,
+            "kernels_hip_sha256": device_source_key(os.path.join(ROOT, "paper_2108_06831_amd", "csrc"))}
     for f in sorted(glob.glob(os.path.join(ROOT, "profiles", "*.md"))):
         for line in open(f):
             if not line.startswith("traffic-record:"):

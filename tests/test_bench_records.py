@@ -51,3 +51,32 @@ def test_committed_records_name_their_plan():
                 assert float(kv["alg_bytes_per_launch"]) > 0 and float(kv["bytes_per_launch"]) > 0
                 n += 1
     assert n >= 3
+
+
+def test_record_is_keyed_on_every_device_source(tmp_path, monkeypatch):
+    """Kernels come from several .hip files and from headers: a change, a new name or a new file of
+    either kind makes the record one of other kernels."""
+    make_tree(tmp_path)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    csrc = tmp_path / "paper_2108_06831_amd" / "csrc"
+    (csrc / "pass_kernels.hip").write_bytes(b"// passes\n")
+    (csrc / "pass_util.h").write_bytes(b"// gate bodies\n")
+    (csrc / "planner.cpp").write_bytes(b"// host\n")
+    key = bench.device_source_key(str(csrc))
+    md = tmp_path / "profiles" / "k.md"
+    md.write_text(
+        f"traffic-record: config=3 precision=c64 kernel=sweep kernels_hip_sha256={key} "
+        "bytes_per_launch=1000 alg_bytes_per_launch=990.0 fetch_scale=2.0 write_scale=1.0\n")
+    assert bench.stored_traffic(3, "c64", "sweep", 990.0) == 1000.0
+    (csrc / "planner.cpp").write_bytes(b"// another host file\n")
+    assert bench.stored_traffic(3, "c64", "sweep", 990.0) == 1000.0
+    for name, body in (("pass_kernels.hip", b"// passes\n"), ("pass_util.h", b"// gate bodies\n")):
+        (csrc / name).write_bytes(b"// changed\n")
+        assert bench.stored_traffic(3, "c64", "sweep", 990.0) is None
+        (csrc / name).write_bytes(body)
+        assert bench.stored_traffic(3, "c64", "sweep", 990.0) == 1000.0
+    (csrc / "pass_util.h").rename(csrc / "pass_util2.h")
+    assert bench.stored_traffic(3, "c64", "sweep", 990.0) is None
+    (csrc / "pass_util2.h").rename(csrc / "pass_util.h")
+    (csrc / "device_util.h").write_bytes(b"// more\n")
+    assert bench.stored_traffic(3, "c64", "sweep", 990.0) is None

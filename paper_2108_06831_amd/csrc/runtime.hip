@@ -260,7 +260,7 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   d = new DevPath();
   d->device = dev;
   path->dev = d;
-  if (path->res.lists.empty()) {
+  if (!path->small_items.empty()) {  // (empty: the lists stay in LDS, or other passes take their steps)
     HIP_TRY(upload(&d->steps, path->small_steps));
     HIP_TRY(upload(&d->lists, path->small_lists));
     HIP_TRY(upload(&d->levels, path->small_levels));

@@ -618,7 +618,9 @@ tn_status plan_order(const tn_network* net, const tn_plan_opts& opts, std::vecto
 uint64_t splitmix(uint64_t& s);
 double modeled_seconds(const tn_path* path);
 // program.cpp
-tn_status compile_program(const tn_network* net, tn_path* path, const std::vector<int32_t>* final_layout = nullptr);
+// (price: only what modeled_seconds reads; such a path does not run)
+tn_status compile_program(const tn_network* net, tn_path* path, const std::vector<int32_t>* final_layout = nullptr,
+                          bool price = false);
 std::vector<int32_t> output_layout(const tn_network* net);
 // fused passes of the adjoint sweep over the path's final tensor (sets path->adj_state)
 void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<int32_t>& slot_of_gate);

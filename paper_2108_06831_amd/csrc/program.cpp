@@ -424,7 +424,8 @@ void mark_runs(Desc* g, int n) {
   }
 }
 
-void build_chains(tn_path* path, int T) {
+// (price: for the run-time model alone, without the tables of the register form)
+void build_chains(tn_path* path, int T, bool price) {
   path->chains.clear();
   path->passes.clear();
   path->segments.clear();
@@ -605,7 +606,7 @@ void build_chains(tn_path* path, int T) {
       ps.ctab_off = (int32_t)path->sweep_val_src.size() - ch.first_val;
       ps.ctab_n = (int32_t)ctab.size();
       path->sweep_val_src.insert(path->sweep_val_src.end(), ctab.begin(), ctab.end());
-      build_reg_pass(path, ps, R);
+      if (!price) build_reg_pass(path, ps, R);
       path->passes.push_back(ps);
     }
     ch.n_passes = (int32_t)path->passes.size() - ch.first_pass;
@@ -839,7 +840,7 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
 
 }  // namespace
 
-tn_status compile_program(const tn_network* net, tn_path* path, const std::vector<int32_t>* final_layout) {
+tn_status compile_program(const tn_network* net, tn_path* path, const std::vector<int32_t>* final_layout, bool price) {
   const int T = (int)net->tensors.size();
   const int S = (int)path->pairs.size() / 2;
   std::vector<Loc> loc(T + S);
@@ -1373,9 +1374,11 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
       }
     }
   }
-  build_chains(path, T);
-  build_outer_chains(path, T);
-  find_seq_chain(net, path, loc, modes);
+  build_chains(path, T, price);
+  if (!price) {
+    build_outer_chains(path, T);
+    find_seq_chain(net, path, loc, modes);
+  }
   // independent sub-trees of the interpreter's steps -> one work list each.  Where the ordered passes
   // or a chain from |0...0> take these steps, the interpreter does not run: the lists are then only
   // counted (planning a sequential QAOA circuit of 12 qubits takes 0.8 ms so, 4.0 with their tables).
@@ -1384,7 +1387,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
   path->small_items.clear();
   path->res = ResProgram();
   path->res_final = -1;
-  const bool interpreter = path->n_small > 0 && path->seq.end == 0 && path->zero_steps == 0;
+  const bool interpreter = !price && path->n_small > 0 && path->seq.end == 0 && path->zero_steps == 0;
   bool resident = interpreter;
   if (path->n_small > 0) {
     std::vector<int> consumer(S, -1);
@@ -1546,7 +1549,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
   }
   path->ws_elems = std::max<int64_t>(alloc.peak, 32);
   path->n_inputs = T;
-  build_q328_program(net, path);
+  if (!price) build_q328_program(net, path);
   return TN_OK;
 }
 
@@ -2007,7 +2010,7 @@ static tn_status plan_path_impl(const tn_network* net, const tn_plan_opts& o, tn
         b->min_log2 = std::min(b->min_log2, (int)ml);
         if (s == TN_OK) {
           q->pairs = reorder_small_first(net, q->pairs, &q->n_small, &q->small_region);
-          s = compile_program(net, q, &fl);
+          s = compile_program(net, q, &fl, true);
         }
         if (s != TN_OK) {
           delete q;
@@ -2018,7 +2021,6 @@ static tn_status plan_path_impl(const tn_network* net, const tn_plan_opts& o, tn
           continue;
         }
         const double t = modeled_seconds(q);
-        q->stats.modeled_seconds = t;
         if (!b->p || t < b->t || (t == b->t && i < b->idx)) {
           delete b->p;
           b->p = q;
@@ -2056,10 +2058,19 @@ static tn_status plan_path_impl(const tn_network* net, const tn_plan_opts& o, tn
     }
     for (size_t k = 0; k < bests.size(); ++k)
       if (k != best_i) delete bests[k].p;
-    if (best_i != SIZE_MAX) p = bests[best_i].p;
-    if (!p) return set_error(TN_ELIMIT, "every searched order's largest intermediate (at best 2^" +
-                                            std::to_string(min_log2) + ")" + cap_msg);
+    if (best_i == SIZE_MAX)
+      return set_error(TN_ELIMIT, "every searched order's largest intermediate (at best 2^" +
+                                      std::to_string(min_log2) + ")" + cap_msg);
     clear_error();
+    // the trials were compiled as far as the model reads; the winner is compiled whole
+    p = new tn_path();
+    p->pairs = std::move(bests[best_i].p->pairs);
+    p->n_small = bests[best_i].p->n_small;
+    p->small_region = bests[best_i].p->small_region;
+    delete bests[best_i].p;
+    const tn_status s = compile_program(net, p, &fl);
+    if (s != TN_OK) { delete p; return s; }
+    p->stats.modeled_seconds = modeled_seconds(p);
   }
   *path_out = p;
   return TN_OK;

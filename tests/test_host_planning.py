@@ -1,12 +1,29 @@
 """Host cost of planning.  Times are the least of several runs, compared between
 plans made in the same process, so that the machine's speed does not enter."""
+import ctypes
+import os
+import subprocess
 import time
 
 import numpy as np
 import pytest
 
 import workloads
-from paper_2108_06831_amd import Network
+from paper_2108_06831_amd import Network, _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def internals(tmp_path_factory):
+    """host_internals.cpp, compiled against the library's headers; its symbols come from the loaded library."""
+    out = str(tmp_path_factory.mktemp("internals") / "internals.so")
+    _lib.lib()
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2108_06831_amd", "csrc"),
+                    "-o", out, os.path.join(ROOT, "tests", "host_internals.cpp"),
+                    _lib.LIB_PATH, "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH)], check=True)
+    return ctypes.CDLL(out)
 
 
 def least_seconds(fn, runs=9):
@@ -27,6 +44,27 @@ def qaoa_network(n):
 def test_ordered_passes_plan_no_interpreter_tables(n):
     """A sequential circuit of at most 12 qubits is all interpreter steps by size, but runs as one
     ordered pass.  At 14 qubits most steps are too large for the interpreter, so that plan never had
-    its tables: the smaller circuits, with fewer gates, must take less time to plan (0.25 to 0.5 of it, and 0.8 to 3.4 with the tables)."""
+    its tables: the smaller circuits, with fewer gates, must take less time to plan (0.25 to 0.5 of
+    it, and 0.8 to 3.4 with the tables)."""
     small, large = qaoa_network(n), qaoa_network(14)
     assert least_seconds(lambda: small.plan("sequential")) <= 0.75 * least_seconds(lambda: large.plan("sequential"))
+
+
+def brickwork_network(n, depth, fuse):
+    return Network.from_circuit(workloads.brickwork(n, depth, np.random.default_rng(n)), fuse=fuse)
+
+
+@pytest.mark.parametrize("make", [lambda: brickwork_network(6, 3, False), lambda: brickwork_network(10, 8, "split"),
+                                  lambda: brickwork_network(20, 8, "split"), lambda: qaoa_network(12),
+                                  lambda: qaoa_network(18)])
+@pytest.mark.parametrize("kind", ["greedy", "sequential", "search"])
+def test_search_prices_orders_without_launch_tables(internals, make, kind):
+    """A trial of the search is compiled as far as the run-time model reads, to the same modelled time
+    as the whole program; the tables that only launches read are the winner's alone."""
+    net = make()
+    path = net.plan(kind)
+    seconds, entries, full = ctypes.c_double(), ctypes.c_int64(), ctypes.c_int64()
+    assert internals.priced_program(net.handle, path.handle, ctypes.byref(seconds), ctypes.byref(entries),
+                                    ctypes.byref(full)) == 0
+    assert seconds.value == path.stats["modeled_seconds"]
+    assert entries.value == 0 and full.value > 0

@@ -628,7 +628,9 @@ void build_adjoint_plan(const tn_network* net, tn_path* path, const std::vector<
 void build_reg_pass(tn_path* path, SweepPass& ps, int R);
 void build_adj_reg_pass(tn_path* path, SweepPass& ps, int R);
 // seqpass.cpp: ordered passes over `items` on a 2^R state, chunks of at most 2^lmax elements
-// One work list (steps by ascending level) added to `prog`; false if it does not fit LDS.
+// One work list (steps by ascending level) added to `prog`; false if it does not fit LDS
+// (resident_list_fits: told from its sizes, before any of it is planned).
+bool resident_list_fits(const std::vector<SmallStep>& steps, const std::vector<int>& level);
 bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<int>& level, ResProgram* prog);
 bool build_seq_program(int R, const std::vector<SeqItem>& items, int lmax, bool adjoint, SeqProgram* out);
 // moves every step that is small and depends only on inputs or such steps to the

@@ -13,26 +13,62 @@
 namespace tnq {
 namespace {
 
-// Places of power-of-two sizes at multiples of their size, first fit.
+// Places of power-of-two sizes at multiples of their size, first fit; a bit per element.
 struct Places {
-  std::vector<char> used = std::vector<char>(kResElems, 0);
+  static_assert(kResElems % 64 == 0, "whole words");
+  uint64_t used[kResElems / 64] = {};
 
   int take(int n) {
+    if (n < 64) {
+      const uint64_t mask = ((uint64_t)1 << n) - 1;
+      for (int w = 0; w < kResElems / 64; ++w) {
+        if (used[w] == ~(uint64_t)0) continue;
+        for (int at = 0; at < 64; at += n)
+          if (!(used[w] & (mask << at))) {
+            used[w] |= mask << at;
+            return 64 * w + at;
+          }
+      }
+      return -1;
+    }
     for (int at = 0; at + n <= kResElems; at += n)
-      if (std::find(used.begin() + at, used.begin() + at + n, 1) == used.begin() + at + n) {
-        std::fill(used.begin() + at, used.begin() + at + n, 1);
+      if (std::find_if(used + at / 64, used + (at + n) / 64, [](uint64_t u) { return u != 0; }) == used + (at + n) / 64) {
+        set(at, n, true);
         return at;
       }
     return -1;
   }
-  void give(int at, int n) { std::fill(used.begin() + at, used.begin() + at + n, 0); }
+  void set(int at, int n, bool on) {  // (at: a multiple of n)
+    if (n < 64) {
+      const uint64_t mask = (((uint64_t)1 << n) - 1) << (at & 63);
+      used[at / 64] = on ? used[at / 64] | mask : used[at / 64] & ~mask;
+    } else {
+      std::fill(used + at / 64, used + (at + n) / 64, on ? ~(uint64_t)0 : 0);
+    }
+  }
 };
 
 }  // namespace
 
-bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<int>& level, ResProgram* prog) {
+// Whether the list's steps, levels and inputs are within the kernel's tables and LDS.
+bool resident_list_fits(const std::vector<SmallStep>& steps, const std::vector<int>& level) {
   const int S = (int)steps.size();
   if (S < 1 || S > kResSteps) return false;
+  int levels = 0;
+  int64_t inputs = 0;
+  for (int s = 0; s < S; ++s) {
+    const SmallStep& d = steps[s];
+    if (d.c_bits > kSmallMaxBits || d.a_bits > kSmallMaxBits || d.b_bits > kSmallMaxBits) return false;
+    levels += s == 0 || level[s] != level[s - 1];
+    if (d.a_buf == BUF_IN) inputs += (int64_t)1 << d.a_bits;
+    if (d.b_buf == BUF_IN) inputs += (int64_t)1 << d.b_bits;
+  }
+  return levels <= kResLevels && inputs <= kResElems;
+}
+
+bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<int>& level, ResProgram* prog) {
+  const int S = (int)steps.size();
+  if (!resident_list_fits(steps, level)) return false;
   ResList L;
   L.level0 = (int32_t)prog->levels.size();
   L.step0 = (int32_t)prog->steps.size();
@@ -53,23 +89,22 @@ bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<in
   std::vector<Input> inputs;
   for (int s = 0; s < S; ++s) {
     const SmallStep& d = steps[s];
-    if (d.c_bits > kSmallMaxBits || d.a_bits > kSmallMaxBits || d.b_bits > kSmallMaxBits) return false;
     if (d.a_buf == BUF_IN) inputs.push_back({s, 0, d.a_bits, d.a_off});
     if (d.b_buf == BUF_IN) inputs.push_back({s, 1, d.b_bits, d.b_off});
   }
   std::stable_sort(inputs.begin(), inputs.end(), [](const Input& x, const Input& y) { return x.bits > y.bits; });
   for (const Input& in : inputs) {
     const int n = 1 << in.bits, at = (int)copy.size();
-    if (at + n > kResElems || in.off < 0 || in.off + n > ((int64_t)1 << 32)) return false;
+    if (in.off < 0 || in.off + n > ((int64_t)1 << 32)) return false;
     (in.side ? out[in.step].b : out[in.step].a) = (uint16_t)at;
-    std::fill(places.used.begin() + at, places.used.begin() + at + n, 1);
+    places.set(at, n, true);
     for (int e = 0; e < n; ++e) copy.push_back((uint32_t)(in.off + e));
   }
   std::map<int64_t, int> result_at;  // workspace offset -> place
   for (int s0 = 0; s0 < S;) {
     int s1 = s0;
     while (s1 < S && level[s1] == level[s0]) ++s1;
-    if (++L.n_levels > kResLevels) return false;
+    ++L.n_levels;
     int64_t total = 0;
     for (int s = s0; s < s1; ++s) {
       const SmallStep& d = steps[s];
@@ -101,34 +136,40 @@ bool add_resident_list(const std::vector<SmallStep>& steps, const std::vector<in
     }
     // work items: about equal work (outputs times summed terms, plus the store) per thread
     const size_t first = items.size();
-    for (int64_t target = std::max<int64_t>(1, (total + kSmallThreads - 1) / kSmallThreads);; target *= 2) {
-      items.resize(first);
-      for (int s = s0; s < s1; ++s) {
-        const SmallStep& d = steps[s];
-        const int64_t per = ((int64_t)1 << d.k_bits) + 4;
-        int lc = 0;  // log2 of the outputs per item
-        while (lc < d.c_bits && ((int64_t)2 << lc) * per <= target) ++lc;
-        const int qb = d.c_bits - lc;
-        for (int j = 0; j < (1 << qb); ++j) {
-          ResItem it;
-          it.a = out[s].a;
-          it.b = out[s].b;
-          for (int p = 0; p < qb; ++p)
-            if ((j >> p) & 1) {
-              if (d.apos[p] >= 0) it.a |= (uint16_t)(1 << d.apos[p]);
-              if (d.bpos[p] >= 0) it.b |= (uint16_t)(1 << d.bpos[p]);
-            }
-          it.what = (uint32_t)s | (uint32_t)j << 8 | (uint32_t)qb << 20;
-          items.push_back(it);
+    int64_t target = std::max<int64_t>(1, (total + kSmallThreads - 1) / kSmallThreads);
+    auto item_bits = [&](const SmallStep& d) {  // the step has 2^item_bits items
+      const int64_t per = ((int64_t)1 << d.k_bits) + 4;
+      int lc = 0;  // log2 of the outputs per item
+      while (lc < d.c_bits && ((int64_t)2 << lc) * per <= target) ++lc;
+      return d.c_bits - lc;
+    };
+    for (;; target *= 2) {
+      int64_t n = 0;
+      for (int s = s0; s < s1; ++s) n += (int64_t)1 << item_bits(steps[s]);
+      if (n <= kSmallMaxItems) break;
+    }
+    for (int s = s0; s < s1; ++s) {
+      const SmallStep& d = steps[s];
+      const int qb = item_bits(d);
+      const size_t i0 = items.size();
+      for (int j = 0; j < (1 << qb); ++j) {
+        ResItem it;
+        it.a = out[s].a;
+        it.b = out[s].b;
+        if (j) {  // the operands of j without its lowest bit, and that bit's places
+          const int p = __builtin_ctz(j);
+          it.a = items[i0 + (j & (j - 1))].a | (uint16_t)(d.apos[p] >= 0 ? 1 << d.apos[p] : 0);
+          it.b = items[i0 + (j & (j - 1))].b | (uint16_t)(d.bpos[p] >= 0 ? 1 << d.bpos[p] : 0);
         }
+        it.what = (uint32_t)s | (uint32_t)j << 8 | (uint32_t)qb << 20;
+        items.push_back(it);
       }
-      if ((int)(items.size() - first) <= kSmallMaxItems) break;
     }
     levels.push_back({(int32_t)(prog->items.size() + first), (int32_t)(items.size() - first)});
     // the level's operands are no longer read
     for (int s = s0; s < s1; ++s) {
-      places.give(out[s].a, 1 << steps[s].a_bits);
-      places.give(out[s].b, 1 << steps[s].b_bits);
+      places.set(out[s].a, 1 << steps[s].a_bits, false);
+      places.set(out[s].b, 1 << steps[s].b_bits, false);
     }
     s0 = s1;
   }

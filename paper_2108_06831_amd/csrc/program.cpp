@@ -1416,6 +1416,8 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
     for (int s = 0; s < path->n_small; ++s) trees[root[s]].push_back(s);
     path->small_levels.clear();
     path->small_lists.push_back(0);
+    std::vector<std::vector<SmallStep>> res_steps;
+    std::vector<std::vector<int>> res_levels;
     for (auto& kv : trees) {
       std::vector<int> lst = kv.second;
       std::stable_sort(lst.begin(), lst.end(), [&](int x, int y) { return level[x] < level[y]; });
@@ -1425,17 +1427,18 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
         path->small_steps.push_back(path->steps[lst[i]].sm);
       }
       path->small_lists.push_back((int32_t)path->small_levels.size());
-      if (resident) {
-        std::vector<SmallStep> sm;
-        std::vector<int> lv;
-        for (int q : lst) {
-          sm.push_back(path->steps[q].sm);
-          lv.push_back(level[q]);
-        }
-        if (lst.back() == S - 1) path->res_final = (int32_t)path->res.lists.size();
-        resident = add_resident_list(sm, lv, &path->res);
+      if (!resident) continue;
+      res_steps.emplace_back();
+      res_levels.emplace_back();
+      for (int q : lst) {
+        res_steps.back().push_back(path->steps[q].sm);
+        res_levels.back().push_back(level[q]);
       }
+      resident = resident_list_fits(res_steps.back(), res_levels.back());
+      if (lst.back() == S - 1) path->res_final = (int32_t)res_steps.size() - 1;
     }
+    for (size_t i = 0; i < res_steps.size() && resident; ++i)
+      resident = add_resident_list(res_steps[i], res_levels[i], &path->res);
     if (!resident) {
       path->res = ResProgram();
       path->res_final = -1;

@@ -1,5 +1,9 @@
 // Reads of the library's host data structures that its C interface does not show
 // (built and called by test_host_planning.py).
+#include <algorithm>
+#include <chrono>
+#include <vector>
+
 #include "internal.h"
 
 using namespace tnq;
@@ -25,4 +29,81 @@ extern "C" int priced_program(const tn_network* net, const tn_path* full, double
   *entries = table_entries(p);
   *entries_full = table_entries(*full);
   return st;
+}
+
+// Least seconds of `runs` compilations of the order of `full`: whole, and for the run-time model alone.
+extern "C" void compile_seconds(const tn_network* net, const tn_path* full, int runs, double* whole, double* priced) {
+  const std::vector<int32_t> layout = output_layout(net);
+  for (int price = 0; price < 2; ++price) {
+    double best = 1e9;
+    for (int r = 0; r < runs; ++r) {
+      tn_path p;
+      p.pairs = full->pairs;
+      p.n_small = full->n_small;
+      p.small_region = full->small_region;
+      const auto t0 = std::chrono::steady_clock::now();
+      (void)compile_program(net, &p, &layout, price != 0);
+      best = std::min(best, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
+    }
+    *(price ? priced : whole) = best;
+  }
+}
+
+// The lists that stay in LDS, run on the host: every tensor's elements carry the id of the tensor that was written
+// last.  Returns -1 if the path has no such lists, else the number of operand reads or writes that find another
+// tensor's elements, or lie outside LDS.
+extern "C" int64_t resident_overlaps(const tn_path* p) {
+  const ResProgram& R = p->res;
+  if (R.lists.empty()) return -1;
+  int64_t bad = 0;
+  for (const ResList& L : R.lists) {
+    std::vector<int64_t> owner(kResElems, -1);  // >= 0: result of that step; -2: an input element
+    std::vector<int> last_level(L.n_steps, 0);
+    for (int e = 0; e < L.n_copy; ++e) owner[e] = -2;
+    for (int lv = 0; lv < L.n_levels; ++lv) {
+      const ResLevel& V = R.levels[L.level0 + lv];
+      std::vector<int64_t> next = owner;  // a level's results are read from the next one on
+      std::vector<char> written(kResElems, 0), read(kResElems, 0);
+      for (int i = V.item0; i < V.item0 + V.n_items; ++i) {
+        const ResItem& it = R.items[i];
+        const int s = it.what & 255, j0 = (it.what >> 8) & 4095, qb = it.what >> 20;
+        const ResStep& st = R.steps[L.step0 + s];
+        for (int t = 0; t < (1 << (st.c_bits - qb)); ++t) {
+          const int o = j0 | (t << qb);
+          int a = st.a, b = st.b, a0 = it.a, b0 = it.b;
+          for (int q = 0; q < st.c_bits; ++q)
+            if ((o >> q) & 1) {
+              if (st.apos[q] >= 0) a |= 1 << st.apos[q];
+              if (st.bpos[q] >= 0) b |= 1 << st.bpos[q];
+            }
+          if (t == 0 && (a != a0 || b != b0)) ++bad;  // the item's own addresses
+          for (int k = 0; k < (1 << st.k_bits); ++k) {
+            int ak = a, bk = b;
+            for (int q = 0; q < st.k_bits; ++q)
+              if ((k >> q) & 1) {
+                ak |= 1 << st.ka[q];
+                bk |= 1 << st.kb[q];
+              }
+            for (int x : {ak, bk}) {
+              if (x < 0 || x >= kResElems || owner[x] == -1) ++bad;
+              else read[x] = 1;
+            }
+            // one owner per operand: that of its first element
+            if (ak < kResElems && owner[ak] != owner[st.a]) ++bad;
+            if (bk < kResElems && owner[bk] != owner[st.b]) ++bad;
+          }
+          if (st.c != kResOut) {
+            if (st.c + o >= kResElems || written[st.c + o]) ++bad;
+            else {
+              written[st.c + o] = 1;
+              next[st.c + o] = s;
+            }
+          }
+        }
+      }
+      for (int e = 0; e < kResElems; ++e) bad += written[e] && read[e];
+      owner = next;
+    }
+  }
+  return bad;
 }

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -135,6 +136,7 @@ static void prof_stop(hipStream_t s, hipEvent_t a, int kind, double bytes, doubl
 // ---------------------------------------------------------------------------
 struct DevNet {
   int device = -1;
+  void* block = nullptr;  // the allocation that holds every table
   DevTensor* tensors = nullptr;
   Recipe* recipes = nullptr;
   RecipeOp* ops = nullptr;
@@ -150,15 +152,44 @@ struct DevNet {
 // tables must exist before a capture starts (their upload is not a graph node)
 static thread_local bool g_capturing = false;
 
-template <typename T>
-static hipError_t upload(T** dst, const std::vector<T>& v) {
-  *dst = nullptr;
-  if (v.empty()) return hipSuccess;
-  if (g_capturing) return hipErrorStreamCaptureUnsupported;
-  hipError_t e = hipMalloc((void**)dst, sizeof(T) * v.size());
-  if (e != hipSuccess) return e;
-  return hipMemcpy(*dst, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice);
-}
+// The tables of a network or path in one allocation and one copy: a blocking copy of a few KB costs
+// 10 to 20 us and an allocation as much, and a path has up to 21 tables.
+struct TableBlock {
+  struct Part {
+    void** dst;
+    const void* src;
+    size_t bytes, off;
+  };
+  std::vector<Part> parts;
+  size_t total = 0;
+
+  template <typename T>
+  void add(T** dst, const std::vector<T>& v) {
+    *dst = nullptr;
+    if (v.empty()) return;
+    parts.push_back({(void**)dst, v.data(), sizeof(T) * v.size(), total});
+    total += (sizeof(T) * v.size() + 255) & ~(size_t)255;
+  }
+  // *block: what hipFree takes.  On an error nothing is set.
+  hipError_t place(void** block) {
+    *block = nullptr;
+    if (parts.empty()) return hipSuccess;
+    if (g_capturing) return hipErrorStreamCaptureUnsupported;
+    std::vector<char> host(total);
+    for (const Part& p : parts) memcpy(host.data() + p.off, p.src, p.bytes);
+    void* at = nullptr;
+    hipError_t e = hipMalloc(&at, total);
+    if (e != hipSuccess) return e;
+    e = hipMemcpy(at, host.data(), total, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      (void)hipFree(at);
+      return e;
+    }
+    for (const Part& p : parts) *p.dst = (char*)at + p.off;
+    *block = at;
+    return hipSuccess;
+  }
+};
 
 static tn_status ensure_device(tn_network* net, DevNet** out) {
   int dev = 0;
@@ -166,9 +197,9 @@ static tn_status ensure_device(tn_network* net, DevNet** out) {
   DevNet* d = (DevNet*)net->dev;
   if (d && d->device == dev) { *out = d; return TN_OK; }
   if (d) { device_release_network(net); }
-  d = new DevNet();
+  std::unique_ptr<DevNet> made(new DevNet());
+  d = made.get();
   d->device = dev;
-  net->dev = d;
   std::vector<DevTensor> ts;
   for (const TensorDef& t : net->tensors) {
     DevTensor x;
@@ -176,12 +207,13 @@ static tn_status ensure_device(tn_network* net, DevNet** out) {
     x.offset = t.offset; x.size = t.size;
     ts.push_back(x);
   }
-  HIP_TRY(upload(&d->tensors, ts));
-  HIP_TRY(upload(&d->recipes, net->recipes));
-  HIP_TRY(upload(&d->ops, net->ops));
-  HIP_TRY(upload(&d->mats, net->matrices));
-  HIP_TRY(upload(&d->sweep_recipes, net->sweep_recipes));
-  HIP_TRY(upload(&d->sweep_ops, net->sweep_ops));
+  TableBlock tables;
+  tables.add(&d->tensors, ts);
+  tables.add(&d->recipes, net->recipes);
+  tables.add(&d->ops, net->ops);
+  tables.add(&d->mats, net->matrices);
+  tables.add(&d->sweep_recipes, net->sweep_recipes);
+  tables.add(&d->sweep_ops, net->sweep_ops);
   std::vector<int32_t> sp;
   d->slot_of_gate.assign(net->sweep.size(), -1);
   for (size_t i = 0; i < net->sweep.size(); ++i)
@@ -198,7 +230,9 @@ static tn_status ensure_device(tn_network* net, DevNet** out) {
       if (sp[i] == p) ps.push_back((int32_t)i);
   }
   ps[net->n_params] = (int32_t)ps.size();
-  HIP_TRY(upload(&d->param_slots, ps));
+  tables.add(&d->param_slots, ps);
+  HIP_TRY(tables.place(&d->block));
+  net->dev = made.release();
   *out = d;
   return TN_OK;
 }
@@ -209,8 +243,7 @@ void device_release_network(tn_network* net) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(d->device);
-  (void)hipFree(d->tensors); (void)hipFree(d->recipes); (void)hipFree(d->ops); (void)hipFree(d->mats);
-  (void)hipFree(d->sweep_recipes); (void)hipFree(d->sweep_ops); (void)hipFree(d->param_slots);
+  (void)hipFree(d->block);
   (void)hipSetDevice(cur);
   delete d;
   net->dev = nullptr;
@@ -218,6 +251,7 @@ void device_release_network(tn_network* net) {
 
 struct DevPath {
   int device = -1;
+  void *block = nullptr, *adj_block = nullptr;  // the allocations that hold every table, and those of the reverse sweep
   SmallStep* steps = nullptr;
   int32_t* lists = nullptr;
   int32_t* levels = nullptr;
@@ -257,32 +291,35 @@ static tn_status ensure_path_device(tn_path* path, DevPath** out) {
   DevPath* d = (DevPath*)path->dev;
   if (d && d->device == dev) { *out = d; return TN_OK; }
   if (d) device_release_path(path);
-  d = new DevPath();
+  std::unique_ptr<DevPath> made(new DevPath());
+  d = made.get();
   d->device = dev;
-  path->dev = d;
+  TableBlock tables;
   if (!path->small_items.empty()) {  // (empty: the lists stay in LDS, or other passes take their steps)
-    HIP_TRY(upload(&d->steps, path->small_steps));
-    HIP_TRY(upload(&d->lists, path->small_lists));
-    HIP_TRY(upload(&d->levels, path->small_levels));
-    HIP_TRY(upload(&d->items, path->small_items));
+    tables.add(&d->steps, path->small_steps);
+    tables.add(&d->lists, path->small_lists);
+    tables.add(&d->levels, path->small_levels);
+    tables.add(&d->items, path->small_items);
   }
-  HIP_TRY(upload(&d->res_lists, path->res.lists));
-  HIP_TRY(upload(&d->res_levels, path->res.levels));
-  HIP_TRY(upload(&d->res_steps, path->res.steps));
-  HIP_TRY(upload(&d->res_items, path->res.items));
-  HIP_TRY(upload(&d->res_copy, path->res.copy));
-  HIP_TRY(upload(&d->sweep_gates, path->sweep_gates));
-  HIP_TRY(upload(&d->segments, path->segments));
-  HIP_TRY(upload(&d->sweep_val_src, path->sweep_val_src));
-  HIP_TRY(upload(&d->slice_tensors, path->slice_tensors));
-  HIP_TRY(upload(&d->reg_segs, path->reg_segs));
-  HIP_TRY(upload(&d->reg_ops, path->reg_ops));
-  HIP_TRY(upload(&d->reg_phases, path->reg_phases));
-  HIP_TRY(upload(&d->reg_words, path->reg_words));
-  HIP_TRY(upload(&d->seq_segs, path->seq.prog.segs));
-  HIP_TRY(upload(&d->seq_wins, path->seq.prog.wins));
-  HIP_TRY(upload(&d->seq_words, path->seq.prog.words));
-  HIP_TRY(upload(&d->seq_vals, path->seq.prog.vals));
+  tables.add(&d->res_lists, path->res.lists);
+  tables.add(&d->res_levels, path->res.levels);
+  tables.add(&d->res_steps, path->res.steps);
+  tables.add(&d->res_items, path->res.items);
+  tables.add(&d->res_copy, path->res.copy);
+  tables.add(&d->sweep_gates, path->sweep_gates);
+  tables.add(&d->segments, path->segments);
+  tables.add(&d->sweep_val_src, path->sweep_val_src);
+  tables.add(&d->slice_tensors, path->slice_tensors);
+  tables.add(&d->reg_segs, path->reg_segs);
+  tables.add(&d->reg_ops, path->reg_ops);
+  tables.add(&d->reg_phases, path->reg_phases);
+  tables.add(&d->reg_words, path->reg_words);
+  tables.add(&d->seq_segs, path->seq.prog.segs);
+  tables.add(&d->seq_wins, path->seq.prog.wins);
+  tables.add(&d->seq_words, path->seq.prog.words);
+  tables.add(&d->seq_vals, path->seq.prog.vals);
+  HIP_TRY(tables.place(&d->block));
+  path->dev = made.release();
   *out = d;
   return TN_OK;
 }
@@ -293,22 +330,8 @@ void device_release_path(tn_path* path) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(d->device);
-  (void)hipFree(d->steps);
-  (void)hipFree(d->lists);
-  (void)hipFree(d->levels);
-  (void)hipFree(d->items);
-  (void)hipFree(d->sweep_gates);
-  (void)hipFree(d->segments);
-  (void)hipFree(d->sweep_val_src);
-  (void)hipFree(d->slice_tensors);
-  for (void* p : {(void*)d->res_lists, (void*)d->res_levels, (void*)d->res_steps, (void*)d->res_items, (void*)d->res_copy,
-                  (void*)d->reg_segs, (void*)d->reg_ops, (void*)d->reg_phases, (void*)d->reg_words,
-                  (void*)d->adj_reg_segs, (void*)d->adj_reg_ops, (void*)d->adj_reg_phases, (void*)d->adj_reg_words,
-                  (void*)d->seq_segs, (void*)d->seq_wins, (void*)d->seq_words, (void*)d->seq_vals, (void*)d->adj_seq_segs,
-                  (void*)d->adj_seq_wins, (void*)d->adj_seq_words, (void*)d->adj_seq_vals})
-    (void)hipFree(p);
-  (void)hipFree(d->adj_gates);
-  (void)hipFree(d->adj_segments);
+  (void)hipFree(d->block);
+  (void)hipFree(d->adj_block);
   (void)hipSetDevice(cur);
   delete d;
   path->dev = nullptr;
@@ -1517,11 +1540,13 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     DevPath* dp;
     if ((st = ensure_path_device(path, &dp)) != TN_OK) return st;
     const SeqProgram& pr = path->adj_seq;
-    if (!dp->adj_seq_segs) {
-      HIP_TRY(upload(&dp->adj_seq_segs, pr.segs));
-      HIP_TRY(upload(&dp->adj_seq_wins, pr.wins));
-      HIP_TRY(upload(&dp->adj_seq_words, pr.words));
-      HIP_TRY(upload(&dp->adj_seq_vals, pr.vals));
+    if (!dp->adj_block) {
+      TableBlock tables;
+      tables.add(&dp->adj_seq_segs, pr.segs);
+      tables.add(&dp->adj_seq_wins, pr.wins);
+      tables.add(&dp->adj_seq_words, pr.words);
+      tables.add(&dp->adj_seq_vals, pr.vals);
+      HIP_TRY(tables.place(&dp->adj_block));
     }
     const int bits = (int)path->final_bits.size();
     n_cols = seq_adjoint_columns(pr.passes[0], bits);
@@ -1555,13 +1580,15 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
     // fused passes: both states stream through LDS once per pass
     DevPath* dp;
     if ((st = ensure_path_device(path, &dp)) != TN_OK) return st;
-    if (!dp->adj_gates) {
-      HIP_TRY(upload(&dp->adj_gates, path->adj_gates));
-      HIP_TRY(upload(&dp->adj_segments, path->adj_segments));
-      HIP_TRY(upload(&dp->adj_reg_segs, path->adj_reg_segs));
-      HIP_TRY(upload(&dp->adj_reg_ops, path->adj_reg_ops));
-      HIP_TRY(upload(&dp->adj_reg_phases, path->adj_reg_phases));
-      HIP_TRY(upload(&dp->adj_reg_words, path->adj_reg_words));
+    if (!dp->adj_block) {
+      TableBlock tables;
+      tables.add(&dp->adj_gates, path->adj_gates);
+      tables.add(&dp->adj_segments, path->adj_segments);
+      tables.add(&dp->adj_reg_segs, path->adj_reg_segs);
+      tables.add(&dp->adj_reg_ops, path->adj_reg_ops);
+      tables.add(&dp->adj_reg_phases, path->adj_reg_phases);
+      tables.add(&dp->adj_reg_words, path->adj_reg_words);
+      HIP_TRY(tables.place(&dp->adj_block));
     }
     const int bits = (int)path->final_bits.size();
     n_cols = adjoint_blocks(path->adj_passes[0], bits);

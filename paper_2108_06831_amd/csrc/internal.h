@@ -649,6 +649,9 @@ std::shared_ptr<tn_network> sliced_network(const tn_network* net, const std::vec
 tn_status slice_gather_tables(const tn_network* net, const tn_network* sliced, const std::vector<int32_t>& slice_modes,
                               std::vector<SliceTensor>* out);
 // network.cpp
+// Gradient slots, one per parametric gate of the sweep in circuit order: of each gate (or -1), and of each
+// parameter p as param_slots[param_slots[p] .. param_slots[p + 1]).  Returns their number.
+int gradient_slots(const tn_network& net, std::vector<int32_t>* slot_of_gate, std::vector<int32_t>* param_slots);
 void network_values_host(const tn_network* net, const double* params, const uint64_t* bits, double* out);
 // runtime
 void device_release_network(tn_network* net);

@@ -117,6 +117,24 @@ void network_values_host(const tn_network* net, const double* params, const uint
   }
 }
 
+int gradient_slots(const tn_network& net, std::vector<int32_t>* slot_of_gate, std::vector<int32_t>* param_slots) {
+  slot_of_gate->assign(net.sweep.size(), -1);
+  std::vector<int32_t> next(net.n_params + 1, 0);  // slots of the parameters before p, then where p's next one goes
+  int n = 0;
+  for (size_t i = 0; i < net.sweep.size(); ++i)
+    if (net.sweep[i].gen != GEN_NONE) {
+      (*slot_of_gate)[i] = n++;
+      next[net.sweep[i].param + 1]++;
+    }
+  for (int p = 0; p < net.n_params; ++p) next[p + 1] += next[p];
+  for (int32_t& x : next) x += net.n_params + 1;
+  *param_slots = next;  // the table of starts
+  param_slots->resize(net.n_params + 1 + n);
+  for (size_t i = 0; i < net.sweep.size(); ++i)
+    if ((*slot_of_gate)[i] >= 0) (*param_slots)[next[net.sweep[i].param]++] = (*slot_of_gate)[i];
+  return n;
+}
+
 }  // namespace tnq
 
 using namespace tnq;

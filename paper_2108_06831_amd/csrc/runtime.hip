@@ -214,22 +214,8 @@ static tn_status ensure_device(tn_network* net, DevNet** out) {
   tables.add(&d->mats, net->matrices);
   tables.add(&d->sweep_recipes, net->sweep_recipes);
   tables.add(&d->sweep_ops, net->sweep_ops);
-  std::vector<int32_t> sp;
-  d->slot_of_gate.assign(net->sweep.size(), -1);
-  for (size_t i = 0; i < net->sweep.size(); ++i)
-    if (net->sweep[i].gen != GEN_NONE) {
-      d->slot_of_gate[i] = (int32_t)sp.size();
-      sp.push_back(net->sweep[i].param);
-    }
-  d->n_slots = (int)sp.size();
-  // the slots of each parameter, in order, behind a table of their starts
-  std::vector<int32_t> ps(net->n_params + 1, 0);
-  for (int p = 0; p < net->n_params; ++p) {
-    ps[p] = (int32_t)ps.size();
-    for (size_t i = 0; i < sp.size(); ++i)
-      if (sp[i] == p) ps.push_back((int32_t)i);
-  }
-  ps[net->n_params] = (int32_t)ps.size();
+  std::vector<int32_t> ps;
+  d->n_slots = gradient_slots(*net, &d->slot_of_gate, &ps);
   tables.add(&d->param_slots, ps);
   HIP_TRY(tables.place(&d->block));
   net->dev = made.release();

@@ -107,3 +107,13 @@ extern "C" int64_t resident_overlaps(const tn_path* p) {
   }
   return bad;
 }
+
+// The gradient slots of a network; table: room for n_params + 1 + slots entries (may be NULL); returns the slots.
+extern "C" int slot_table(const tn_network* net, int32_t* table, double* seconds) {
+  std::vector<int32_t> of_gate, t;
+  const auto t0 = std::chrono::steady_clock::now();
+  const int n = gradient_slots(*net, &of_gate, &t);
+  *seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  if (table) std::copy(t.begin(), t.end(), table);
+  return n;
+}

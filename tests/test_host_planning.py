@@ -93,3 +93,35 @@ def test_resident_lists_keep_tensors_apart(internals, seed):
     net = Network.from_circuit(workloads.brickwork(n, int(rng.integers(2, 7)), rng), fuse=[False, "dense", "split"][seed % 3])
     path = net.plan("greedy")
     assert internals.resident_overlaps(path.handle) == 0
+
+
+def test_gradient_slots_of_shared_parameters(internals):
+    """Slots are numbered in circuit order, and a parameter's are listed in that order; some parameters
+    are read by several gates, some by none."""
+    rng = np.random.default_rng(3)
+    reads = [int(x) for x in rng.integers(0, 7, size=40) if x != 4]
+    gates = []
+    for i, p in enumerate(reads):
+        gates += [workloads.Gate("H", (i % 3,)), workloads.Gate(["RX", "RZ"][i % 2], (i % 3,), (0.0,), (p,))]
+    net = Network.from_circuit(workloads.Circuit(3, gates, 7))
+    table, seconds = (ctypes.c_int32 * (8 + len(reads)))(), ctypes.c_double()
+    assert internals.slot_table(net.handle, table, ctypes.byref(seconds)) == len(reads)
+    for p in range(7):
+        assert list(table[table[p]:table[p + 1]]) == [i for i, q in enumerate(reads) if q == p]
+    none = Network.from_circuit(workloads.Circuit(2, [workloads.Gate("H", (0,)), workloads.Gate("CZ", (0, 1))], 0))
+    one = (ctypes.c_int32 * 1)()
+    assert internals.slot_table(none.handle, one, ctypes.byref(seconds)) == 0 and one[0] == 1
+
+
+def test_gradient_slots_take_linear_time(internals):
+    """The table of a circuit of 40000 parameters costs less than building its network (by far); a
+    search of all slots for each parameter costs several times as much as building it."""
+    n = 40000
+    circ = workloads.Circuit(4, [workloads.Gate("RX", (i % 4,), (0.0,), (i,)) for i in range(n)], n)
+    t = time.perf_counter()
+    net = Network.from_circuit(circ)
+    build = time.perf_counter() - t
+    seconds = ctypes.c_double()
+    best = min((internals.slot_table(net.handle, None, ctypes.byref(seconds)), seconds.value)[1] for _ in range(3))
+    print(f"build {build:.3f} s, table {best:.4f} s")
+    assert best < 0.25 * build

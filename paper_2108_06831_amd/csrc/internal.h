@@ -3,6 +3,7 @@
 #pragma once
 #include <stdint.h>
 
+#include <algorithm>
 #include <memory>
 #include <string>
 #include <vector>
@@ -612,6 +613,11 @@ struct tn_path {
 };
 
 namespace tnq {
+// The first step with a launch of its own: those before it are the interpreter's, an ordered pass's, or merges of |0>
+// vectors that a chain from |0...0> does not need.
+inline int first_launched_step(const tn_path* path) {
+  return std::max({path->n_small, path->seq.end, path->zero_steps});
+}
 // planner.cpp
 tn_status plan_order(const tn_network* net, const tn_plan_opts& opts, std::vector<int32_t>& pairs,
                      double* max_log2_out, double alpha = 1.0, double temp = 0.0, uint64_t seed = 0);

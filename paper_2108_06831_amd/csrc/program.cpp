@@ -1507,7 +1507,7 @@ tn_status compile_program(const tn_network* net, tn_path* path, const std::vecto
     }
   }
   st.n_product_launches = 0;
-  for (int s = std::max({path->n_small, path->seq.end, path->zero_steps}), run0 = -1, run_len = 0; s < S; ++s) {
+  for (int s = first_launched_step(path), run0 = -1, run_len = 0; s < S; ++s) {
     const StepProgram& P = path->steps[s];
     if (P.chain != -1) {
       run0 = -1;

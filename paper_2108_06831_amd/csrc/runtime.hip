@@ -476,7 +476,7 @@ static tn_status run_steps_body(hipStream_t s, tn_path* path, const Bases& B, in
     for (int i = 0; i < path->n_small; ++i) { fl += path->steps[i].flops; by += path->steps[i].bytes; }
     prof_stop(s, ev, TN_KERNEL_INTERP, by * batch, fl * batch);
   }
-  for (size_t si = std::max({path->n_small, seq_end, path->zero_steps}); si < path->steps.size(); ++si) {
+  for (size_t si = B.pair_a ? 0 : first_launched_step(path); si < path->steps.size(); ++si) {
     const StepProgram& P = path->steps[si];
     if (P.chain == -2) continue;
     if (P.chain >= 0) {
@@ -1748,13 +1748,14 @@ extern "C" tn_status tn_autotune(void* stream, int32_t precision, tn_network* ne
   // products that share a launch keep their shape: alone, another shape would
   // have to save more than the launch it adds
   std::vector<char> grouped(path->steps.size(), 0);
-  for (size_t si = path->n_small; si < path->steps.size();) {
+  const size_t launched = first_launched_step(path);
+  for (size_t si = launched; si < path->steps.size();) {
     const size_t e = group_end(path, si, precision);
     if (e - si >= 2)
       for (size_t t = si; t < e; ++t) grouped[t] = 1;
     si = e;
   }
-  for (size_t si = 0; si < path->steps.size() && result == TN_OK; ++si) {
+  for (size_t si = launched; si < path->steps.size() && result == TN_OK; ++si) {
     StepProgram& P = path->steps[si];
     if (P.kind != SK_GEMM || P.chain != -1) continue;
     auto time_shape = [&](const GemmDesc& g, int tile, int split, double* sec) -> hipError_t {

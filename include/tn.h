@@ -386,9 +386,14 @@ void tn_graph_destroy(tn_graph* graph);
  * 128x64 or 64x64 in the 3M form, K cut into 1, 2, 4 or 8 ranges
  * where the step's result is small, the one-output-per-thread vector kernel
  * where K <= 1024, each for C = A B and for C = B^T A^T -- over `reps` launches (hipEvents on `stream`) and
- * keeps the fastest in the path for `precision`.  Synchronises the stream.
+ * keeps the fastest in the path for `precision`.  Only products that a call
+ * launches by themselves are timed.  Synchronises the stream.
  * Later contractions along the path give the same results up to rounding
- * order (a K split sums partial products in another order).
+ * order (a K split sums partial products in another order; the 3M form rounds
+ * imaginary parts to the magnitude of the real ones).  The tuner
+ * may take the 3M form where the defaults do not, and in BF16X3 it may change
+ * the order of sums that they keep, which shows in the last of an operand's
+ * two parts (2^-17).
  *   workspace_dev: >= tn_workspace_bytes(net, path, batch) bytes (contents
  *   overwritten);  report (may be NULL): number of product steps, steps whose
  *   shape changed, and the sum of their measured times before and after.
@@ -405,9 +410,9 @@ tn_status tn_autotune(void* stream, int32_t precision, tn_network* net, tn_path*
  * given, e.g. to restore shapes tuned earlier.  tile: 0..3 = MFMA tiles
  * 128x64, 128x32, 64x64, 64x32 complex in the real-embedding (4M) form;
  * 4 = vector kernel (K <= 1024 only, split 1); 5, 6 = MFMA tiles 128x64,
- * 64x64 in the three-product (3M) form (TN_PREC_C64 only); 7 = 3M,
+ * 64x64 in the three-product (3M) form (TN_PREC_C64 only); 7 = 4M,
  * batch-packed: four batch items of at most 32 x 32 per workgroup, one per
- * wave (TN_PREC_C64, M and N <= 32, a batch of at least 4 only); 8 = 3M,
+ * wave (TN_PREC_C64, M and N <= 32, a batch of at least 4 only); 8 = 4M,
  * column-packed: M <= 32 and four 32-column slices of N per workgroup, one
  * per wave (TN_PREC_C64, N >= 64 only).
  * split: 1, 2, 4 or 8, dividing K, at most the step's reserved

@@ -368,10 +368,10 @@ struct GemmDesc {
   BufRef tmp;
 };
 // tiles 0-3: real-embedding (4M) MFMA tiles; 4: vector kernel; 5-6: 3M MFMA
-// tiles (FP32 only); 7: 3M, batch-packed (four batch items of at most 32 x 32
-// per block, one per wave; batch of at least 4, FP32 only); 8: 3M,
-// column-packed (M <= 32, four 32-column slices of N per block, one per wave;
-// FP32 only)
+// tiles (FP32 only); 7: batch-packed (four batch items of at most 32 x 32
+// per block, one per wave; batch of at least 4, FP32 only); 8: column-packed
+// (M <= 32, four 32-column slices of N per block, one per wave; FP32 only),
+// both with the four products of 4M
 constexpr int kGemmVector = 4;
 constexpr int kGemmBatchPacked = 7;
 constexpr int kGemmColumnPacked = 8;

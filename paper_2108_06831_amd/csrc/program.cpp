@@ -1788,11 +1788,36 @@ void gemm_tile_by_blocks(const GemmDesc& g, int* tile, int* split) {
   *split = sp;
 }
 
+// how many of C's lowest five address bits are column bits, in order
+static int low_columns(const GemmDesc& g) {
+  int c = 0;
+  while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
+  return c;
+}
+
+// The launch shape that the planner's model prices: by the sizes alone, so that a plan does not move with the rules
+// above (another plan is another order of sums, which a BF16x3 result shows).
+static int model_shape(const GemmDesc (&gm)[2], int* tile, int* split) {
+  int tl[2], sp[2];
+  for (int o = 0; o < 2; ++o) {
+    gemm_tile_by_blocks(gm[o], &tl[o], &sp[o]);
+    if ((tl[o] == 0 || tl[o] == 2) && gm[o].N >= 64) tl[o] = tl[o] == 0 ? 5 : 6;
+  }
+  const int o = gm[0].K <= 32 && tl[0] != kGemmVector && tl[1] != kGemmVector && low_columns(gm[1]) > low_columns(gm[0]) ? 1 : 0;
+  *tile = tl[o];
+  *split = sp[o];
+  return o;
+}
+
 // Default launch shapes of a product for `prec`, set in both orientations; returns the one to run.
 // The figures are microseconds per call of the product alone (M x N x K), the line's choice last.
 int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
   const bool c64 = prec == TN_PREC_C64;
   const int64_t K = gm[0].K, out = gm[0].batch * gm[0].M * gm[0].N, work = out * K;
+  // An FP32 result takes three real products only where the shapes that follow from the sizes alone do (model_shape).
+  int model_tile, model_split;
+  model_shape(gm, &model_tile, &model_split);
+  const bool three = model_tile > kGemmVector;
   for (GemmDesc& g : gm) {
     const int64_t lo = std::min(g.M, g.N), hi = std::max(g.M, g.N);
     int tile, split;
@@ -1820,13 +1845,13 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
         gemm_tile_supported(g, kGemmColumnPacked))
       tile = kGemmColumnPacked;
     if (tile < kGemmVector && g.M >= 64 && g.N >= 64) {
-      // 64 x 64 tiles in the three-product form once they give every compute unit one: 1024 x 1024 x 128 23.4 in
-      // 64 x 32, 20.9; 512 x 512 x 512 28.8, 25.4 in four ranges of K
+      // 64 x 64 tiles once they give every compute unit one: 1024 x 1024 x 128 23.4 in 64 x 32, 19.8 in four real
+      // products, 18.2 in three; 512 x 512 x 512 29.8, 25.8 and 23.7; 4 x 1024 x 512 x 256 60.8 in 128 x 32, 43.2, 35.5
       const int64_t blocks = ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
       int sp = 1;
       while (sp < g.max_split && blocks * sp < 256 && K / (sp * 2) >= 64 && K % (sp * 2) == 0) sp *= 2;
       if (c64 && blocks * sp >= 256) {
-        tile = 6;
+        tile = three ? 6 : 2;
         split = sp;
       }
       // BF16x3 takes the largest tile that fills the chip (1024 x 4096 x 128: 39.8 in 64 x 64, 35.4), if the product
@@ -1856,13 +1881,6 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
   return work > ((int64_t)1 << 23) && waste(gm[1]) < waste(gm[0]) ? 1 : 0;
 }
 
-// how many of C's lowest five address bits are column bits, in order
-static int low_columns(const GemmDesc& g) {
-  int c = 0;
-  while (c < g.nbn && c < 5 && g.c_n[c] == c) ++c;
-  return c;
-}
-
 // One output per thread or tiles, ranges of K and orientation by the sizes alone, with k in its own order.  (A tile's
 // size does not change a sum.)
 int gemm_fixed_sum(GemmDesc (&gm)[2]) {
@@ -1877,20 +1895,6 @@ int gemm_fixed_sum(GemmDesc (&gm)[2]) {
                  low_columns(gm[1]) > low_columns(gm[0])
              ? 1
              : 0;
-}
-
-// The launch shape that the planner's model prices: by the sizes alone, so that a plan does not move with the rules
-// above (another plan is another order of sums, which a BF16x3 result shows).
-static int model_shape(const GemmDesc (&gm)[2], int* tile, int* split) {
-  int tl[2], sp[2];
-  for (int o = 0; o < 2; ++o) {
-    gemm_tile_by_blocks(gm[o], &tl[o], &sp[o]);
-    if ((tl[o] == 0 || tl[o] == 2) && gm[o].N >= 64) tl[o] = tl[o] == 0 ? 5 : 6;
-  }
-  const int o = gm[0].K <= 32 && tl[0] != kGemmVector && tl[1] != kGemmVector && low_columns(gm[1]) > low_columns(gm[0]) ? 1 : 0;
-  *tile = tl[o];
-  *split = sp[o];
-  return o;
 }
 
 double modeled_seconds(const tn_path* path) {

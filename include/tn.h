@@ -390,10 +390,10 @@ void tn_graph_destroy(tn_graph* graph);
  * launches by themselves are timed.  Synchronises the stream.
  * Later contractions along the path give the same results up to rounding
  * order (a K split sums partial products in another order; the 3M form rounds
- * imaginary parts to the magnitude of the real ones).  The tuner
- * may take the 3M form where the defaults do not, and in BF16X3 it may change
- * the order of sums that they keep, which shows in the last of an operand's
- * two parts (2^-17).
+ * imaginary parts to the magnitude of the real ones).  The default shapes
+ * take neither a longer sum nor the 3M form for speed; the tuner may, and in
+ * BF16X3 it may change the order that the defaults keep, which shows in the
+ * last of an operand's two parts (2^-17).
  *   workspace_dev: >= tn_workspace_bytes(net, path, batch) bytes (contents
  *   overwritten);  report (may be NULL): number of product steps, steps whose
  *   shape changed, and the sum of their measured times before and after.

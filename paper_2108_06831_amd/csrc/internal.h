@@ -402,6 +402,11 @@ constexpr int kElemSkinnyBits = 15;
 inline bool elem_group_shape(int out_bits, int m_bits, int n_bits, int k_bits) {
   return out_bits <= kElemSmallBits && k_bits <= kElemKBits && (m_bits < 6 || n_bits < 5 || k_bits <= 5);
 }
+// log2 of the adjacent lanes that share one result's sum there: sums of 128 terms and more, about eight terms a lane
+// (at most 32 lanes, and at most 2^20 threads for a product)
+inline int elem_lane_bits(int out_bits, int k_bits) {
+  return k_bits >= 7 ? std::max(0, std::min({k_bits - 3, 5, 20 - out_bits})) : 0;
+}
 // default launch shapes of a product's two orientations for a precision (before any measurement);
 // returns the orientation to run
 int gemm_default_launch(GemmDesc (&gm)[2], int prec);

@@ -1760,11 +1760,8 @@ hipError_t launch_elem_group(hipStream_t s, const ElemGroupArgs& a, int batch, i
     ElemMember& m = g.m[i];
     if (m.out_bits < 0 || m.out_bits > kElemGroupOutBits || m.k_bits < 0 || m.k_bits > kElemKBits)
       return hipErrorInvalidValue;
-    // one thread per result, or for sums of 128 terms and more 2^lane_bits
-    // lanes per result, about eight terms each (at most 32 lanes, and at most
-    // 2^20 threads for the member)
-    int lb = m.k_bits >= 7 ? std::min(m.k_bits - 3, 5) : 0;
-    while (lb > 0 && m.out_bits + lb > 20) --lb;
+    // one thread per result, or 2^lane_bits lanes for a long sum
+    const int lb = elem_lane_bits(m.out_bits, m.k_bits);
     m.lane_bits = lb;
     m.block0 = blocks;
     blocks += (int32_t)((((int64_t)1 << (m.out_bits + lb)) + kThreads - 1) / kThreads);
@@ -1776,18 +1773,30 @@ hipError_t launch_elem_group(hipStream_t s, const ElemGroupArgs& a, int batch, i
   return hipLaunchKernel(fn, dim3((unsigned)blocks, batch), dim3(kThreads), args, 0, s);
 }
 
-// C[i] = sum over s of partial[s][i] (split-K), contiguous per parameter vector
-__global__ void k_sum_partials(const float2* part, int64_t part_bs, int split, int64_t n, float2* C, int64_t c_bs) {
+// C[i] = sum over s of partial[s][i] (split-K), contiguous per parameter vector: in pairs (PAIRS), which rounds an
+// element log2 SPLIT times instead of SPLIT - 1, or in turn where BF16x3 results keep their order of sums.
+template <int SPLIT, bool PAIRS>
+__global__ void k_sum_partials(const float2* part, int64_t part_bs, int64_t n, float2* C, int64_t c_bs) {
   const int z = blockIdx.y;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+    float2 v[SPLIT];
+#pragma unroll
+    for (int s = 0; s < SPLIT; ++s) v[s] = part[(int64_t)z * part_bs + (int64_t)s * n + i];
+#pragma unroll
+    for (int h = 1; h < SPLIT; h *= 2)
+#pragma unroll
+      for (int s = 0; s < SPLIT; s += 2 * h)
+        if (PAIRS) v[s] = f2(v[s].x + v[s + h].x, v[s].y + v[s + h].y);
     float2 acc = f2(0.f, 0.f);
-    for (int s = 0; s < split; ++s) {
-      const float2 v = part[(int64_t)z * part_bs + (int64_t)s * n + i];
-      acc.x += v.x;
-      acc.y += v.y;
-    }
+#pragma unroll
+    for (int s = 0; s < (PAIRS ? 1 : SPLIT); ++s) acc = f2(acc.x + v[s].x, acc.y + v[s].y);
     C[(int64_t)z * c_bs + i] = acc;
   }
+}
+
+template <bool PAIRS>
+static void* sum_fn(int split) {
+  return split == 2 ? (void*)k_sum_partials<2, PAIRS> : split == 4 ? (void*)k_sum_partials<4, PAIRS> : (void*)k_sum_partials<8, PAIRS>;
 }
 
 template <int TM, int TN, int F>
@@ -1985,7 +1994,8 @@ hipError_t launch_gemm(hipStream_t s, const GemmDesc& desc, int tile, int split,
   }
   TileArgs g;
   split = split > 1 ? split : 1;
-  if (split > 1 && (d.K % split != 0 || split > d.max_split || !tmp)) return hipErrorInvalidValue;
+  if (split > 1 && (d.K % split != 0 || split > d.max_split || !tmp || (split != 2 && split != 4 && split != kGemmMaxSplit)))
+    return hipErrorInvalidValue;
   g.A = a; g.B = b;
   g.C = split > 1 ? tmp : c;
   g.a_bs = a_bs; g.b_bs = b_bs;
@@ -2018,9 +2028,10 @@ hipError_t launch_gemm(hipStream_t s, const GemmDesc& desc, int tile, int split,
   if (e != hipSuccess || split == 1) return e;
   int64_t rb = (c_elems + kThreads - 1) / kThreads;
   if (rb > 16384) rb = 16384;
-  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)rb, batch), dim3(kThreads), 0, s, tmp, tmp_bs, split, c_elems,
-                     c, c_bs);
-  return hipGetLastError();
+  const float2* part = tmp;
+  void* sum_args[] = {&part, &tmp_bs, (void*)&c_elems, &c, &c_bs};
+  return hipLaunchKernel(precision == TN_PREC_BF16X3 ? sum_fn<false>(split) : sum_fn<true>(split),
+                         dim3((unsigned)rb, batch), dim3(kThreads), sum_args, 0, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -1814,10 +1814,16 @@ static int model_shape(const GemmDesc (&gm)[2], int* tile, int* split) {
 int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
   const bool c64 = prec == TN_PREC_C64;
   const int64_t K = gm[0].K, out = gm[0].batch * gm[0].M * gm[0].N, work = out * K;
-  // An FP32 result takes three real products only where the shapes that follow from the sizes alone do (model_shape).
-  int model_tile, model_split;
-  model_shape(gm, &model_tile, &model_split);
+  // An FP32 result is rounded no more often than in the shapes that follow from the sizes alone (model_shape): three
+  // products only where those take them, and K in as many parts, which are that shape's ranges or, on the per-output
+  // kernel, the lanes that share a sum (8 x 8 x 512 x 256: relative error 1.0e-7 in 32 lanes, 4.1e-7 along a tile's
+  // K).  A tile takes that many ranges where it may (8 x 8 x 4096 x 512: 281 in lanes, 59 in one range, 55 in four;
+  // 8 x 16 x 1024 x 512: 143, 43, 24 in eight); else the sum stays in lanes.
+  int model_tile, parts;
+  model_shape(gm, &model_tile, &parts);
   const bool three = model_tile > kGemmVector;
+  if (model_tile == kGemmVector) parts = 1 << elem_lane_bits(gm[0].nbb + gm[0].nbm + gm[0].nbn, gm[0].nbk);
+  if (!c64) parts = 1;
   for (GemmDesc& g : gm) {
     const int64_t lo = std::min(g.M, g.N), hi = std::max(g.M, g.N);
     int tile, split;
@@ -1827,7 +1833,8 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
     // lanes per output there: 128 x 128 x 128 9.9 in tiles, 6.8; 64 x 64 x 256 11.4, 7.4; 512 x 128 x 512 is left
     // to tiles (13.9).
     if ((K <= 8 && work <= ((int64_t)1 << 19)) || (K <= 32 && work <= ((int64_t)1 << 18)) ||
-        (K >= 128 && K <= kElemMaxK && work <= ((int64_t)1 << 21)))
+        (K >= 128 && K <= kElemMaxK && work <= ((int64_t)1 << 21)) ||
+        (model_tile == kGemmVector && parts > g.max_split))
       tile = kGemmVector;
     // Else a tile, also half empty: 32 x 1024 x 32 9.4, 5.8; 8 x 32 x 2048 x 8 16.2, 6.0; 256 x 256 x 32 9.5, 5.6;
     // 8 x 4096 x 512 42 either way
@@ -1836,7 +1843,7 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
     if (tile == kGemmVector) split = 1;
     // batches of small products, four per block: 4096 x 32 x 32 x 32 of a 32-qubit amplitude batch 369 -> 258 for the
     // whole pass, 4096 x 8 x 32 x 32 258 -> 239, 4096 x 32 x 32 x 8 420 -> 393
-    if (tile == kGemmVector && g.batch >= 64 && g.M <= 32 && g.N <= 32 && g.M * g.N >= 256 && K >= 8 &&
+    if (tile == kGemmVector && parts == 1 && g.batch >= 64 && g.M <= 32 && g.N <= 32 && g.M * g.N >= 256 && K >= 8 &&
         K <= kElemMaxK && out >= ((int64_t)1 << 18) && work > ((int64_t)1 << 23))
       tile = c64 && gemm_tile_supported(g, kGemmBatchPacked) ? kGemmBatchPacked : kGemmVector - 1;  // (64 x 32: 269)
     // a short side against a very long one, four 32-column slices per block: 1024 x 16 x 1024 x 16 98 in 64 x 32, 87;
@@ -1865,6 +1872,7 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
                              ((g.N + kGemmTileN[tile] - 1) / kGemmTileN[tile]);
       while (split < g.max_split && blocks * split < 128 && K / (split * 2) >= 64 && K % (split * 2) == 0) split *= 2;
       while (split > 1 && (K < 256 || K / split < 64 || (blocks * split >= 1024 && K / split < 256))) split /= 2;
+      split = std::max(split, std::min(parts, g.max_split));
     }
     g.tile[prec] = tile;
     g.split[prec] = split;

@@ -1560,7 +1560,8 @@ extern "C" tn_status tn_backward(void* stream, int32_t precision, tn_network* ne
       HIP_TRY(launch_seq_adjoint(s, ps, bits, rt, umats, (int64_t)net->sweep.size() * 16, psi, pbs, lam, lbs, batch,
                                  parts, pstride, precision));
     }
-    prof_stop(s, ev, TN_KERNEL_ADJOINT, 32.0 * (double)n * pr.passes.size() * batch, fl * batch);
+    // one chunk: psi is read once, and written before that if the launch forms it; lambda stays on chip
+    prof_stop(s, ev, TN_KERNEL_ADJOINT, (one ? both ? 16.0 : 8.0 : 32.0 * pr.passes.size()) * (double)n * batch, fl * batch);
   }
   if (path->adj_state == 1) {
     // fused passes: both states stream through LDS once per pass

@@ -380,9 +380,8 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
   __shared__ __attribute__((aligned(16))) float2 vwin[kSeqWinVals];  // the window's values (a reverse sweep's conjugated)
   __shared__ uint32_t wwin[kSeqWinWords];
   const int z = blockIdx.y, lane = threadIdx.x & 63;
-  // chunks of fewer than 2^10 elements leave threads of the wave without elements: they repeat others
+  // chunks of fewer than 2^10 elements (forward) leave threads of the wave without elements: they repeat others
   const int n_thr = 1 << (a.l - 4), tid = threadIdx.x & (n_thr - 1);
-  const bool active = (int)threadIdx.x < n_thr;
   const uint32_t base = (uint32_t)deposit(blockIdx.x, a.rest, a.n_rest);
   const float2* V = vals + (int64_t)z * a.vals_bs;
   float2* P = const_cast<float2*>(a.in) + (int64_t)z * a.in_bs;
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(1 << (LMAX - 4)) void k_seq_pass(SeqArgs a, const S
   const int col = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   double* part = a.partials + (int64_t)z * a.pstride + col;
   auto add_grad = [&](int slot, double v) {
-    v = wave_sum_d(active ? v : 0.0);
+    v = wave_sum_d(v);
     if (lane == 63) part[(int64_t)slot * kReduceBlocks] = v;
   };
   float2 x[16], y[16];  // psi (or the state), lambda
@@ -529,12 +528,14 @@ template <int PREC, int NS>
 void seq_launch(hipStream_t s, const SeqArgs& a, const SeqTables& t, const SeqPass& ps, const float2* vals, int chunks,
                 int batch) {
   const dim3 grid(chunks, batch), block(std::max(64, 1 << (ps.l - 4)));
-  if (ps.l <= 12)
-    hipLaunchKernelGGL((k_seq_pass<PREC, NS, 12>), grid, block, 0, s, a, t.segs + ps.first_seg, t.wins + ps.first_win,
-                       t.words, t.vals, vals);
-  else
-    hipLaunchKernelGGL((k_seq_pass<PREC, NS, NS == 2 ? kSeqAdjMaxLocal : kSeqMaxLocal>), grid, block, 0, s, a,
-                       t.segs + ps.first_seg, t.wins + ps.first_win, t.words, t.vals, vals);
+  if constexpr (NS == 1)
+    if (ps.l <= 12) {
+      hipLaunchKernelGGL((k_seq_pass<PREC, NS, 12>), grid, block, 0, s, a, t.segs + ps.first_seg, t.wins + ps.first_win,
+                         t.words, t.vals, vals);
+      return;
+    }
+  hipLaunchKernelGGL((k_seq_pass<PREC, NS, NS == 2 ? kSeqAdjMaxLocal : kSeqMaxLocal>), grid, block, 0, s, a,
+                     t.segs + ps.first_seg, t.wins + ps.first_win, t.words, t.vals, vals);
 }
 
 // the pass's chunk and the bits outside it (out_pos[p]: position of address bit p in the result, NULL: p)
@@ -641,7 +642,9 @@ hipError_t launch_seq_adjoint(hipStream_t s, const SeqPass& ps, int bits, const 
   a.vals_bs = u_bs;
   a.partials = partials;
   a.pstride = partial_stride;
-  if (!seq_args(ps, bits, kSeqAdjMaxLocal, nullptr, &a) || seq_adjoint_columns(ps, bits) > kReduceBlocks)
+  // (a state of one chunk is launch_seq_gradient's, so a chunk here is never less than the widest)
+  if (!seq_args(ps, bits, kSeqAdjMaxLocal, nullptr, &a) || ps.l != kSeqAdjMaxLocal ||
+      seq_adjoint_columns(ps, bits) > kReduceBlocks)
     return hipErrorInvalidValue;
   if (precision == TN_PREC_BF16X3) seq_launch<TN_PREC_BF16X3, 2>(s, a, t, ps, u, 1 << a.n_rest, batch);
   else seq_launch<TN_PREC_C64, 2>(s, a, t, ps, u, 1 << a.n_rest, batch);

@@ -224,7 +224,8 @@ struct RegOp {
   int32_t gform[4];     // adjoint dense, per register bit: AdjForm of the generator
   float g0[4], g1[4];   // adjoint, per register bit: DIAG the generator's entries; dense with ADJ_GEN_X its factor in g0
   int32_t tot;          // COUNT: per register bit (bytes) its edges to address bits
-  int32_t pc[3];        // COUNT: edges between register bits, per unordered pair (bytes, see count_pair)
+  int32_t pc[2];        // COUNT: edges between register bits, a byte per pair (01 02 03 12 | 13 23)
+  int32_t pad;
 };
 static_assert(sizeof(RegOp) == 128 && sizeof(RegPhase) == 32 && sizeof(RegSeg) % 16 == 0, "read with wide scalar loads");
 

@@ -88,3 +88,40 @@ def test_gradients(n, layers, dense):
         e = np.linalg.norm(got - want) / max(np.linalg.norm(grad[b]) * np.sqrt(len(which) / k), 1.0)
         print(f"n={n} {dense} vector {b}: {e:.2e}", flush=True)
         assert e < TOL
+
+
+@pytest.mark.parametrize("n,layers", [(18, 3), (19, 2)])
+@pytest.mark.parametrize("dense", ["RX", "MIXER"])
+def test_gradients_of_x_generators(n, layers, dense):
+    """RY layers between those of X generators, so that every derivative differs from zero: gradients of
+    angles of each kind by the exact parameter shift, each kind's normwise, two parameter vectors."""
+    from paper_2108_06831_amd import Network, Observable, backward
+    rng = np.random.default_rng(11 * n + layers)
+    gates, kinds = [], []
+    for layer in range(layers):
+        for kind in ("RY", dense, "RZ"):
+            for q in range(n):
+                gates.append(workloads.Gate(kind, (q,), (0.0,), (len(kinds),)))
+                kinds.append(kind)
+        gates += [workloads.Gate("CZ", (q, (q + 1) % n)) for q in range(n)]
+    gates += [workloads.Gate("RY", (q,), (0.3 + 0.1 * q,)) for q in range(n)]
+    circ = workloads.Circuit(n, gates, len(kinds))
+    m, c = workloads.zz_ring_observable(n)
+    params = rng.uniform(0.2, np.pi - 0.2, size=(2, circ.n_params))
+    net = Network.from_circuit(circ)
+    path = net.plan("sequential")
+    value, grad = backward(net, path, params, Observable(m, c), batch=2)
+    value, grad = value.cpu().numpy(), grad.cpu().numpy()
+    for b in range(2):
+        assert abs(value[b] - oracle.circuit_expectation(circ, params[b], m, c)) < TOL * n
+        for kind in ("RY", dense, "RZ"):
+            mine = [i for i, x in enumerate(kinds) if x == kind]
+            which = [int(x) for x in rng.choice(mine, size=4, replace=False)]
+            g = oracle.param_shift_gradient(circ, params[b], m, c, which=which)
+            want = np.array([g[i] for i in which])
+            got = np.array([grad[b][i] for i in which])
+            size = np.linalg.norm(grad[b][mine]) * np.sqrt(len(which) / len(mine))
+            print(f"n={n} {dense} {kind} vector {b}: oracle norm {np.linalg.norm(want):.2f}, "
+                  f"error {np.linalg.norm(got - want):.2e}", flush=True)
+            assert np.linalg.norm(want) > 0.05  # (a term left out, or its factor wrong, would show)
+            assert np.linalg.norm(got - want) < TOL * max(size, 1.0)

@@ -1861,9 +1861,8 @@ int gemm_default_launch(GemmDesc (&gm)[2], int prec) {
         tile = three ? 6 : 2;
         split = sp;
       }
-      // BF16x3 takes the largest tile that fills the chip (1024 x 4096 x 128: 39.8 in 64 x 64, 35.4), if the product
-      // fills the tile (8 x 64 x 4096 x 512: 91 in 128 x 64, 69)
-      if (!c64 && kGemmTileM[tile] > g.M) tile = 2;
+      // BF16x3 takes the largest tile that fills the chip (1024 x 4096 x 128: 39.8 in 64 x 64, 35.4), also where the
+      // product has half the tile's rows (8 x 64 x 2048 x 1024: 109 in 64 x 64, 57 in 128 x 32 as in 64 x 32)
     }
     // ranges of K no shorter than 64 and no more than fill the chip: the sum over them is a launch and a pass of its
     // own (BF16x3 512 x 512 x 128: 16.9 in four, 16.1 in two, 14.3 whole)

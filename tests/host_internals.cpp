@@ -117,3 +117,51 @@ extern "C" int slot_table(const tn_network* net, int32_t* table, double* seconds
   if (table) std::copy(t.begin(), t.end(), table);
   return n;
 }
+
+// Default launch shape of a product whose indices lie in blocks (bit counts of its batch, m, n and k), and the shape
+// that follows from the sizes alone, in the orientation that runs.
+extern "C" void default_shape(int b, int m, int n, int k, int prec, int32_t* tile, int32_t* split, int32_t* by_blocks) {
+  GemmDesc g{};
+  g.batch = (int64_t)1 << b;
+  g.M = (int64_t)1 << m;
+  g.N = (int64_t)1 << n;
+  g.K = (int64_t)1 << k;
+  g.nbb = b;
+  g.nbm = m;
+  g.nbn = n;
+  g.nbk = k;
+  auto put = [](int8_t* pos, int count, int at) {
+    for (int j = 0; j < count; ++j) pos[j] = (int8_t)(at + j);
+  };
+  put(g.a_k, k, 0);
+  put(g.a_m, m, k);
+  put(g.a_b, b, k + m);
+  put(g.b_n, n, 0);
+  put(g.b_k, k, n);
+  put(g.b_b, b, n + k);
+  put(g.c_n, n, 0);
+  put(g.c_m, m, n);
+  put(g.c_b, b, n + m);
+  GemmDesc t = g;  // B^T A^T
+  std::swap(t.M, t.N);
+  std::swap(t.nbm, t.nbn);
+  std::copy(g.b_b, g.b_b + kGemmMaxBits, t.a_b);
+  std::copy(g.b_n, g.b_n + kGemmMaxBits, t.a_m);
+  std::copy(g.b_k, g.b_k + kGemmMaxBits, t.a_k);
+  std::copy(g.a_b, g.a_b + kGemmMaxBits, t.b_b);
+  std::copy(g.a_m, g.a_m + kGemmMaxBits, t.b_n);
+  std::copy(g.a_k, g.a_k + kGemmMaxBits, t.b_k);
+  std::swap_ranges(t.c_m, t.c_m + kGemmMaxBits, t.c_n);
+  GemmDesc gm[2] = {g, t};
+  for (GemmDesc& x : gm) {
+    int by, sp;
+    gemm_tile_by_blocks(x, &by, &sp);
+    x.max_split = sp;
+    if ((by != kGemmVector || x.K >= 256) && b + m + n + 3 <= 22 && k >= 6) x.max_split = kGemmMaxSplit;
+  }
+  const int o = gemm_default_launch(gm, prec);
+  int sp;
+  gemm_tile_by_blocks(gm[o], by_blocks, &sp);
+  *tile = gm[o].tile[prec];
+  *split = gm[o].split[prec];
+}

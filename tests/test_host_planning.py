@@ -125,3 +125,21 @@ def test_gradient_slots_take_linear_time(internals):
     best = min((internals.slot_table(net.handle, None, ctypes.byref(seconds)), seconds.value)[1] for _ in range(3))
     print(f"build {build:.3f} s, table {best:.4f} s")
     assert best < 0.25 * build
+
+
+def default_shape(internals, size, prec):
+    tile, split, by_blocks = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    internals.default_shape(*size, prec, ctypes.byref(tile), ctypes.byref(split), ctypes.byref(by_blocks))
+    return tile.value, split.value, by_blocks.value
+
+
+@pytest.mark.parametrize("size", [(3, 6, 11, 10), (3, 6, 11, 6), (5, 6, 9, 8), (7, 6, 7, 10), (3, 6, 12, 8)])
+def test_bf16x3_products_of_64_rows_fill_the_chip(internals, size):
+    """The widest tile that gives every compute unit two blocks, though half of its rows be empty, not
+    64 x 64 complex with half as many blocks: 8 x 64 x 2048 x 1024 takes 57 us so, 109 in those."""
+    tile, split, by_blocks = default_shape(internals, size, 1)
+    assert (tile, split) == (by_blocks, 1)
+    rows, columns = {0: (128, 64), 1: (128, 32), 3: (64, 32)}[tile]
+    m, n = 1 << size[1], 1 << size[2]
+    blocks = max(-(-p // rows) * -(-q // columns) for p, q in ((m, n), (n, m))) << size[0]
+    assert blocks >= 512

@@ -831,8 +831,11 @@ void find_seq_chain(const tn_network* net, tn_path* path, const std::vector<Loc>
   }
   if (ch.out.buf != BUF_WS) return;
   ch.last = ch.end == S;
-  // a state of several chunks: four of 2^13 rather than two of 2^14 (a pass is bound by the arithmetic of the compute
-  // units that have a chunk; 15 qubits, 12 layers, no fusion: 304 us in 2^14, 219 in 2^13, 220 in 2^12; BF16x3 800, 482)
+  // A state of several chunks: four of 2^13 rather than two of 2^14 (a pass is bound by the arithmetic of the compute
+  // units that have a chunk; 15 qubits, 12 layers, no fusion: 304 us in 2^14, 219 in 2^13, 220 in 2^12; BF16x3 800,
+  // 482).  A state that fits one chunk is one, so that an expectation or a gradient is one launch: 13 qubits 127 us
+  // against 173 in two chunks, BF16x3 342 and 349; 14 qubits 209 against 199, BF16x3 674 and 442 (its 14-bit kernel
+  // spills: 16 waves leave a thread 128 registers).
   const int lmax = ch.bits > kSeqMaxLocal ? kSeqMaxLocal - 1 : kSeqMaxLocal;
   if (!build_seq_program(ch.bits, items, lmax, false, &ch.prog)) return;
   path->seq = std::move(ch);
@@ -1795,8 +1798,9 @@ static int low_columns(const GemmDesc& g) {
   return c;
 }
 
-// The launch shape that the planner's model prices: by the sizes alone, so that a plan does not move with the rules
-// above (another plan is another order of sums, which a BF16x3 result shows).
+// The launch shape that follows from the sizes alone.  The planner's model prices it, so that a plan does not move with
+// the rules below (another plan is another order of sums, which a BF16x3 result shows), and complex64 products are
+// rounded no more than in it.
 static int model_shape(const GemmDesc (&gm)[2], int* tile, int* split) {
   int tl[2], sp[2];
   for (int o = 0; o < 2; ++o) {
